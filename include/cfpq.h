@@ -99,7 +99,7 @@ typedef struct {
  *   CFPQ_PATH  bits, mfma, fp4, rows or cols: used where options.path is
  *              AUTO (any other value is ignored); the bits are the same.
  *   CFPQ_LOG   a file name, or "-" for stderr: cfpq_closure appends JSON
- *              lines -- {"event": "loop", ...} per host-driven loop (loop,
+ *              lines -- {"event": "loop", ...} per loop that is not replayed (loop,
  *              rules_launched, changed nonterminals, products so far,
  *              host_ms), {"event": "replay", ...} per replay of captured
  *              loops, and {"event": "closure", ...} per call with its totals.
@@ -136,12 +136,18 @@ typedef struct {
                                 decisions, change flags, loop count) lives on the device and the
                                 host reads it back once per `capture` loops; 0 = host-driven
                                 loop with one read-back per loop.  Ignored when profile is set
-                                or the hybrid choice is in effect.  Default 8. */
+                                or the hybrid choice or the row sweeps are in effect.  Default 8. */
     int32_t hybrid;          /* CFPQ_HYBRID_AUTO (default): for padded sizes of at least 4096,
                                 each product of each loop picks the dense kernel, ROWS or COLS
                                 from the current number of set bits of its operands (a cost
                                 model; the bits are the same whichever runs).  The loop is then
-                                host-driven.  CFPQ_HYBRID_OFF: every product is dense. */
+                                host-driven.  With path AUTO, the in-place schedule, the dirty
+                                worklist, no profile, tile or warm start, 513 to 16384 nodes and
+                                at most 16 edges per padded row, the rules with an edge-matrix
+                                operand run as row sweeps at any of those sizes (counted as sparse
+                                products, delta ones after the first loop; sparse_bytes stays 0)
+                                and only rules over two growing operands as products.
+                                CFPQ_HYBRID_OFF: every product is dense. */
     int32_t warm_start;      /* 0: d_result is overwritten.  1: d_result already holds matrices in
                                 the bit layout that are subsets of R (for example a result of
                                 CFPQ_ENOTCONV, or R of the same graph with fewer edges); the edge
@@ -204,8 +210,8 @@ CFPQ_API cfpq_status cfpq_workspace_bytes(const cfpq_graph* graph, const cfpq_gr
  * Relational CFPQ closure (Algorithm 1, section 4.2).
  *   graph, grammar   inputs as above (validated on the host; with
  *                    edges_on_device = 1 the edge ids are checked by the
- *                    initialisation kernel and an out-of-range edge makes the
- *                    call return CFPQ_EINVAL before any product runs)
+ *                    initialisation kernel, which skips an out-of-range edge,
+ *                    and the call returns CFPQ_EINVAL)
  *   opt              NULL = cfpq_default_options
  *   stream           hipStream_t or NULL
  *   d_workspace      device scratch of at least cfpq_workspace_bytes bytes

@@ -180,6 +180,13 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
 // runs as a one-instance batch.
 size_t batch_workspace_one(const cfpq_graph& graph, const cfpq_grammar* grammar, const cfpq_options& o);
 
+// cfpq_closure and its workspace for a server lane (closure.hip): as with
+// path AUTO, whatever dense kernel o.path names; CFPQ_PATH is not read.  The
+// graph and grammar must be valid.
+size_t lane_workspace(const cfpq_graph* graph, const cfpq_grammar* grammar, const cfpq_options& o);
+cfpq_status lane_closure(const cfpq_graph* graph, const cfpq_grammar* grammar, const cfpq_options& o, void* stream,
+                         void* d_workspace, size_t workspace_bytes, uint64_t* d_result, cfpq_stats* stats);
+
 // ---- launchers (batch_engine.hip) ----
 hipError_t engine_zero(const EngineBuffers& b, const int32_t* ids, int32_t count, hipStream_t s);
 hipError_t engine_scatter(const EngineBuffers& b, const int32_t* ids, int32_t count, int64_t total_edges,

@@ -70,8 +70,12 @@ struct LoopState {
 // ---- kernels (each launcher only enqueues work on `s`) ----
 
 // Predicates: a launch given a non-null `go` does nothing unless *go == want
-// (read on the device, so the launch can sit in a captured graph).  For
-// launch_transpose, want = 0 means "unless *go != 0".
+// (read on the device, so the launch can sit in a captured graph), or with
+// want < 0 unless *go has a bit of the mask -want.  For launch_transpose,
+// want = 0 means "unless *go != 0".
+__device__ __forceinline__ bool launch_off(const int32_t* go, int32_t want) {
+    return go != nullptr && (want < 0 ? (*go & -want) == 0 : *go != want);
+}
 
 // Fill `words` uint64 with zero by a kernel (safe inside captured graphs).
 hipError_t launch_zero(uint64_t* p, size_t words, hipStream_t s, const int32_t* go = nullptr, int32_t want = 1);

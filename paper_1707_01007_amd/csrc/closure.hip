@@ -33,6 +33,8 @@
 
 #include "batch_engine.h"
 #include "cfpq_internal.h"
+#include "closure_common.h"
+#include "sweep.h"
 
 namespace cfpq {
 
@@ -88,6 +90,27 @@ cfpq_status validate_graph(const cfpq_graph* g, const cfpq_grammar* gr) {
     return CFPQ_OK;
 }
 
+int32_t choose_path(const Layout& L, int32_t requested, int32_t* tile) {
+    if (requested == CFPQ_PATH_BITS || reads_ct(requested)) return requested;
+    int32_t p = 0, t = 0;
+    if (tuned_choice(L, &p, &t)) {
+        if (tile) *tile = t;
+        return p;
+    }
+    return L.n <= kMfmaMaxNodes ? CFPQ_PATH_FP4 : CFPQ_PATH_BITS;
+}
+
+HybridModel make_model(const Layout& L, int32_t path, float tuned_ms) {
+    HybridModel m;
+    const double npad = static_cast<double>(L.npad);
+    // dense rates measured for the kernels at n = 16384 (bit-ops per us)
+    const double rate = path == CFPQ_PATH_FP4 ? 7.0e9 : path == CFPQ_PATH_MFMA ? 4.0e9 : 1.8e9;
+    m.dense_us = tuned_ms > 0 ? 1000.0 * tuned_ms : 5.0 + 2.0 * npad * npad * npad / rate;
+    m.row_us = static_cast<double>(L.W) * 8.0 / 12.0e6;              // gathered rows, mostly cache hits
+    m.mat_us = static_cast<double>(L.mat_words) * 8.0 / 5.0e6;       // streamed, ~5 TB/s
+    return m;
+}
+
 namespace {
 
 // CFPQ_PATH in the environment (bits, mfma, fp4, rows, cols) replaces the
@@ -111,47 +134,6 @@ cfpq_options resolve(const cfpq_options* opt) {
     if (opt) o = *opt;
     if (o.path == CFPQ_PATH_AUTO) o.path = env_path();
     return o;
-}
-
-// CFPQ_LOG in the environment names a file ("-": stderr) that receives JSON
-// lines: one per loop of the host-driven closure, one per replay of captured
-// loops, and one per closure call with its totals.  Each line is written
-// with one call and flushed, so calls on several threads do not interleave
-// within a line.
-struct JsonLog {
-    FILE* f = nullptr;
-    bool own = false;
-    JsonLog() {
-        const char* v = std::getenv("CFPQ_LOG");
-        if (!v || !*v) return;
-        if (std::strcmp(v, "-") == 0) {
-            f = stderr;
-        } else {
-            f = std::fopen(v, "a");
-            own = f != nullptr;
-        }
-    }
-    ~JsonLog() {
-        if (own) std::fclose(f);
-    }
-    JsonLog(const JsonLog&) = delete;
-    JsonLog& operator=(const JsonLog&) = delete;
-    void line(const std::string& text) {
-        if (!f) return;
-        std::fputs((text + "\n").c_str(), f);
-        std::fflush(f);
-    }
-};
-
-const char* path_name(int32_t path) {
-    switch (path) {
-        case CFPQ_PATH_BITS: return "bits";
-        case CFPQ_PATH_MFMA: return "mfma";
-        case CFPQ_PATH_FP4: return "fp4";
-        case CFPQ_PATH_ROWS: return "rows";
-        case CFPQ_PATH_COLS: return "cols";
-        default: return "auto";
-    }
 }
 
 // Workspace carve-up (all offsets 256-byte aligned).
@@ -188,29 +170,6 @@ bool resident_route(const cfpq_graph* g, const cfpq_grammar* gr, const cfpq_opti
     if (o.path != CFPQ_PATH_AUTO || o.profile || o.warm_start != 0 || g->n_nodes <= 0) return false;
     if (o.schedule == CFPQ_SCHEDULE_JACOBI) return resident_jacobi_fits(g->n_nodes, gr->n_nonterminals);
     return o.schedule == CFPQ_SCHEDULE_INPLACE && layout_for(g->n_nodes).npad <= kSmallMaxPad;
-}
-
-// AUTO: the autotuned kernel of the size bucket, else the fp4 MFMA while fp32 sums
-// are exact.  *tile is only changed for an autotuned choice.
-int32_t choose_path(const Layout& L, int32_t requested, int32_t* tile = nullptr) {
-    if (requested == CFPQ_PATH_BITS || reads_ct(requested)) return requested;
-    int32_t p = 0, t = 0;
-    if (tuned_choice(L, &p, &t)) {
-        if (tile) *tile = t;
-        return p;
-    }
-    return L.n <= kMfmaMaxNodes ? CFPQ_PATH_FP4 : CFPQ_PATH_BITS;
-}
-
-HybridModel make_model(const Layout& L, int32_t path, float tuned_ms) {
-    HybridModel m;
-    const double npad = static_cast<double>(L.npad);
-    // dense rates measured for the kernels at n = 16384 (bit-ops per us)
-    const double rate = path == CFPQ_PATH_FP4 ? 7.0e9 : path == CFPQ_PATH_MFMA ? 4.0e9 : 1.8e9;
-    m.dense_us = tuned_ms > 0 ? 1000.0 * tuned_ms : 5.0 + 2.0 * npad * npad * npad / rate;
-    m.row_us = static_cast<double>(L.W) * 8.0 / 12.0e6;              // gathered rows, mostly cache hits
-    m.mat_us = static_cast<double>(L.mat_words) * 8.0 / 5.0e6;       // streamed, ~5 TB/s
-    return m;
 }
 
 Plan make_plan(const cfpq_graph* g, const cfpq_grammar* gr, const cfpq_options& o) {
@@ -330,7 +289,7 @@ hipError_t aux_stream(hipStream_t* out) { return private_stream(1, out); }
 
 cfpq_status closure_impl(const cfpq_graph* graph, const cfpq_grammar* grammar, const cfpq_options* opt,
                          void* stream, void* d_workspace, size_t workspace_bytes, uint64_t* d_result,
-                         cfpq_stats* stats, bool no_alloc);
+                         cfpq_stats* stats, bool no_alloc, bool sweeps);
 
 // Workspace of cfpq_closure_static: a file-scope device array, so nothing is
 // allocated when the call runs.  Each GPU the library runs on holds its own
@@ -369,6 +328,24 @@ cfpq_status static_workspace(int dev, void** out, std::mutex** mu) {
     *out = w.ptr[dev];
     *mu = &w.dev_mu[dev];
     return CFPQ_OK;
+}
+
+// Workspace of a closure that is not resident.  Where the sweeps may run it
+// covers the product loops too: a graph with too many edges for the
+// adjacency lists takes those, and the size must not depend on the edges.
+static size_t loop_workspace(const cfpq_graph* graph, const cfpq_grammar* grammar, const cfpq_options& o, bool sweeps) {
+    const size_t loops = make_plan(graph, grammar, o).total;
+    return sweeps && sweep_route(graph, grammar, o) ? std::max(loops, sweep_workspace(graph, grammar)) : loops;
+}
+
+size_t lane_workspace(const cfpq_graph* graph, const cfpq_grammar* grammar, const cfpq_options& o) {
+    return loop_workspace(graph, grammar, o, true);
+}
+
+cfpq_status lane_closure(const cfpq_graph* graph, const cfpq_grammar* grammar, const cfpq_options& o, void* stream,
+                         void* d_workspace, size_t workspace_bytes, uint64_t* d_result, cfpq_stats* stats) {
+    clear_last_error();
+    return closure_impl(graph, grammar, &o, stream, d_workspace, workspace_bytes, d_result, stats, false, true);
 }
 
 }  // namespace cfpq
@@ -413,7 +390,7 @@ cfpq_status cfpq_workspace_bytes(const cfpq_graph* graph, const cfpq_grammar* gr
         return fail(CFPQ_EINVAL, "graph size out of range");
     const cfpq_options o = resolve(opt);
     *bytes = resident_route(graph, grammar, o) ? batch_workspace_one(*graph, grammar, o)
-                                               : make_plan(graph, grammar, o).total;
+                                               : loop_workspace(graph, grammar, o, o.path == CFPQ_PATH_AUTO);
     return CFPQ_OK;
 }
 
@@ -421,7 +398,8 @@ cfpq_status cfpq_closure(const cfpq_graph* graph, const cfpq_grammar* grammar, c
                          void* stream, void* d_workspace, size_t workspace_bytes, uint64_t* d_result,
                          cfpq_stats* stats) {
     g_last_error.clear();
-    return closure_impl(graph, grammar, opt, stream, d_workspace, workspace_bytes, d_result, stats, false);
+    return closure_impl(graph, grammar, opt, stream, d_workspace, workspace_bytes, d_result, stats, false,
+                        resolve(opt).path == CFPQ_PATH_AUTO);
 }
 
 cfpq_status cfpq_closure_static(const cfpq_graph* graph, const cfpq_grammar* grammar, const cfpq_options* opt,
@@ -451,7 +429,7 @@ cfpq_status cfpq_closure_static(const cfpq_graph* graph, const cfpq_grammar* gra
     st = static_workspace(dev, &ws, &dev_mu);
     if (st != CFPQ_OK) return st;
     std::lock_guard<std::mutex> lk(*dev_mu);  // calls on one device share its array: one at a time
-    return closure_impl(graph, grammar, &o, stream, ws, CFPQ_STATIC_WORKSPACE_BYTES, d_result, stats, true);
+    return closure_impl(graph, grammar, &o, stream, ws, CFPQ_STATIC_WORKSPACE_BYTES, d_result, stats, true, false);
 }
 
 }  // extern "C"
@@ -462,9 +440,10 @@ namespace cfpq {
 // calls that may allocate -- HIP events for the device time, graph capture,
 // the resident route's side stream and events -- are left out: the loop is
 // host-driven, device_ms is the host's wall time over the enqueued work.
+// sweeps: the row sweeps (sweep.h) may run the closure where they apply.
 cfpq_status closure_impl(const cfpq_graph* graph, const cfpq_grammar* grammar, const cfpq_options* opt,
                          void* stream, void* d_workspace, size_t workspace_bytes, uint64_t* d_result,
-                         cfpq_stats* stats, bool no_alloc) {
+                         cfpq_stats* stats, bool no_alloc, bool sweeps) {
     cfpq_status st = validate_grammar(grammar);
     if (st != CFPQ_OK) return st;
     st = validate_graph(graph, grammar);
@@ -507,6 +486,8 @@ cfpq_status closure_impl(const cfpq_graph* graph, const cfpq_grammar* grammar, c
         }
         return rs;
     }
+    if (sweeps && sweep_route(graph, grammar, o) && graph->n_edges <= sweep_max_edges(layout_for(graph->n_nodes)))
+        return closure_sweep(graph, grammar, o, stream, d_workspace, workspace_bytes, d_result, stats);
     const Plan p = make_plan(graph, grammar, o);
     if (p.total > 0 && !d_workspace) return fail(CFPQ_EINVAL, "d_workspace is NULL");
     if (workspace_bytes < p.total)

@@ -26,7 +26,7 @@ __global__ __launch_bounds__(256) void bits_product_kernel(const uint32_t* __res
                                                            const uint32_t* __restrict__ Cm,
                                                            uint32_t* Am, int W2, int kdw,
                                                            int32_t* changed, const int32_t* go, int32_t want) {
-    if (go != nullptr && *go != want) return;
+    if (launch_off(go, want)) return;
     const int strip = blockIdx.x;
     const int row = blockIdx.y * 256 + threadIdx.x;
     const uint32_t* brow = Bm + static_cast<size_t>(row) * W2;

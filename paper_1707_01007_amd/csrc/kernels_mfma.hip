@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void mfma_product_kernel(const uint32_t* __res
                                                            uint32_t* Am, int W2, int kchunks,
                                                            int tiles_dim, int grouped,
                                                            int32_t* changed, const int32_t* go, int32_t want) {
-    if (go != nullptr && *go != want) return;
+    if (launch_off(go, want)) return;
     int tile_i, tile_j;
     grouped_tile(blockIdx.x, tiles_dim, grouped, &tile_i, &tile_j);
 
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(256) void mfma4_persistent_kernel(const uint32_t* _
                                                                int W2, int kchunks, int tiles_dim, int grouped,
                                                                int32_t* changed, const int32_t* go, int32_t want) {
     using namespace mfma;
-    if (go != nullptr && *go != want) return;
+    if (launch_off(go, want)) return;
     const int total = tiles_dim * tiles_dim;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;

@@ -43,7 +43,7 @@ __global__ void init_scatter_kernel(const cfpq_edge* __restrict__ edges, int64_t
 __global__ __launch_bounds__(256) void transpose_kernel(const uint64_t* __restrict__ src,
                                                         uint64_t* __restrict__ dst, int64_t W,
                                                         const int32_t* __restrict__ pred, int32_t want) {
-    if (pred != nullptr && (want == 0 ? *pred == 0 : *pred != want)) return;
+    if (pred != nullptr && (want == 0 ? *pred == 0 : launch_off(pred, want))) return;
     const int lane = threadIdx.x & 63;
     const int64_t G = W >> 2;  // tiles per tile row
     const int64_t item = static_cast<int64_t>(blockIdx.x) * (blockDim.x >> 6) + (threadIdx.x >> 6);

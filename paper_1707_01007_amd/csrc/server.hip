@@ -235,9 +235,7 @@ size_t footprint_of(const Request& r) {
         cfpq_grammar gr;
         fill_lane_inputs(r, &g, &gr);
         const cfpq_options o = lane_options();
-        size_t bytes = 0;
-        if (cfpq_workspace_bytes(&g, &gr, &o, &bytes) != CFPQ_OK) return SIZE_MAX;
-        return bytes;
+        return lane_workspace(&g, &gr, o);
     }
     const size_t mat = static_cast<size_t>(r.L.mat_words) * 8;
     size_t f = align_up(mat * r.n_nt, 256);
@@ -565,7 +563,7 @@ void lane_main(cfpq_server* srv, int idx) {
         fill_lane_inputs(*r, &g, &gr);
         const cfpq_options o = lane_options();
         cfpq_stats st{};
-        const cfpq_status rc = cfpq_closure(&g, &gr, &o, ls, srv->arena_base + r->arena_off, r->footprint,
+        const cfpq_status rc = lane_closure(&g, &gr, o, ls, srv->arena_base + r->arena_off, r->footprint,
                                             r->d_result, &st);
         const double t = now_s();
         std::lock_guard<std::mutex> lk(srv->mu);
