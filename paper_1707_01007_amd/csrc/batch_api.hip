@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "batch_engine.h"
+#include "resident.h"
 
 namespace cfpq {
 namespace {
@@ -18,13 +19,16 @@ namespace {
 struct BatchPlan {
     int32_t n = 0;
     std::vector<SlotDesc> descs;
-    std::vector<int32_t> rules, modes, trans, term, large, small8, small16, all_ids;
+    std::vector<int32_t> rules, modes, trans, term, large, small8, small16;
+    std::vector<int32_t> sweep[kResidentClasses];  // slots of the resident sweep, by launch class
+    int32_t sweep_lds[kResidentClasses] = {};
+    std::vector<int32_t> all_ids;  // the slots whose matrices the batch initialises (not the resident sweep's)
     std::vector<int64_t> edge_begin;
     std::vector<size_t> edge_copy_off;  // per slot: byte offset in the edge region, or SIZE_MAX (device edges)
     int64_t total_edges = 0;
     int32_t large_rules = 0, large_trans = 0;
     size_t off_descs = 0, off_states = 0, off_rules = 0, off_go = 0, off_mode = 0, off_trans = 0, off_term = 0;
-    size_t off_jobs = 0, off_tjobs = 0, off_large = 0, off_small8 = 0, off_small16 = 0, off_all = 0;
+    size_t off_jobs = 0, off_tjobs = 0, off_large = 0, off_small8 = 0, off_small16 = 0, off_sweep = 0, off_all = 0;
     size_t off_edge_begin = 0, off_es = 0, off_edges = 0, off_tt = 0, total = 0;
     std::vector<size_t> tt_off;  // per slot: byte offset of its transposes (large) in the tt region
 };
@@ -39,7 +43,7 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
     p.descs.resize(n);
     p.edge_copy_off.assign(n, SIZE_MAX);
     p.tt_off.assign(n, 0);
-    p.edge_begin.assign(n + 1, 0);
+    p.edge_begin.assign(1, 0);
     size_t edge_bytes = 0, tt_bytes = 0;
     for (int32_t i = 0; i < n; ++i) {
         const cfpq_graph& g = inst[i].graph;
@@ -106,23 +110,37 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
         }
         p.trans.insert(p.trans.end(), tr.begin(), tr.end());
         p.modes.insert(p.modes.end(), md.begin(), md.end());
-        p.edge_begin[i + 1] = p.edge_begin[i] + g.n_edges;
         if (!g.edges_on_device && g.n_edges > 0) {
             p.edge_copy_off[i] = edge_bytes;
             edge_bytes += align_up(static_cast<size_t>(g.n_edges) * sizeof(cfpq_edge), 256);
         }
+        ResidentPlan rp;
         if (d.n_rules == 0) {
             // nothing to iterate: initialisation only
         } else if (d.kind == kSlotLarge) {
             p.large.push_back(i);
+        } else if (!d.jacobi && d.dirty &&
+                   resident_plan(gr->bin_rules, gr->n_bin_rules, gr->term_rules, gr->n_term_rules, d.n_nt, d.n,
+                                 d.n_edges, &rp)) {
+            // the kernel's grammar stands among the rule triples (in whole triples)
+            constexpr size_t kTriples = (sizeof(ResidentGrammar) + 11) / 12;
+            d.rule_off = static_cast<int32_t>(p.rules.size() / 3);
+            p.rules.resize(p.rules.size() + 3 * kTriples, 0);
+            std::memcpy(p.rules.data() + 3 * static_cast<size_t>(d.rule_off), &rp.g, sizeof(rp.g));
+            p.modes.resize(p.modes.size() + kTriples, kModeDense);
+            d.tile = rp.turned;
+            p.sweep[rp.cls].push_back(i);
+            p.sweep_lds[rp.cls] = std::max(p.sweep_lds[rp.cls], rp.lds);
+            continue;  // initialised by its workgroup
         } else if (d.W == 4) {
             p.small8.push_back(i);
         } else {
             p.small16.push_back(i);
         }
         p.all_ids.push_back(i);
+        p.edge_begin.push_back(p.edge_begin.back() + g.n_edges);
     }
-    p.total_edges = p.edge_begin[n];
+    p.total_edges = p.edge_begin.back();
     std::stable_sort(p.large.begin(), p.large.end(),
                      [&](int32_t a, int32_t b) { return p.descs[a].npad > p.descs[b].npad; });
     size_t off = 0;
@@ -144,8 +162,9 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
     p.off_large = take(4 * static_cast<size_t>(n));
     p.off_small8 = take(4 * static_cast<size_t>(n));
     p.off_small16 = take(4 * static_cast<size_t>(n));
-    p.off_all = take(4 * p.all_ids.size());
-    p.off_edge_begin = take(8 * p.edge_begin.size());
+    p.off_sweep = take(4 * static_cast<size_t>(n));
+    p.off_all = take(4 * static_cast<size_t>(n));
+    p.off_edge_begin = take(8 * (static_cast<size_t>(n) + 1));
     p.off_es = take(sizeof(EngineState));
     p.off_edges = take(edge_bytes);
     p.off_tt = take(tt_bytes);
@@ -428,6 +447,13 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
     put(p.off_large, p.large.data(), 4 * p.large.size());
     put(p.off_small8, p.small8.data(), 4 * p.small8.size());
     put(p.off_small16, p.small16.data(), 4 * p.small16.size());
+    {
+        size_t at = p.off_sweep;
+        for (const auto& v : p.sweep) {
+            put(at, v.data(), 4 * v.size());
+            at += 4 * v.size();
+        }
+    }
     put(p.off_all, p.all_ids.data(), 4 * p.all_ids.size());
     put(p.off_edge_begin, p.edge_begin.data(), 8 * p.edge_begin.size());
     EngineState es0;
@@ -446,21 +472,33 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
     CFPQ_HIP(hipEventRecord(ev0, s));
 
     // Matrix initialisation of every instance.
-    CFPQ_HIP(engine_zero(b, all_ids, n_instances, s));
+    const int32_t n_init = static_cast<int32_t>(p.all_ids.size());
+    CFPQ_HIP(engine_zero(b, all_ids, n_init, s));
     // Device edges with an id out of range are counted and skipped by the
     // scatter; the count is read with the final states (no round trip here).
-    CFPQ_HIP(engine_scatter(b, all_ids, n_instances, p.total_edges, s));
+    CFPQ_HIP(engine_scatter(b, all_ids, n_init, p.total_edges, s));
 
-    // Small instances: one resident workgroup each, on a side stream.
-    const bool any_small = !p.small8.empty() || !p.small16.empty();
-    hipStream_t side = nullptr;
-    if (any_small) {
+    // Small instances: one resident workgroup each, on a side stream beside
+    // the large ones (there being any); the longest launches first.
+    const bool any_small = p.all_ids.size() < static_cast<size_t>(n_instances) || !p.small8.empty() ||
+                           !p.small16.empty();
+    const bool beside = !p.large.empty();
+    hipStream_t side = s;
+    if (any_small && beside) {
         CFPQ_HIP(aux_stream(&side));
         CFPQ_HIP(hipEventRecord(fork, s));
         CFPQ_HIP(hipStreamWaitEvent(side, fork, 0));
-        CFPQ_HIP(engine_resident(b, b.small_ids, static_cast<int32_t>(p.small8.size()), 8, side));
+    }
+    if (any_small) {
+        for (int32_t cls : {5, 4, 2, 1, 3, 0}) {
+            size_t at = 0;
+            for (int32_t q = 0; q < cls; ++q) at += p.sweep[q].size();
+            CFPQ_HIP(resident_sweep(b, reinterpret_cast<int32_t*>(ws + p.off_sweep) + at,
+                                    static_cast<int32_t>(p.sweep[cls].size()), cls, p.sweep_lds[cls], side));
+        }
         CFPQ_HIP(engine_resident(b, small16_ids, static_cast<int32_t>(p.small16.size()), 16, side));
-        CFPQ_HIP(hipEventRecord(join, side));
+        CFPQ_HIP(engine_resident(b, b.small_ids, static_cast<int32_t>(p.small8.size()), 8, side));
+        if (beside) CFPQ_HIP(hipEventRecord(join, side));
     }
 
     // Large instances: captured loops over the shared work list.
@@ -518,7 +556,7 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
             if (hes[cur].running <= 0) break;
         }
     }
-    if (any_small) CFPQ_HIP(hipStreamWaitEvent(s, join, 0));
+    if (any_small && beside) CFPQ_HIP(hipStreamWaitEvent(s, join, 0));
     CFPQ_HIP(hipEventRecord(ev1, s));
     CFPQ_HIP(hipMemcpyAsync(hstates.data(), b.states, sizeof(SlotState) * hstates.size(), hipMemcpyDeviceToHost, s));
     CFPQ_HIP(hipStreamSynchronize(s));

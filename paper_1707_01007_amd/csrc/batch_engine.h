@@ -3,8 +3,9 @@
 //
 // Instances live in "slots" of a device table.  Two kinds:
 //  * small (padded side <= kSmallMaxPad): one workgroup runs the instance's
-//    whole fixpoint in a single resident kernel launch (VALU product with the
-//    right operand staged in LDS, change flags in LDS);
+//    whole fixpoint in a single resident kernel launch -- the resident sweep
+//    (resident.h), or for the Jacobi schedule and what the sweep does not take
+//    the resident product (VALU, right operand staged in LDS, flags in LDS);
 //  * large: every loop, a plan kernel turns the dirty rules of all running
 //    large slots into work lists -- fp4-MFMA tiles for dense rules (256 x 256
 //    per workgroup, or 128 x 128 per wavefront, by the slot's size bucket),
@@ -71,7 +72,8 @@ struct SlotDesc {
     int32_t kind;
     int32_t dirty;
     int32_t jacobi;  // small slots only: Algorithm 1's simultaneous step (see resident_jacobi_fits)
-    int32_t tile;    // large slots: 256 (workgroup tiles) or 128 (wavefront tiles) of the dense rules
+    int32_t tile;    // large slots: 256 (workgroup tiles) or 128 (wavefront tiles) of the dense rules; resident
+                     // sweep: 1 when its LDS holds transposed operands
 };
 
 struct SlotState {

@@ -35,6 +35,7 @@
 #include <vector>
 
 #include "batch_engine.h"
+#include "resident.h"
 
 namespace cfpq {
 namespace {
@@ -100,6 +101,8 @@ struct Request {
     bool small = false;  // resident route (batch tuning table at submit)
     int32_t tile = 256;  // tile route: 256 or 128 tiles
     bool lane = false;   // runs on a lane thread (hybrid closure)
+    bool swept = false;  // small: by the resident sweep, launched as planned
+    ResidentPlan sweep;
     int32_t n_right = 0;
     std::vector<int32_t> modes;  // per binary rule: engine product mode (large slots)
     size_t footprint = 0;
@@ -281,6 +284,8 @@ void fill_slot(cfpq_server* srv, Request& r, SlotDesc& d, std::vector<int32_t>& 
         rules[3 * q + 1] = r.bin[q].left;
         rules[3 * q + 2] = r.bin[q].right;
     }
+    static_assert(sizeof(ResidentGrammar) <= 4 * 3 * kSrvMaxRules, "stands where the slot's rule triples would");
+    if (r.swept) std::memcpy(rules.data(), &r.sweep.g, sizeof(r.sweep.g));
     modes.assign(kSrvMaxRules, kModeDense);
     std::copy(r.modes.begin(), r.modes.end(), modes.begin());
     d.trans_off = s * CFPQ_MAX_NONTERMINALS;
@@ -298,7 +303,7 @@ void fill_slot(cfpq_server* srv, Request& r, SlotDesc& d, std::vector<int32_t>& 
     std::vector<int32_t> fill(cnt.begin(), cnt.end() - 1);
     for (const auto& t : r.term) term[kSrvMaxTerminals + 1 + fill[t.terminal]++] = t.lhs;
     d.kind = r.small ? kSlotSmall : kSlotLarge;
-    d.tile = r.small ? 0 : r.tile;
+    d.tile = r.small ? (r.swept ? r.sweep.turned : 0) : r.tile;
 }
 
 // One turn of the worker.  Returns false on a device error (its message in
@@ -317,8 +322,13 @@ bool turn(cfpq_server* srv, std::vector<Request*>& admitted) {
     void* pin_states = static_cast<char*>(pin) + up_bytes;
     // ---- 2. initialise admitted requests ----
     if (!admitted.empty()) {
-        std::vector<int32_t> s8, s16;
-        int64_t edges_end = 0;
+        std::vector<int32_t> s8, s16, sweep[kResidentClasses];
+        int32_t sweep_lds[kResidentClasses] = {};
+        // the resident sweep initialises its own slots: the others come first
+        const auto own = std::stable_partition(admitted.begin(), admitted.end(),
+                                               [](const Request* r) { return !r->swept; });
+        const int32_t k_init = static_cast<int32_t>(own - admitted.begin());
+        int64_t edges_end = 0, edges_init = 0;
         const int32_t k = static_cast<int32_t>(admitted.size());
         std::vector<int32_t> rules, modes, trans, term;
         for (int32_t x = 0; x < k; ++x) {
@@ -334,6 +344,7 @@ bool turn(cfpq_server* srv, std::vector<Request*>& admitted) {
             st.fresh = 1;
             srv->hstates[r->slot] = st;
             edges_end += r->n_edges;
+            if (x < k_init) edges_init = edges_end;
             uint32_t* rec = up + static_cast<size_t>(x) * kUpWords;
             rec[0] = static_cast<uint32_t>(r->slot);
             rec[1] = static_cast<uint32_t>(edges_end & 0xFFFFFFFF);
@@ -344,19 +355,24 @@ bool turn(cfpq_server* srv, std::vector<Request*>& admitted) {
             std::memcpy(rec + kUpTrans, trans.data(), 4 * trans.size());
             std::memcpy(rec + kUpTerm, term.data(), 4 * term.size());
             std::memcpy(rec + kUpState, &st, sizeof(st));
-            if (d.n_rules > 0 && r->small) (d.W == 4 ? s8 : s16).push_back(r->slot);
+            if (x >= k_init) {
+                sweep[r->sweep.cls].push_back(r->slot);
+                sweep_lds[r->sweep.cls] = std::max(sweep_lds[r->sweep.cls], r->sweep.lds);
+            } else if (d.n_rules > 0 && r->small) {
+                (d.W == 4 ? s8 : s16).push_back(r->slot);
+            }
         }
         // every table of every admitted request in one copy and one launch
         SRV_HIP(hipMemcpyAsync(srv->upload, up, static_cast<size_t>(k) * kUpWords * 4, hipMemcpyHostToDevice, s));
         upload_slots_kernel<<<dim3(static_cast<unsigned>(k)), dim3(256), 0, s>>>(srv->upload, k, srv->b,
                                                                                  srv->ids_init);
         SRV_HIP(hipGetLastError());
-        SRV_HIP(engine_zero(srv->b, srv->ids_init, k, s));
+        SRV_HIP(engine_zero(srv->b, srv->ids_init, k_init, s));
         // Device edges with an id out of range are counted and skipped by the
         // scatter; the request runs on the rest and fails when it retires (the
         // count comes back with the states, no round trip here).
-        SRV_HIP(engine_scatter(srv->b, srv->ids_init, k, edges_end, s));
-        if (!s8.empty() || !s16.empty()) {
+        SRV_HIP(engine_scatter(srv->b, srv->ids_init, k_init, edges_init, s));
+        if (!s8.empty() || !s16.empty() || k_init < k) {
             // The slot list of a launch sits at one of 64 ring positions in
             // device memory; the batch that used the position before must have
             // finished reading it.
@@ -365,6 +381,11 @@ bool turn(cfpq_server* srv, std::vector<Request*>& admitted) {
             if (prev != srv->small_batches.end()) SRV_HIP(hipEventSynchronize(prev->second.done));
             std::vector<int32_t> both(s8);
             both.insert(both.end(), s16.begin(), s16.end());
+            size_t sweep_at[kResidentClasses];
+            for (int32_t c = 0; c < kResidentClasses; ++c) {
+                sweep_at[c] = both.size();
+                both.insert(both.end(), sweep[c].begin(), sweep[c].end());
+            }
             int32_t* list = srv->ids_small8 + (id % 64) * S;
             SRV_HIP(hipMemcpyAsync(list, both.data(), 4 * both.size(), hipMemcpyHostToDevice, s));
             SmallBatch sb;
@@ -374,8 +395,11 @@ bool turn(cfpq_server* srv, std::vector<Request*>& admitted) {
             SRV_HIP(hipEventRecord(ready, s));
             SRV_HIP(hipStreamWaitEvent(srv->side, ready, 0));
             (void)hipEventDestroy(ready);
-            SRV_HIP(engine_resident(srv->b, list, static_cast<int32_t>(s8.size()), 8, srv->side));
+            for (int32_t c : {5, 4, 2, 1, 3, 0})  // the longest launches first
+                SRV_HIP(resident_sweep(srv->b, list + sweep_at[c], static_cast<int32_t>(sweep[c].size()), c,
+                                       sweep_lds[c], srv->side));
             SRV_HIP(engine_resident(srv->b, list + s8.size(), static_cast<int32_t>(s16.size()), 16, srv->side));
+            SRV_HIP(engine_resident(srv->b, list, static_cast<int32_t>(s8.size()), 8, srv->side));
             SRV_HIP(hipEventRecord(sb.done, srv->side));
             sb.live = static_cast<int32_t>(both.size());
             for (int32_t q : both) srv->slot_req[q]->small_batch = id;
@@ -786,6 +810,8 @@ cfpq_status cfpq_server_submit(cfpq_server* srv, const cfpq_graph* graph, const 
     r->tile = rt.tile;
     r->lane = srv->cfg.hybrid_lanes > 0 && r->L.npad >= kHybridMinRows;
     const int32_t nb = static_cast<int32_t>(r->bin.size());
+    r->swept = r->small && resident_plan(r->bin.data(), nb, r->term.data(), static_cast<int32_t>(r->term.size()),
+                                         r->n_nt, r->n, r->n_edges, &r->sweep);
     r->modes.assign(nb, kModeDense);
     if (!r->small && !r->lane) {
         for (int32_t q = 0; q < nb; ++q) r->modes[q] = engine_rule_mode(r->bin.data(), nb, q, r->n_edges, r->L.npad);
