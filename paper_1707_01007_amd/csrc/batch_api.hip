@@ -114,6 +114,14 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
             p.edge_copy_off[i] = edge_bytes;
             edge_bytes += align_up(static_cast<size_t>(g.n_edges) * sizeof(cfpq_edge), 256);
         }
+        // room for the resident sweep's grammar among the rule triples (in whole
+        // triples), whatever route and schedule the instance takes
+        constexpr size_t kTriples = (sizeof(ResidentGrammar) + 11) / 12;
+        const size_t grammar_at = p.rules.size() / 3;
+        if (d.n_rules > 0 && L.npad <= kSmallMaxPad) {
+            p.rules.resize(p.rules.size() + 3 * kTriples, 0);
+            p.modes.resize(p.modes.size() + kTriples, kModeDense);
+        }
         ResidentPlan rp;
         if (d.n_rules == 0) {
             // nothing to iterate: initialisation only
@@ -122,12 +130,8 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
         } else if (!d.jacobi && d.dirty &&
                    resident_plan(gr->bin_rules, gr->n_bin_rules, gr->term_rules, gr->n_term_rules, d.n_nt, d.n,
                                  d.n_edges, &rp)) {
-            // the kernel's grammar stands among the rule triples (in whole triples)
-            constexpr size_t kTriples = (sizeof(ResidentGrammar) + 11) / 12;
-            d.rule_off = static_cast<int32_t>(p.rules.size() / 3);
-            p.rules.resize(p.rules.size() + 3 * kTriples, 0);
-            std::memcpy(p.rules.data() + 3 * static_cast<size_t>(d.rule_off), &rp.g, sizeof(rp.g));
-            p.modes.resize(p.modes.size() + kTriples, kModeDense);
+            d.rule_off = static_cast<int32_t>(grammar_at);
+            std::memcpy(p.rules.data() + 3 * grammar_at, &rp.g, sizeof(rp.g));
             d.tile = rp.turned;
             p.sweep[rp.cls].push_back(i);
             p.sweep_lds[rp.cls] = std::max(p.sweep_lds[rp.cls], rp.lds);
