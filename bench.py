@@ -258,23 +258,17 @@ def bench_hybrid(cfpq, torch, inst, edges, dense_out, args, dense_s):
                          "ms_per_closure": round(prof["sparse_ms"], 3)}}
 
 
-# VALU: 256 CUs x 64 lanes per clock x 2.4 GHz integer instructions.  A
-# 32-bit min-plus term needs at least 1.5 of them (one v_add_u32 per term, one
-# v_min3_u32 per two terms): 26.2 T terms/s.  The narrow kernel, which the
-# library runs while every length fits 14 bits (its first 14 steps: a step's
-# lengths are at most twice the last one's), takes two terms per
-# v_pk_add_u16 and v_pk_min_u16: one instruction per term, 39.3 T terms/s.
-PEAK_VALU_INT32_T = 256 * 64 * 2.4e9 / 1e12
-PEAK_MINPLUS_TERMS_T = PEAK_VALU_INT32_T / 1.5
-PEAK_MINPLUS_NARROW_TERMS_T = PEAK_VALU_INT32_T
-NARROW_MINPLUS_STEPS = 14
+# Min-plus terms a second.  While lengths are at most 16 the product runs on
+# the bf16 MFMA as powers of two, one multiply-add a term: half of 2.5 PFLOP/s.
+# Steps of longer lengths run on the VALU (one integer instruction a term in
+# 16-bit pairs, 39.3 T terms/s), so a closure with such steps stays well below.
+PEAK_MINPLUS_TERMS_T = 2500.0 / 2
 
 
 def bench_single_path(cfpq, torch, n=4096, steps=2):
     """Single-path lengths (section 5) on the ER Dyck recipe at n = 4096: time
-    per closure, and the min-plus kernel's rate in (i, j, k) terms against the
-    VALU roofline of the variant that ran (1.5 integer instructions per term at
-    least, or one with 16-bit pairs)."""
+    per closure, and the min-plus tile kernels' rate in (i, j, k) terms against
+    the bf16 MFMA roofline (one multiply-add a term)."""
     from workloads import configs
     inst = configs.config3(n)
     edges = torch.from_numpy(inst.edges).cuda()
@@ -287,17 +281,14 @@ def bench_single_path(cfpq, torch, n=4096, steps=2):
     t = (time.perf_counter() - t0) / steps
     st = res.stats
     achieved = st["minplus_terms"] / (st["product_ms"] / 1e3) / 1e12 if st["product_ms"] else 0.0
-    # every step of this closure ran the narrow kernel when it took at most 14
-    narrow = st["iterations"] <= NARROW_MINPLUS_STEPS
-    peak = PEAK_MINPLUS_NARROW_TERMS_T if narrow else PEAK_MINPLUS_TERMS_T
+    peak = PEAK_MINPLUS_TERMS_T
     print(f"[bench] single path n={n}: {t * 1e3:.1f} ms, {st['iterations']} loops, min-plus "
           f"{st['minplus_terms']:.3e} terms in {st['product_ms']:.1f} ms", file=sys.stderr, flush=True)
     return {"workload": inst.tag, "n": n, "ms_per_closure": round(t * 1e3, 3), "loops": st["iterations"],
             "minplus_terms": st["minplus_terms"], "minplus_ms": round(st["product_ms"], 3),
-            "roofline": {"bound": "alu", "kernel": "minplus_kernel<true>" if narrow else "minplus_kernel<false>",
+            "roofline": {"bound": "mfma", "kernel": "minplus_pow_kernel, minplus_kernel for lengths above 16",
                          "achieved": round(achieved, 2), "peak": round(peak, 1),
-                         "unit": ("T terms/s (16-bit add + min per (i, j, k), two per instruction)" if narrow
-                                  else "T terms/s (int32 add + min per (i, j, k))"),
+                         "unit": "T terms/s (one bf16 multiply-add per (i, j, k))",
                          "frac": round(achieved / peak, 4)}}
 
 

@@ -304,7 +304,9 @@ CFPQ_API cfpq_status cfpq_popcount(int32_t n_nodes, int32_t count, const uint64_
 CFPQ_API size_t cfpq_lengths_bytes(int32_t n_nodes, int32_t n_nonterminals);
 
 /* Workspace for cfpq_single_path: two more bit matrices per nonterminal
- * (the next step and the step's new cells), transposed right operands,
+ * (the next step and the step's new cells), transposed right operands, two
+ * bytes per cell of a matrix where a rule has two derived operands (those of
+ * a min-plus product on the matrix cores),
  * per-loop counts and 64 x 64 tile flags of the new cells (4 bytes per tile
  * and nonterminal), a column index (npad + 1 offsets, npad cursors, one row
  * id per edge) for each fixed sparse right operand, plus small tables. */

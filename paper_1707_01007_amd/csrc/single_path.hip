@@ -22,7 +22,8 @@
 //     (minplus_rows_kernel); one whose C is, C's columns through a column
 //     index built once (minplus_cols_kernel); the others take the row walk
 //     or minplus_kernel over the 64 x 64 output tiles that hold new cells of
-//     A (split along k when they are few), whichever a cost model from the
+//     A (split along k when they are few) -- while the lengths are at most 16
+//     minplus_pow_kernel on the matrix cores -- whichever a cost model from the
 //     counts prefers;
 //  4. X = Y.
 // Lengths are uint32 in cells of a |N| x npad x npad array (0 = absent); sums
@@ -283,6 +284,198 @@ __global__ __launch_bounds__(256) void minplus_kernel(const uint64_t* __restrict
     }
 }
 
+// ---- min-plus on the matrix cores, while every operand length is at most 16
+//
+// A length l becomes the power of two 2^(67 - 8 l), an absent cell 0.  A
+// product of two is 2^(134 - 8 s), s the sum of the lengths, so over 64 k the
+// sum of the products lies in [2^(134 - 8 s), 64 * 2^(134 - 8 s)], s being the
+// smallest sum: at most 6 of the 8 exponent steps to the next smaller sum are
+// used up, and the exponent alone gives s.  Powers of two, their products
+// (exponents -122 .. 118 for s = 32 .. 2) and every rounding of sums of positive
+// terms keep those bounds, so the lengths are exact.  Chunks of 64 k are
+// combined by a maximum: the larger sum has the smaller s.
+//
+// In bf16 such a power has no mantissa and, with an odd bias, an even biased
+// exponent, so its low byte is 0: the operands are kept as the high bytes
+// (length_bytes_kernel), a quarter of the uint32 lengths, and spread by one
+// v_perm_b32 per two cells on the way to LDS.
+constexpr int32_t kPowMaxLength = 16;
+constexpr int kPowStep = 8, kPowBias = 67;
+
+// The high byte of bf16 2^(kPowBias - kPowStep * l), 0 unless 1 <= l <= 16.
+__device__ __forceinline__ uint32_t power_byte(uint32_t l) {
+    return l - 1u < static_cast<uint32_t>(kPowMaxLength) ? (kPowBias + 127 - kPowStep * l) >> 1 : 0u;
+}
+
+// Operand bytes of one matrix of lengths, cells without the previous step's
+// bit X left out: rows[i][k] as it lies, cols[j][k] transposed (either may be
+// null).  One workgroup per 64 x 64 tile; thread t holds 16 cells of row t / 4.
+__global__ __launch_bounds__(256) void length_bytes_kernel(const uint32_t* __restrict__ L,
+                                                           const uint64_t* __restrict__ X, uint8_t* __restrict__ rows,
+                                                           uint8_t* __restrict__ cols, int64_t W, int64_t npad) {
+    __shared__ uint32_t tile[64][17];  // 64 bytes a row, padded
+    const int t = threadIdx.x;
+    const int64_t ti = blockIdx.x / W, tj = blockIdx.x % W;
+    const int r = t >> 2, c = (t & 3) * 16;
+    const int64_t i = ti * 64 + r;
+    const uint32_t bits = static_cast<uint32_t>(X[i * W + tj] >> c) & 0xFFFFu;
+    const uint4* src = reinterpret_cast<const uint4*>(L + i * npad + tj * 64 + c);
+    uint32_t out[4] = {0, 0, 0, 0};
+    if (bits != 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint4 v = src[q];
+            const uint32_t l[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                out[q] |= ((bits >> (4 * q + u)) & 1u ? power_byte(l[u]) : 0u) << (8 * u);
+        }
+    }
+    if (rows != nullptr)
+        *reinterpret_cast<uint4*>(rows + i * npad + tj * 64 + c) = make_uint4(out[0], out[1], out[2], out[3]);
+    if (cols == nullptr) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) tile[r][(t & 3) * 4 + q] = out[q];
+    __syncthreads();
+    // row j = t / 4 of the transpose, its bytes k = c .. c + 15
+    const uint8_t* tb = reinterpret_cast<const uint8_t*>(tile);
+    uint32_t o[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        o[q] = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) o[q] |= static_cast<uint32_t>(tb[(c + 4 * q + u) * 68 + r]) << (8 * u);
+    }
+    *reinterpret_cast<uint4*>(cols + (tj * 64 + r) * npad + ti * 64 + c) = make_uint4(o[0], o[1], o[2], o[3]);
+}
+
+// L_A = min(L_A, min-plus product) on the new cells, 128 x 128 cells a
+// workgroup: four wavefronts of 64 x 64 (2 x 2 blocks of 32 x 32), chunks of
+// 64 k staged in two LDS buffers, the next chunk's bytes loaded while one is
+// multiplied.  Workgroups without a new cell return at once.
+//
+// What bounds it: LDS reads (16 KiB a wavefront and chunk for 16 MFMAs, even
+// with the matrix pipe) and the operand bytes from L2.  A full product at
+// n = 4096 (6.9e10 terms) takes 260 us = 264 T terms/s; the VALU kernel took
+// 2750 us for the same step (25 T terms/s).  The closure of ER Dyck n = 4096
+// went from 9.7 to 4.5 ms with it and the column kernel below.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+constexpr int kPowTile = 128, kPowChunk = 64, kPowStride = kPowChunk + 8;  // LDS rows of 144 bytes: no bank conflicts
+
+__global__ __launch_bounds__(256) void minplus_pow_kernel(const uint8_t* __restrict__ B, const uint8_t* __restrict__ CT,
+                                                          const uint64_t* __restrict__ D, uint32_t* LA, int64_t W,
+                                                          int64_t npad, int32_t chunks,
+                                                          const int32_t* __restrict__ tflag,
+                                                          unsigned long long* cells) {
+    const int64_t side = npad / kPowTile;
+    const int64_t ti = blockIdx.x / side, tj = blockIdx.x % side;
+    const int32_t* f = tflag + ti * 2 * W + tj * 2;
+    if (!(f[0] | f[1] | f[W] | f[W + 1])) return;
+    __shared__ __align__(16) uint16_t As[2][kPowTile][kPowStride], Bs[2][kPowTile][kPowStride];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int g = lane >> 5, r32 = lane & 31;
+    const int wi = (wave >> 1) * 64, wj = (wave & 1) * 64;
+    // staging: thread t takes 32 bytes (half a row) of each operand
+    const int sr = t >> 1, sh = (t & 1) * 32;
+    const uint8_t* bp = B + (ti * kPowTile + sr) * npad + sh;
+    const uint8_t* cp = CT + (tj * kPowTile + sr) * npad + sh;
+    uint4 ab[2], cb[2];
+    auto load = [&](int c) {
+        const uint4* x = reinterpret_cast<const uint4*>(bp + static_cast<int64_t>(c) * kPowChunk);
+        const uint4* y = reinterpret_cast<const uint4*>(cp + static_cast<int64_t>(c) * kPowChunk);
+        ab[0] = x[0];
+        ab[1] = x[1];
+        cb[0] = y[0];
+        cb[1] = y[1];
+    };
+    // four bytes b0..b3 -> bf16 pairs (b0 << 8, b1 << 8), (b2 << 8, b3 << 8)
+    auto spread = [](uint32_t v, uint32_t* o) {
+        o[0] = __builtin_amdgcn_perm(v, v, 0x010C000Cu);
+        o[1] = __builtin_amdgcn_perm(v, v, 0x030C020Cu);
+    };
+    auto store = [&](uint16_t* row, const uint4 (&v)[2]) {
+        uint4* dst = reinterpret_cast<uint4*>(row + sh);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            uint32_t o[8];
+            spread(v[q].x, o);
+            spread(v[q].y, o + 2);
+            spread(v[q].z, o + 4);
+            spread(v[q].w, o + 6);
+            dst[2 * q] = make_uint4(o[0], o[1], o[2], o[3]);
+            dst[2 * q + 1] = make_uint4(o[4], o[5], o[6], o[7]);
+        }
+    };
+    f32x16 best[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) best[a][b][e] = 0.0f;
+    load(0);
+    store(As[0][sr], ab);
+    store(Bs[0][sr], cb);
+    __syncthreads();
+    for (int32_t c = 0; c < chunks; ++c) {
+        const int cur = c & 1;
+        const bool more = c + 1 < chunks;
+        if (more) load(c + 1);
+        f32x16 acc[2][2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.0f;
+#pragma unroll
+        for (int s = 0; s < kPowChunk / 16; ++s) {
+            bf16x8 af[2], bf[2];
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                af[a] = *reinterpret_cast<const bf16x8*>(&As[cur][wi + 32 * a + r32][16 * s + 8 * g]);
+                bf[a] = *reinterpret_cast<const bf16x8*>(&Bs[cur][wj + 32 * a + r32][16 * s + 8 * g]);
+            }
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[a], bf[b], acc[a][b], 0, 0, 0);
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) best[a][b][e] = fmaxf(best[a][b][e], acc[a][b][e]);
+        if (more) {
+            store(As[cur ^ 1][sr], ab);  // last read a barrier ago
+            store(Bs[cur ^ 1][sr], cb);
+        }
+        __syncthreads();
+    }
+    if (t == 0) atomicAdd(cells, static_cast<unsigned long long>(chunks) * kPowChunk * kPowTile * kPowTile);
+    // accumulator e of lane (g, r32): row 8 (e / 4) + 4 g + e % 4, column r32 of its block
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int64_t i = ti * kPowTile + wi + 32 * a + 8 * (e / 4) + 4 * g + (e % 4);
+            const int64_t jw = (tj * kPowTile + wj) / 64;
+            const uint64_t drow = D[i * W + jw];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const float v = best[a][b][e];
+                if (v <= 0.0f || !((drow >> (32 * b + r32)) & 1ull)) continue;
+                const int ex = static_cast<int>(__float_as_uint(v) >> 23) - 127;
+                const uint32_t s = static_cast<uint32_t>(2 * kPowBias - ex + kPowStep - 1) / kPowStep;
+                uint32_t* cell = LA + i * npad + jw * 64 + 32 * b + r32;
+                if (s < *cell) *cell = s;
+            }
+        }
+}
+
 // Row walk min-plus: L_A(i, j) = min over the set bits k of X_B's row i of
 // L_B(i, k) + L_C(k, j), for the new cells (i, j) where X_C(k, j) is set.
 // A work item is (row i, group of kGatherWords words of X_B's row): long rows
@@ -429,11 +622,64 @@ __global__ __launch_bounds__(256) void minplus_cols_kernel(const uint64_t* __res
     }
 }
 
+// The same, a workgroup a row: L_B's row (kInf where X_B is clear) is read once
+// into LDS, and each new cell takes the smallest entry of its column's list,
+// plus one -- a fixed matrix holds edges only, of length 1.  One coalesced
+// read of the row and LDS reads an edge, where the lanes above chase three
+// dependent loads per cell and edge (the densest step of ER Dyck n = 4096, 275
+// -> 96 us).  For rows that fit LDS, and steps with at
+// least kColsRowCells new cells a row on average (fewer do not repay reading
+// the row).
+constexpr int32_t kColsRowMax = 16384;
+constexpr unsigned long long kColsRowCells = 128;
+
+__global__ __launch_bounds__(256) void minplus_cols_row_kernel(const uint64_t* __restrict__ D,
+                                                               const uint64_t* __restrict__ XB,
+                                                               const int32_t* __restrict__ cptr,
+                                                               const int32_t* __restrict__ cidx, const uint32_t* LB,
+                                                               uint32_t* LA, int64_t W, int64_t npad, int32_t n) {
+    extern __shared__ uint32_t row[];
+    const int64_t i = blockIdx.x;
+    const uint64_t* drow = D + i * W;
+    const uint64_t* brow = XB + i * W;
+    bool any = false;
+    for (int64_t w = threadIdx.x; w < W; w += 256) any = any || drow[w] != 0;
+    if (!__syncthreads_or(any)) return;
+    const uint32_t* lb = LB + i * npad;
+    for (int32_t k = threadIdx.x; k < n; k += 256) row[k] = (brow[k >> 6] >> (k & 63)) & 1ull ? lb[k] : kInf;
+    __syncthreads();
+    uint32_t* la = LA + i * npad;
+    // four columns a step, so that their list lookups are in flight together
+    for (int32_t j0 = threadIdx.x; j0 < n; j0 += 1024) {
+        int32_t e[4], e1[4], k[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int32_t j = j0 + 256 * u;
+            const bool have = j < n && ((drow[j >> 6] >> (j & 63)) & 1ull);
+            e[u] = have ? cptr[j] : 0;
+            e1[u] = have ? cptr[j + 1] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) k[u] = e[u] < e1[u] ? cidx[e[u]] : 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (e[u] >= e1[u]) continue;
+            uint32_t best = row[k[u]];
+            for (int32_t q = e[u] + 1; q < e1[u]; ++q) best = min(best, row[cidx[q]]);
+            const int32_t j = j0 + 256 * u;
+            if (best < kInf - 1 && best + 1 < la[j]) la[j] = best + 1;
+        }
+    }
+}
+
 // Overflow check: a new cell that no rule gave a finite sum (still kInf)
 // has a length that did not fit (its Boolean product term exists, so some sum
 // was >= 2^31 - 1); it goes back to 0 (absent).
-__global__ void check_new_cells_kernel(const uint64_t* __restrict__ D, uint32_t* __restrict__ LA, int64_t W,
-                                       int64_t npad, int32_t* overflow) {
+// *longest gets the largest length of the others.
+__global__ __launch_bounds__(256) void check_new_cells_kernel(const uint64_t* __restrict__ D,
+                                                              uint32_t* __restrict__ LA, int64_t W, int64_t npad,
+                                                              int32_t* overflow, uint32_t* longest) {
+    uint32_t most = 0;
     for (int64_t w = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; w < npad * W;
          w += static_cast<int64_t>(gridDim.x) * blockDim.x) {
         uint64_t d = D[w];
@@ -443,12 +689,18 @@ __global__ void check_new_cells_kernel(const uint64_t* __restrict__ D, uint32_t*
             const int b = __ffsll(static_cast<unsigned long long>(d)) - 1;
             d &= d - 1;
             uint32_t* cell = LA + i * npad + j0 + b;
-            if (*cell >= kInf) {
+            const uint32_t l = *cell;
+            if (l >= kInf) {
                 *cell = 0;
                 atomicOr(overflow, 1);
+            } else {
+                most = max(most, l);
             }
         }
     }
+    for (int o = 32; o > 0; o >>= 1) most = max(most, static_cast<uint32_t>(__shfl_xor(static_cast<int>(most), o, 64)));
+    if ((threadIdx.x & 63) == 0 && most > __hip_atomic_load(longest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(longest, most);
 }
 
 // Tile kernel launch shape: split each active tile along k until about
@@ -475,7 +727,8 @@ struct SpPlan {
     int32_t n_right = 0, n_csc = 0;
     size_t off_edges = 0, off_term_off = 0, off_term_lhs = 0, off_flags = 0, off_bad = 0, off_second = 0,
            off_delta = 0, off_trans = 0, off_rowor = 0, off_csc = 0, csc_bytes = 0, off_csc_cursor = 0,
-           off_csc_idx = 0, off_tinfo = 0, tinfo_bytes = 0, off_tiles = 0, off_tflag = 0, total = 0;
+           off_csc_idx = 0, off_tinfo = 0, tinfo_bytes = 0, off_tiles = 0, off_tflag = 0, off_bytes = 0, total = 0;
+    bool any_tiles = false;  // a rule without a fixed operand: its min-plus may run on the matrix cores
 };
 
 SpPlan sp_plan(const cfpq_graph* g, const cfpq_grammar* gr) {
@@ -491,7 +744,7 @@ SpPlan sp_plan(const cfpq_graph* g, const cfpq_grammar* gr) {
     p.off_term_lhs = off;
     off += align_up(static_cast<size_t>(std::max(gr->n_term_rules, 1)) * 4, 256);
     p.off_flags = off;
-    off += align_up(static_cast<size_t>(p.n_nt) * 4 + 8, 256);
+    off += align_up(static_cast<size_t>(p.n_nt) * 4 + 12, 256);  // change flags, overflow, longest length
     p.off_bad = off;
     off += 256;
     p.off_second = off;  // Y
@@ -514,6 +767,7 @@ SpPlan sp_plan(const cfpq_graph* g, const cfpq_grammar* gr) {
             continue;
         }
         if (p.mfma && p.right_slot[br.right] < 0) p.right_slot[br.right] = p.n_right++;
+        if (!p.rows_left[br.right]) p.any_tiles = true;
         // min-plus through the column index of a fixed sparse right operand
         // (its cells come from edges, so at most n_edges of them)
         if (p.rows_left[br.right] && p.csc_slot[br.right] < 0 && g->n_edges < INT32_MAX)
@@ -535,6 +789,8 @@ SpPlan sp_plan(const cfpq_graph* g, const cfpq_grammar* gr) {
     p.off_tflag = p.off_tiles + align_up(static_cast<size_t>(p.n_nt) * 4, 256);
     p.tinfo_bytes = p.off_tflag + align_up(static_cast<size_t>(p.n_nt) * p.L.W * p.L.W * 4, 256);
     off += p.tinfo_bytes;
+    p.off_bytes = off;  // operand bytes of a min-plus product: the left one's rows, the right one's columns
+    if (p.any_tiles) off += 2 * static_cast<size_t>(p.L.npad) * static_cast<size_t>(p.L.npad);
     p.total = off;
     return p;
 }
@@ -598,6 +854,8 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
     auto* d_term_lhs = reinterpret_cast<int32_t*>(ws + p.off_term_lhs);
     auto* d_flags = reinterpret_cast<int32_t*>(ws + p.off_flags);
     auto* d_overflow = d_flags + n_nt;
+    auto* d_longest = reinterpret_cast<uint32_t*>(d_overflow + 1);
+    auto* d_bytes = reinterpret_cast<uint8_t*>(ws + p.off_bytes);
     auto* d_bad = reinterpret_cast<int32_t*>(ws + p.off_bad);
     uint64_t* X = d_result;
     uint64_t* Y = reinterpret_cast<uint64_t*>(ws + p.off_second);
@@ -629,7 +887,7 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
         d_edges = dst;
     }
     CFPQ_HIP(hipMemsetAsync(d_bad, 0, 16, s));
-    CFPQ_HIP(hipMemsetAsync(d_overflow, 0, 4, s));
+    CFPQ_HIP(hipMemsetAsync(d_overflow, 0, 8, s));
     CFPQ_HIP(hipEventRecord(ev0, s));
     CFPQ_HIP(launch_zero(X, mw * n_nt, s));
     CFPQ_HIP(launch_init_scatter(d_edges, graph->n_edges, d_term_off, d_term_lhs, grammar->n_terminals,
@@ -678,15 +936,15 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
     const int64_t cap = max_iters > 0 ? max_iters : nn * nn * n_nt + 1;
     const size_t lmat = static_cast<size_t>(L.npad) * static_cast<size_t>(L.npad);
     const int32_t kchunks = static_cast<int32_t>((L.n + 31) / 32);
-    std::vector<int32_t> flags(n_nt + 1, 0);
+    std::vector<int32_t> flags(n_nt + 2, 0);
     // a loop's read-backs land in pinned memory (new-cell counts, change flags
     // with the overflow flag, new-cell tiles) and one synchronisation waits
     // for all three
     void* pb = nullptr;
-    CFPQ_HIP(pinned_readback(static_cast<size_t>(n_nt) * 16 + 4, &pb));
+    CFPQ_HIP(pinned_readback(static_cast<size_t>(n_nt) * 16 + 8, &pb));
     auto* h_dcount = static_cast<unsigned long long*>(pb);
     auto* h_flags = reinterpret_cast<int32_t*>(h_dcount + n_nt);
-    int32_t* h_tiles = h_flags + n_nt + 1;
+    int32_t* h_tiles = h_flags + n_nt + 2;
     int64_t iters = 0, products = 0, sparse = 0;
     bool converged = grammar->n_bin_rules == 0 || graph->n_nodes == 0;
     int32_t overflow = 0;
@@ -703,6 +961,8 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
         CFPQ_HIP(hipMemsetAsync(d_flags, 0, static_cast<size_t>(n_nt) * 4, s));
         for (int32_t r = 0; r < grammar->n_bin_rules; ++r) {
             const auto& br = grammar->bin_rules[r];
+            // operands the previous step left as they were have been multiplied
+            if (iters > 0 && !flags[br.left] && !flags[br.right]) continue;
             int32_t* flag = d_flags + br.lhs;
             if (p.rows_left[br.left]) {
                 CFPQ_HIP(launch_rowor_product(X + br.left * mw, X + br.right * mw, Y + br.lhs * mw, L, flag, rowor_ws,
@@ -721,11 +981,11 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
         delta_all_kernel<<<dim3(grid_for(static_cast<int64_t>(mw), 256), static_cast<unsigned>(n_nt)), dim3(256), 0,
                            s>>>(Y, X, D, d_lengths, L.W, L.npad, d_dcount, d_tflag, d_tiles);
         CFPQ_HIP(hipGetLastError());
-        CFPQ_HIP(hipMemcpyAsync(h_flags, d_flags, static_cast<size_t>(n_nt + 1) * 4, hipMemcpyDeviceToHost, s));
+        CFPQ_HIP(hipMemcpyAsync(h_flags, d_flags, static_cast<size_t>(n_nt + 2) * 4, hipMemcpyDeviceToHost, s));
         CFPQ_HIP(hipMemcpyAsync(h_dcount, d_dcount, static_cast<size_t>(n_nt) * 8, hipMemcpyDeviceToHost, s));
         CFPQ_HIP(hipMemcpyAsync(h_tiles, d_tiles, static_cast<size_t>(n_nt) * 4, hipMemcpyDeviceToHost, s));
         CFPQ_HIP(hipStreamSynchronize(s));
-        std::copy(h_flags, h_flags + n_nt + 1, flags.begin());
+        std::copy(h_flags, h_flags + n_nt + 2, flags.begin());
         std::copy(h_dcount, h_dcount + n_nt, dcount.begin());
         std::copy(h_tiles, h_tiles + n_nt, tiles.begin());
         if (pending) {
@@ -750,8 +1010,18 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
         }
         // Min-plus kernel per rule.  A fixed sparse operand: row or column
         // gathers.  Otherwise the row gather when its estimated time is below
-        // the tile kernel's: about 10 ns per (row with new cells, set bit of
-        // X_B in it) pair against 20 T (i, j, k) terms/s over the active tiles.
+        // the tile kernels': about 10 ns per (row with new cells, set bit of
+        // X_B in it) pair, against 20 T (i, j, k) terms/s over the active tiles
+        // on the VALU or, while no operand length exceeds 16 (the longest so
+        // far was read back with the flags), the matrix cores' time.
+        const bool powers = flags[n_nt + 1] <= kPowMaxLength;
+        // 128 x 128 tiles, 2 T terms/s a workgroup and at best 500 over the
+        // chip, after a pass over the lengths (4 bytes a cell at 3 TB/s)
+        auto pow_ms = [&](int32_t active) {
+            const double wgs = std::min<double>(active, static_cast<double>(L.W) * L.W / 4);
+            const double cells = static_cast<double>(L.npad) * L.npad;
+            return std::max(kchunks * 524288.0 / 2e9, wgs * kchunks * 524288.0 / 5e11) + 0.02 + cells * 4 / 3e9;
+        };
         const int64_t gather_items = static_cast<int64_t>(L.n) * ((L.W + kGatherWords - 1) / kGatherWords);
         const unsigned gather_grid = static_cast<unsigned>(std::min<int64_t>((gather_items + 3) / 4, 2048));
         std::vector<char> on_tiles(grammar->n_bin_rules, 0);
@@ -765,8 +1035,9 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
                     std::min({n, static_cast<double>(dcount[br.lhs]), 64.0 * tiles[br.lhs]});
                 const double rows_ms = active_rows * static_cast<double>(xcount[br.left]) / n * 1e-5;
                 const double tile_ms = static_cast<double>(tiles[br.lhs]) * kchunks * 131072.0 / 2e10;
-                rows = rows_ms < tile_ms;
-                on_tiles[r] = rows ? 0 : 1;
+                const bool pow = powers && pow_ms(tiles[br.lhs]) < tile_ms;
+                rows = rows_ms < (pow ? pow_ms(tiles[br.lhs]) : tile_ms);
+                on_tiles[r] = rows ? 0 : pow ? 2 : 1;
             }
             if (rows) {
                 minplus_rows_kernel<<<dim3(gather_grid), dim3(256), 0, s>>>(
@@ -774,6 +1045,15 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
                     d_lengths + br.right * lmat, d_lengths + br.lhs * lmat, L.W, L.npad, L.n);
             } else if (p.csc_slot[br.right] >= 0) {
                 const char* base = ws + p.off_csc + p.csc_bytes * p.csc_slot[br.right];
+                if (L.n <= kColsRowMax && dcount[br.lhs] >= kColsRowCells * L.n) {
+                    minplus_cols_row_kernel<<<dim3(static_cast<unsigned>(L.n)), dim3(256),
+                                              static_cast<size_t>(L.n) * 4, s>>>(
+                        D + br.lhs * mw, X + br.left * mw, reinterpret_cast<const int32_t*>(base),
+                        reinterpret_cast<const int32_t*>(base + p.off_csc_idx), d_lengths + br.left * lmat,
+                        d_lengths + br.lhs * lmat, L.W, L.npad, L.n);
+                    CFPQ_HIP(hipGetLastError());
+                    continue;
+                }
                 minplus_cols_kernel<<<dim3(gather_grid), dim3(256), 0, s>>>(
                     D + br.lhs * mw, X + br.left * mw, reinterpret_cast<const int32_t*>(base),
                     reinterpret_cast<const int32_t*>(base + p.off_csc_idx), d_lengths + br.left * lmat,
@@ -791,6 +1071,23 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
             const auto& br = grammar->bin_rules[r];
             if (!on_tiles[r]) continue;
             const int64_t all_tiles = L.W * L.W;
+            if (on_tiles[r] == 2) {
+                uint8_t* rows_b = d_bytes;
+                uint8_t* cols_b = d_bytes + lmat;
+                const bool same = br.left == br.right;
+                const dim3 bgrid(static_cast<unsigned>(all_tiles));
+                length_bytes_kernel<<<bgrid, dim3(256), 0, s>>>(d_lengths + br.left * lmat, X + br.left * mw, rows_b,
+                                                               same ? cols_b : nullptr, L.W, L.npad);
+                if (!same)
+                    length_bytes_kernel<<<bgrid, dim3(256), 0, s>>>(d_lengths + br.right * lmat, X + br.right * mw,
+                                                                   nullptr, cols_b, L.W, L.npad);
+                const int64_t side = L.npad / kPowTile;
+                minplus_pow_kernel<<<dim3(static_cast<unsigned>(side * side)), dim3(256), 0, s>>>(
+                    rows_b, cols_b, D + br.lhs * mw, d_lengths + br.lhs * lmat, L.W, L.npad,
+                    static_cast<int32_t>((L.n + kPowChunk - 1) / kPowChunk), d_tflag + br.lhs * all_tiles, d_cells);
+                CFPQ_HIP(hipGetLastError());
+                continue;
+            }
             int64_t ksplit = std::max<int64_t>(1, (kTileTarget + tiles[br.lhs] - 1) / std::max(tiles[br.lhs], 1));
             ksplit = std::min<int64_t>({ksplit, kMaxSplit, std::max<int64_t>(1, kchunks / 2),
                                         std::max<int64_t>(1, kMaxTileGrid / all_tiles)});
@@ -814,7 +1111,7 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
         for (int32_t a = 0; a < n_nt; ++a) {
             if (!flags[a]) continue;
             check_new_cells_kernel<<<dim3(grid_for(static_cast<int64_t>(mw), 4096)), dim3(256), 0, s>>>(
-                D + a * mw, d_lengths + a * lmat, L.W, L.npad, d_overflow);
+                D + a * mw, d_lengths + a * lmat, L.W, L.npad, d_overflow, d_longest);
             CFPQ_HIP(hipGetLastError());
             CFPQ_HIP(hipMemcpyAsync(X + a * mw, Y + a * mw, mw * 8, hipMemcpyDeviceToDevice, s));
         }
