@@ -365,7 +365,9 @@ typedef struct {
  * scratch matrices when some rule has k >= 2, two more when some conjunct
  * runs as COLS, plus one matrix per dense conjunct B C that occurs in more
  * than one rule: its product is computed once per loop and read by every
- * use). */
+ * use).  Where the one-conjunct rules are closed first, below: the larger of
+ * that closure's workspace and one matrix per distinct conjunct of the other
+ * rules, with the transposes they read. */
 CFPQ_API cfpq_status cfpq_conjunctive_workspace_bytes(const cfpq_graph* graph, const cfpq_grammar* grammar,
                                                       int32_t n_conj_rules, const cfpq_conj_rule* conj_rules,
                                                       const cfpq_options* opt, size_t* bytes);
@@ -381,6 +383,12 @@ CFPQ_API cfpq_status cfpq_conjunctive_workspace_bytes(const cfpq_graph* graph, c
  * stats.sparse_products, not in bitops); OFF keeps every product dense;
  * capture and profile are ignored (host-driven loop).  d_result, stream,
  * workspace, stats and the return codes as for cfpq_closure.
+ *
+ * With path AUTO, the in-place schedule, hybrid AUTO, the dirty worklist, no
+ * tile and no max_iters, at most 16384 nodes, and no rule that reads the head
+ * of a rule with k >= 2, the one-conjunct rules are closed first, as
+ * cfpq_closure does with its default options (environment included), and the
+ * other rules run once, counted as one more loop.
  */
 CFPQ_API cfpq_status cfpq_conjunctive_closure(const cfpq_graph* graph, const cfpq_grammar* grammar,
                                               int32_t n_conj_rules, const cfpq_conj_rule* conj_rules,

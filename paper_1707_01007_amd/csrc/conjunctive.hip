@@ -16,6 +16,13 @@
 // AUTO, a conjunct whose left operand heads no rule (its matrix is fixed by
 // the edges) runs as a ROWS product when the graph has at most npad^2 / 16
 // edges: the rows of C at the set bits of each row of that sparse matrix.
+//
+// Where no rule reads the head of a rule of several conjuncts (Dyck conjoined
+// with a^n b^n at the start symbol), those rules cannot feed the fixpoint: the
+// one-conjunct rules are closed first, by cfpq_closure's own routes, and then
+// every distinct conjunct is multiplied once and one kernel forms all heads
+// (CjPlan::staged).  ER n = 8192 with that grammar: 7.35 ms as a loop over all
+// rules (186 products of 17 loops), 1.88 ms staged.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -65,6 +72,49 @@ __global__ __launch_bounds__(256) void or_and_into_kernel(uint64_t* A, uint64_t*
     if (__syncthreads_or(ch) && threadIdx.x == 0) raise_flag(changed);
 }
 
+// T_A |= OR over A's rules of (AND of the rule's conjunct products), for every
+// head (grid y) at once: each product is read once however many rules use it.
+// Bound by the bytes of the products and heads (four products of 8 MiB and one
+// head: 14 us, where a pass a rule took 6 times 8 us).
+constexpr int kStagedParts = 16, kStagedRules = 64;
+struct StagedRules {
+    int32_t head[kStagedRules];        // of each entry of begin
+    int32_t begin[kStagedRules + 1];   // first rule of the head
+    uint32_t parts[kStagedRules];      // products of the rule
+};
+
+__global__ __launch_bounds__(256) void combine_kernel(uint64_t* T, const uint64_t* __restrict__ M, int64_t words,
+                                                      StagedRules r) {
+    const int32_t r0 = r.begin[blockIdx.y], r1 = r.begin[blockIdx.y + 1];
+    uint32_t used = 0;
+    for (int32_t k = r0; k < r1; ++k) used |= r.parts[k];
+    uint64_t* A = T + r.head[blockIdx.y] * words;
+    for (int64_t w = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * 2; w < words;
+         w += static_cast<int64_t>(gridDim.x) * 512) {
+        ulonglong2 m[kStagedParts];
+#pragma unroll
+        for (int q = 0; q < kStagedParts; ++q)
+            if ((used >> q) & 1u) m[q] = *reinterpret_cast<const ulonglong2*>(M + q * words + w);
+        ulonglong2 sum = make_ulonglong2(0, 0);
+        for (int32_t k = r0; k < r1; ++k) {
+            const uint32_t parts = r.parts[k];
+            ulonglong2 v = make_ulonglong2(~0ull, ~0ull);
+#pragma unroll
+            for (int q = 0; q < kStagedParts; ++q)
+                if ((parts >> q) & 1u) {
+                    v.x &= m[q].x;
+                    v.y &= m[q].y;
+                }
+            sum.x |= v.x;
+            sum.y |= v.y;
+        }
+        if ((sum.x | sum.y) == 0) continue;
+        ulonglong2* d = reinterpret_cast<ulonglong2*>(A + w);
+        const ulonglong2 old = *d;
+        *d = make_ulonglong2(old.x | sum.x, old.y | sum.y);
+    }
+}
+
 unsigned grid_for(int64_t words) {
     return static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>((words + 255) / 256, 4096)));
 }
@@ -84,7 +134,12 @@ struct CjPlan {
     bool any_rows = false, any_cols = false;  // ROWS conjuncts; COLS conjuncts (a fixed sparse right operand)
     // dense conjuncts B C that occur more than once in the grammar: each is
     // multiplied once per loop into its own matrix, read by every use
+    // (staged: every distinct conjunct of the late rules)
     std::vector<std::pair<int32_t, int32_t>> shared;
+    bool staged = false;
+    std::vector<cfpq_bin_rule> early;  // staged: the one-conjunct rules
+    StagedRules late{};                // and the others, by head
+    int32_t n_late_heads = 0;
     size_t off_edges = 0, off_term_off = 0, off_term_lhs = 0, off_flags = 0, off_bad = 0, off_second = 0,
            off_trans = 0, off_q = 0, off_r = 0, off_rowor = 0, off_shared = 0, off_pt = 0, off_bt = 0, total = 0;
 
@@ -94,6 +149,63 @@ struct CjPlan {
         return -1;
     }
 };
+
+// Largest graph of the staged route: cfpq_closure's row sweeps end here.
+// Beyond, its loops keep up to three more matrices a nonterminal, which the
+// loop below does without; there they would be gigabytes.
+constexpr int32_t kStagedMaxNodes = 16384;
+
+// Fills p->early and p->late where the staged route may run: the default
+// options only (whoever names a kernel, a schedule or a loop cap gets the loop
+// over all rules), no rule reads the head of a rule of several conjuncts, and
+// the tables of combine_kernel hold those rules.
+void stage_rules(const std::vector<Rule>& rules, const cfpq_options& o, CjPlan* p, std::vector<Rule>* late) {
+    if (o.path != CFPQ_PATH_AUTO || o.schedule != CFPQ_SCHEDULE_INPLACE || o.hybrid != CFPQ_HYBRID_AUTO ||
+        !o.dirty_worklist || o.tile != 0 || o.max_iters != 0 || p->L.n <= 0 || p->L.n > kStagedMaxNodes)
+        return;
+    std::vector<char> read(p->n_nt, 0);
+    for (const Rule& r : rules)
+        for (const auto& pc : r.parts) read[pc.first] = read[pc.second] = 1;
+    std::vector<std::pair<int32_t, int32_t>> parts;
+    for (const Rule& r : rules) {
+        if (r.parts.size() == 1) {
+            p->early.push_back({r.lhs, r.parts[0].first, r.parts[0].second});
+            continue;
+        }
+        if (read[r.lhs]) return;
+        late->push_back(r);
+        for (const auto& pc : r.parts)
+            if (std::find(parts.begin(), parts.end(), pc) == parts.end()) parts.push_back(pc);
+    }
+    if (late->empty() || late->size() > kStagedRules || parts.size() > kStagedParts) return;
+    std::stable_sort(late->begin(), late->end(), [](const Rule& a, const Rule& b) { return a.lhs < b.lhs; });
+    for (size_t k = 0; k < late->size(); ++k) {
+        const Rule& r = (*late)[k];
+        if (k == 0 || r.lhs != (*late)[k - 1].lhs) {
+            p->late.head[p->n_late_heads] = r.lhs;
+            p->late.begin[p->n_late_heads++] = static_cast<int32_t>(k);
+        }
+        for (const auto& pc : r.parts)
+            p->late.parts[k] |= 1u << (std::find(parts.begin(), parts.end(), pc) - parts.begin());
+    }
+    p->late.begin[p->n_late_heads] = static_cast<int32_t>(late->size());
+    p->shared = std::move(parts);
+    p->staged = true;
+}
+
+// The grammar of the one-conjunct rules.
+cfpq_grammar early_grammar(const cfpq_grammar* gr, const CjPlan& p) {
+    cfpq_grammar g = *gr;
+    g.n_bin_rules = static_cast<int32_t>(p.early.size());
+    g.bin_rules = p.early.data();
+    return g;
+}
+
+cfpq_options early_options() {
+    cfpq_options o;
+    cfpq_default_options(&o);
+    return o;
+}
 
 cfpq_status collect_rules(const cfpq_grammar* gr, int32_t n_conj, const cfpq_conj_rule* conj,
                           std::vector<Rule>* out) {
@@ -120,7 +232,7 @@ cfpq_status collect_rules(const cfpq_grammar* gr, int32_t n_conj, const cfpq_con
     return CFPQ_OK;
 }
 
-CjPlan cj_plan(const cfpq_graph* g, const cfpq_grammar* gr, const std::vector<Rule>& rules, const cfpq_options& o) {
+CjPlan cj_plan(const cfpq_graph* g, const cfpq_grammar* gr, const std::vector<Rule>& all, const cfpq_options& o) {
     CjPlan p;
     p.L = layout_for(g->n_nodes);
     p.n_nt = gr->n_nonterminals;
@@ -132,11 +244,14 @@ CjPlan cj_plan(const cfpq_graph* g, const cfpq_grammar* gr, const std::vector<Ru
     p.rows_left.assign(p.n_nt, 0);
     if (o.hybrid == CFPQ_HYBRID_AUTO && g->n_edges <= p.L.npad * p.L.npad / 16) {
         std::vector<char> heads(p.n_nt, 0);
-        for (const Rule& r : rules) heads[r.lhs] = 1;
+        for (const Rule& r : all) heads[r.lhs] = 1;
         for (int32_t a = 0; a < p.n_nt; ++a) p.rows_left[a] = heads[a] ? 0 : 1;
     }
+    std::vector<Rule> late;
+    stage_rules(all, o, &p, &late);
+    const std::vector<Rule>& rules = p.staged ? late : all;  // the rules whose conjuncts are multiplied here
     for (const Rule& r : rules) {
-        if (r.parts.size() > 1) p.temps = true;
+        if (r.parts.size() > 1 && !p.staged) p.temps = true;
         for (const auto& pc : r.parts) {
             if (p.rows_left[pc.first]) {
                 p.any_rows = true;
@@ -174,7 +289,7 @@ CjPlan cj_plan(const cfpq_graph* g, const cfpq_grammar* gr, const std::vector<Ru
     p.off_pt = off;  // COLS: the product's transpose, and B^T when B is kept no transpose of
     if (p.any_cols) off += 2 * mat;
     p.off_bt = p.off_pt + mat;
-    {
+    if (!p.staged) {
         std::vector<std::pair<int32_t, int32_t>> seen;
         for (const Rule& r : rules)
             for (const auto& pc : r.parts) {
@@ -188,6 +303,12 @@ CjPlan cj_plan(const cfpq_graph* g, const cfpq_grammar* gr, const std::vector<Ru
     }
     p.off_shared = off;
     off += mat * p.shared.size();
+    if (p.staged) {  // the early closure is done before any of this is written
+        const cfpq_grammar eg = early_grammar(gr, p);
+        const cfpq_options eo = early_options();
+        size_t bytes = 0;
+        if (cfpq_workspace_bytes(g, &eg, &eo, &bytes) == CFPQ_OK) off = std::max(off, bytes);
+    }
     p.total = off;
     return p;
 }
@@ -287,6 +408,7 @@ cfpq_status cfpq_conjunctive_closure(const cfpq_graph* graph, const cfpq_grammar
     uint64_t* SH = reinterpret_cast<uint64_t*>(ws + p.off_shared);
     std::vector<char> shared_ready(p.shared.size(), 0);
     const cfpq_edge* d_edges = graph->edges;
+    cfpq_stats early{};
 
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     CFPQ_HIP(hipEventCreate(&ev0));
@@ -298,24 +420,31 @@ cfpq_status cfpq_conjunctive_closure(const cfpq_graph* graph, const cfpq_grammar
             (void)hipEventDestroy(b);
         }
     } guard{ev0, ev1};
-    CFPQ_HIP(hipMemcpyAsync(d_term_off, term_off.data(), term_off.size() * 4, hipMemcpyHostToDevice, s));
-    CFPQ_HIP(hipMemcpyAsync(d_term_lhs, term_lhs.data(), term_lhs.size() * 4, hipMemcpyHostToDevice, s));
-    if (!graph->edges_on_device && graph->n_edges > 0) {
-        auto* dst = reinterpret_cast<cfpq_edge*>(ws + p.off_edges);
-        CFPQ_HIP(hipMemcpyAsync(dst, graph->edges, static_cast<size_t>(graph->n_edges) * sizeof(cfpq_edge),
-                                hipMemcpyHostToDevice, s));
-        d_edges = dst;
-    }
-    CFPQ_HIP(hipMemsetAsync(d_bad, 0, 4, s));
     CFPQ_HIP(hipEventRecord(ev0, s));
-    CFPQ_HIP(launch_zero(X, mw * n_nt, s));
-    CFPQ_HIP(launch_init_scatter(d_edges, graph->n_edges, d_term_off, d_term_lhs, grammar->n_terminals,
-                                 graph->n_nodes, X, L, d_bad, s));
-    if (graph->edges_on_device) {
-        int32_t bad = 0;
-        CFPQ_HIP(hipMemcpyAsync(&bad, d_bad, 4, hipMemcpyDeviceToHost, s));
-        CFPQ_HIP(hipStreamSynchronize(s));
-        if (bad) return fail(CFPQ_EINVAL, std::to_string(bad) + " device edges have an id out of range");
+    if (p.staged) {
+        const cfpq_grammar eg = early_grammar(grammar, p);
+        const cfpq_options eo = early_options();
+        st = cfpq_closure(graph, &eg, &eo, stream, d_workspace, workspace_bytes, d_result, &early);
+        if (st != CFPQ_OK) return st;
+    } else {
+        CFPQ_HIP(hipMemcpyAsync(d_term_off, term_off.data(), term_off.size() * 4, hipMemcpyHostToDevice, s));
+        CFPQ_HIP(hipMemcpyAsync(d_term_lhs, term_lhs.data(), term_lhs.size() * 4, hipMemcpyHostToDevice, s));
+        if (!graph->edges_on_device && graph->n_edges > 0) {
+            auto* dst = reinterpret_cast<cfpq_edge*>(ws + p.off_edges);
+            CFPQ_HIP(hipMemcpyAsync(dst, graph->edges, static_cast<size_t>(graph->n_edges) * sizeof(cfpq_edge),
+                                    hipMemcpyHostToDevice, s));
+            d_edges = dst;
+        }
+        CFPQ_HIP(hipMemsetAsync(d_bad, 0, 4, s));
+        CFPQ_HIP(launch_zero(X, mw * n_nt, s));
+        CFPQ_HIP(launch_init_scatter(d_edges, graph->n_edges, d_term_off, d_term_lhs, grammar->n_terminals,
+                                     graph->n_nodes, X, L, d_bad, s));
+        if (graph->edges_on_device) {
+            int32_t bad = 0;
+            CFPQ_HIP(hipMemcpyAsync(&bad, d_bad, 4, hipMemcpyDeviceToHost, s));
+            CFPQ_HIP(hipStreamSynchronize(s));
+            if (bad) return fail(CFPQ_EINVAL, std::to_string(bad) + " device edges have an id out of range");
+        }
     }
     if (p.jacobi) CFPQ_HIP(hipMemcpyAsync(Y, X, mw * 8 * n_nt, hipMemcpyDeviceToDevice, s));
     for (int32_t a = 0; a < n_nt; ++a)
@@ -352,11 +481,27 @@ cfpq_status cfpq_conjunctive_closure(const cfpq_graph* graph, const cfpq_grammar
         return CFPQ_OK;
     };
 
+    if (p.staged) {
+        CFPQ_HIP(launch_zero(SH, mw * p.shared.size(), s));
+        for (size_t k = 0; k < p.shared.size(); ++k) {
+            st = product(p.shared[k].first, p.shared[k].second, SH + k * mw, d_spare);
+            if (st != CFPQ_OK) return st;
+        }
+        const unsigned blocks = static_cast<unsigned>(std::min<int64_t>((L.mat_words + 511) / 512, 4096));
+        combine_kernel<<<dim3(blocks, static_cast<unsigned>(p.n_late_heads)), dim3(256), 0, s>>>(X, SH, L.mat_words,
+                                                                                              p.late);
+        CFPQ_HIP(hipGetLastError());
+    }
+
     const int64_t nn = graph->n_nodes;
     const int64_t cap = o.max_iters > 0 ? o.max_iters : nn * nn * n_nt + 1;
     std::vector<int32_t> prev(n_nt, 1), flags(n_nt, 0);
     int64_t iters = 0, products = 0;
-    bool converged = rules.empty() || graph->n_nodes == 0;
+    bool converged = rules.empty() || graph->n_nodes == 0 || p.staged;
+    if (p.staged) {  // the late rules count as one more loop
+        iters = early.iterations + 1;
+        products = early.products + static_cast<int64_t>(p.shared.size());
+    }
     if (!converged) {
         CFPQ_HIP(launch_zero(Q, mw, s));
         CFPQ_HIP(launch_zero(R, mw, s));
@@ -472,8 +617,9 @@ cfpq_status cfpq_conjunctive_closure(const cfpq_graph* graph, const cfpq_grammar
         std::memset(stats, 0, sizeof(*stats));
         stats->iterations = iters;
         stats->products = products;
-        stats->sparse_products = sparse;  // ROWS conjuncts: not counted as bit-operations
-        stats->bitops = 2.0 * static_cast<double>(L.npad) * L.npad * L.npad * static_cast<double>(products - sparse);
+        const int64_t dense = products - early.products - sparse;
+        stats->sparse_products = early.sparse_products + sparse;  // not counted as bit-operations
+        stats->bitops = early.bitops + 2.0 * static_cast<double>(L.npad) * L.npad * L.npad * static_cast<double>(dense);
         stats->device_ms = ms;
         stats->path_used = p.path;
         stats->converged = converged ? 1 : 0;
