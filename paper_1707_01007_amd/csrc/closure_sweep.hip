@@ -231,6 +231,7 @@ cfpq_status closure_sweep(const cfpq_graph* graph, const cfpq_grammar* grammar, 
         int64_t t = 0, waiting = 0;  // waiting: the loop of the oldest report not yet read
         int slot = 0;
         int64_t logged = 0;
+        bool transposed = false;  // the kept transposes exist
         while (true) {
             int64_t queued_report = 0;
             if (t < cap) {
@@ -245,7 +246,8 @@ cfpq_status closure_sweep(const cfpq_graph* graph, const cfpq_grammar* grammar, 
                             for (int c = 0; c < sg.n_dyn && ct; ++c)
                                 if (p.tt_slot[c] >= 0)
                                     CFPQ_HIP(launch_transpose(T_of(c), TT + p.tt_slot[c] * mw, L, s,
-                                                              first ? nullptr : any_prev, -(1 << c)));
+                                                              transposed ? any_prev : nullptr, -(1 << c)));
+                            transposed = true;
                             for (int r = 0; r < sg.n_dd; ++r) {
                                 const auto& q = sg.dd[r];
                                 const int32_t want = -static_cast<int32_t>((1u << q.left) | (1u << q.right));

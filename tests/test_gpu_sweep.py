@@ -125,3 +125,14 @@ def test_sweep_cut_short_is_sound(cfpq, n, iters):
     if res.status == -4:
         assert res.stats["iterations"] == iters and res.stats["converged"] == 0
         assert got.any()
+
+
+@pytest.mark.parametrize("n", [600, 4200])
+def test_sweep_reads_nothing_stale_in_the_workspace(cfpq, n):
+    """A growing pair whose right operand never changes while its left one
+    does: the product must not read a transpose that was never made."""
+    import torch
+    g = _g("idle_right", ["S", "X", "Y", "A", "B"], [("A", "a"), ("B", "b")],
+           [("X", "A", "B"), ("Y", "Y", "B"), ("S", "X", "Y"), ("S", "Y", "X")])
+    _, e = graphs.erdos_renyi(n, 2 * n, 21, labels=2)
+    _check(cfpq, n, e, g, workspace=torch.full((256 << 20,), 255, dtype=torch.uint8, device="cuda"))
