@@ -525,7 +525,11 @@ CFPQ_API cfpq_status cfpq_batch_tune_set(const cfpq_batch_tune_entry* entry);
  * matrix is fixed by the edges) runs as row gathers instead of tiles when the
  * graph has at most npad^2 / 16 edges -- after the first two loops only the
  * rows of its right operand that gained bits since it last ran are pushed
- * into the result; OFF keeps every rule on the tiles.
+ * into the result; OFF keeps every rule on the tiles.  With hybrid AUTO and
+ * the dirty worklist, instances of 513 to 4096 nodes with at most 16 edges per
+ * padded row and a grammar of at most 32 binary and 32 terminal rules run as
+ * row sweeps, whatever tile their route names: only rules over two growing
+ * operands are multiplied (256 x 256 tiles).
  * Results are bit-identical to cfpq_closure on each instance alone.  opt:
  * schedule must be INPLACE and warm_start 0; dirty_worklist, capture,
  * hybrid and max_iters apply to every instance; path, tile and profile are

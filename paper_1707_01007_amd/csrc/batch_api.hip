@@ -10,10 +10,15 @@
 #include <vector>
 
 #include "batch_engine.h"
+#include "closure_common.h"
+#include "group_sweep.h"
 #include "resident.h"
 
 namespace cfpq {
 namespace {
+
+constexpr size_t kGroupMaxSlots = 32767;  // slot numbers of the group sweep's maps have 15 bits
+constexpr int32_t kGroupLoops = 4;        // loops queued per report, as in cfpq_closure's sweeps
 
 // Host-side tables and the workspace carve-up of one batch.
 struct BatchPlan {
@@ -22,6 +27,12 @@ struct BatchPlan {
     std::vector<int32_t> rules, modes, trans, term, large, small8, small16;
     std::vector<int32_t> sweep[kResidentClasses];  // slots of the resident sweep, by launch class
     int32_t sweep_lds[kResidentClasses] = {};
+    std::vector<int32_t> group;  // slots of the group sweep
+    std::vector<GroupGrammar> group_grammars;
+    std::vector<int32_t> group_rows[2], group_tiles, group_trans;  // its launches' blocks
+    std::vector<size_t> group_off;                              // and its slots' workspace in the tt region
+    size_t group_lds[2] = {};
+    bool group_dd = false;
     std::vector<int32_t> all_ids;  // the slots whose matrices the batch initialises (not the resident sweep's)
     std::vector<int64_t> edge_begin;
     std::vector<size_t> edge_copy_off;  // per slot: byte offset in the edge region, or SIZE_MAX (device edges)
@@ -29,9 +40,51 @@ struct BatchPlan {
     int32_t large_rules = 0, large_trans = 0;
     size_t off_descs = 0, off_states = 0, off_rules = 0, off_go = 0, off_mode = 0, off_trans = 0, off_term = 0;
     size_t off_jobs = 0, off_tjobs = 0, off_large = 0, off_small8 = 0, off_small16 = 0, off_sweep = 0, off_all = 0;
-    size_t off_edge_begin = 0, off_es = 0, off_edges = 0, off_tt = 0, total = 0;
+    size_t off_group = 0, off_group_maps = 0, off_edge_begin = 0, off_es = 0, off_edges = 0, off_tt = 0, total = 0;
     std::vector<size_t> tt_off;  // per slot: byte offset of its transposes (large) in the tt region
 };
+
+// Blocks of the group sweep's launches.  Workgroups go to the eight XCDs in
+// turn by their number, so an instance's row groups are placed eight apart:
+// the rows they pull from each other then come through one XCD's L2.  The
+// widest instances go first, each to the XCD with the fewest words so far.
+void group_maps(BatchPlan& p) {
+    constexpr int kXcds = 8;
+    std::vector<size_t> order(p.group.size());
+    std::iota(order.begin(), order.end(), size_t{0});
+    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) {
+        return p.descs[p.group[a]].W > p.descs[p.group[b]].W;
+    });
+    for (int wide = 0; wide < 2; ++wide) {
+        std::vector<int32_t> per[kXcds];
+        int64_t words[kXcds] = {};
+        for (size_t k : order) {
+            const SlotDesc& d = p.descs[p.group[k]];
+            if ((d.W > 32) != (wide == 1)) continue;
+            const auto x = std::min_element(words, words + kXcds) - words;
+            words[x] += static_cast<int64_t>(d.n) * d.W;
+            for (int32_t r = 0; r < (d.n + kGsRows - 1) / kGsRows; ++r)
+                per[x].push_back(static_cast<int32_t>(k) << 16 | r);
+            p.group_lds[wide] = std::max(p.group_lds[wide], group_lds(d.W, p.group_grammars[k].n_dyn));
+        }
+        size_t most = 0;
+        for (const auto& v : per) most = std::max(most, v.size());
+        p.group_rows[wide].assign(most * kXcds, -1);
+        for (int x = 0; x < kXcds; ++x)
+            for (size_t q = 0; q < per[x].size(); ++q) p.group_rows[wide][q * kXcds + x] = per[x][q];
+    }
+    for (size_t k : order) {
+        const GroupGrammar& g = p.group_grammars[k];
+        const int32_t base = static_cast<int32_t>(k) << 16, side = p.descs[p.group[k]].npad / 256;
+        for (int32_t ij = 0; ij < side * side; ++ij) {
+            const int32_t tile = (ij / side) << 4 | (ij % side);
+            for (int32_t r = 0; r < g.n_dd; ++r) p.group_tiles.push_back(base | r << 8 | tile);
+            for (int32_t c = 0; c < g.n_dyn; ++c)
+                if (g.tt_slot[c] >= 0) p.group_trans.push_back(base | c << 8 | tile);
+        }
+        p.group_dd = p.group_dd || g.n_dd > 0;
+    }
+}
 
 // Tables and workspace layout of a batch.  Each instance takes its route
 // from batch_route (forced, or the tuning table); the workspace reserves the
@@ -94,7 +147,17 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
         int32_t n_right = 0;
         std::vector<int32_t> tr(d.n_nt, -1);
         std::vector<int32_t> md(d.n_rules, kModeDense);
-        if (d.n_rules > 0) {
+        // the group sweep takes its instances whatever tile the routes name: the
+        // tiles are those of the dense rules, which it has fewer of
+        GroupGrammar gg;
+        const bool swept = d.n_rules > 0 && d.dirty && !d.jacobi && o.hybrid == CFPQ_HYBRID_AUTO &&
+                           p.group.size() < kGroupMaxSlots && group_grammar(gr, d.n, g.n_edges, &gg);
+        if (swept) {
+            p.group.push_back(i);
+            p.group_grammars.push_back(gg);
+            p.group_off.push_back(tt_bytes);
+            tt_bytes += group_layout(gg, d.n, nullptr, nullptr);
+        } else if (d.n_rules > 0) {
             if (o.hybrid == CFPQ_HYBRID_AUTO)
                 for (int32_t r = 0; r < d.n_rules; ++r)
                     md[r] = engine_rule_mode(gr->bin_rules, d.n_rules, r, g.n_edges, L.npad);
@@ -125,6 +188,8 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
         ResidentPlan rp;
         if (d.n_rules == 0) {
             // nothing to iterate: initialisation only
+        } else if (swept) {
+            continue;  // initialised by group_init
         } else if (d.kind == kSlotLarge) {
             p.large.push_back(i);
         } else if (!d.jacobi && d.dirty &&
@@ -169,6 +234,10 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
     p.off_sweep = take(4 * static_cast<size_t>(n));
     p.off_all = take(4 * static_cast<size_t>(n));
     p.off_edge_begin = take(8 * (static_cast<size_t>(n) + 1));
+    group_maps(p);
+    p.off_group = take(sizeof(GroupSlot) * p.group.size());
+    p.off_group_maps = take(4 * (p.group_rows[0].size() + p.group_rows[1].size() + p.group_tiles.size() +
+                                 p.group_trans.size()));
     p.off_es = take(sizeof(EngineState));
     p.off_edges = take(edge_bytes);
     p.off_tt = take(tt_bytes);
@@ -434,9 +503,9 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
     // table region (descs .. engine state, contiguous), built in pinned
     // memory, followed there by two engine-state slots for the loop's checks.
     const size_t tab_begin = p.off_descs, tab_bytes = p.off_es + sizeof(EngineState) - p.off_descs;
-    const size_t es_slots = align_up(tab_bytes, 64);
+    const size_t es_slots = align_up(tab_bytes, 64), rep_slots = es_slots + 2 * sizeof(EngineState);
     void* pb = nullptr;
-    CFPQ_HIP(pinned_readback(es_slots + 2 * sizeof(EngineState), &pb));
+    CFPQ_HIP(pinned_readback(rep_slots + 2 * sizeof(GroupReport), &pb));
     char* img = static_cast<char*>(pb);
     std::memset(img, 0, tab_bytes);
     auto put = [&](size_t off, const void* src, size_t bytes) {
@@ -460,6 +529,37 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
     }
     put(p.off_all, p.all_ids.data(), 4 * p.all_ids.size());
     put(p.off_edge_begin, p.edge_begin.data(), 8 * p.edge_begin.size());
+    const int32_t n_group = static_cast<int32_t>(p.group.size());
+    auto* d_group = reinterpret_cast<GroupSlot*>(ws + p.off_group);
+    for (int32_t k = 0; k < n_group; ++k) {
+        const SlotDesc& sd = p.descs[p.group[k]];
+        GroupSlot q{};
+        group_layout(p.group_grammars[k], sd.n, ws + p.off_tt + p.group_off[k], &q);
+        q.T = sd.T;
+        q.edges = sd.edges;
+        q.n_edges = sd.n_edges;
+        q.max_iters = sd.max_iters;
+        q.n_nt = sd.n_nt;
+        q.n_terminals = sd.n_terminals;
+        q.slot = p.group[k];
+        put(p.off_group + sizeof(GroupSlot) * k, &q, sizeof(q));
+    }
+    GroupMaps maps;
+    {
+        size_t at = p.off_group_maps;
+        auto list = [&](const std::vector<int32_t>& v, const int32_t** where, int32_t* count) {
+            put(at, v.data(), 4 * v.size());
+            *where = reinterpret_cast<const int32_t*>(ws + at);
+            *count = static_cast<int32_t>(v.size());
+            at += 4 * v.size();
+        };
+        for (int wide = 0; wide < 2; ++wide) {
+            list(p.group_rows[wide], &maps.rows[wide], &maps.n_rows[wide]);
+            maps.lds[wide] = p.group_lds[wide];
+        }
+        list(p.group_tiles, &maps.tiles, &maps.n_tiles);
+        list(p.group_trans, &maps.trans, &maps.n_trans);
+    }
     EngineState es0;
     std::memset(&es0, 0, sizeof(es0));
     es0.n_large = static_cast<int32_t>(p.large.size());
@@ -484,9 +584,9 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
 
     // Small instances: one resident workgroup each, on a side stream beside
     // the large ones (there being any); the longest launches first.
-    const bool any_small = p.all_ids.size() < static_cast<size_t>(n_instances) || !p.small8.empty() ||
-                           !p.small16.empty();
-    const bool beside = !p.large.empty();
+    bool any_small = !p.small8.empty() || !p.small16.empty();
+    for (const auto& v : p.sweep) any_small = any_small || !v.empty();
+    const bool beside = !p.large.empty() || n_group > 0;
     hipStream_t side = s;
     if (any_small && beside) {
         CFPQ_HIP(aux_stream(&side));
@@ -503,6 +603,29 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
         CFPQ_HIP(engine_resident(b, small16_ids, static_cast<int32_t>(p.small16.size()), 16, side));
         CFPQ_HIP(engine_resident(b, b.small_ids, static_cast<int32_t>(p.small8.size()), 8, side));
         if (beside) CFPQ_HIP(hipEventRecord(join, side));
+    }
+
+    // Instances of the group sweep: loops queued in groups, a group's report
+    // awaited only after the next group is queued.
+    Drain drain{s, n_group > 0};
+    if (n_group > 0) {
+        int32_t max_lists = 0;
+        for (const GroupGrammar& g : p.group_grammars) max_lists = std::max(max_lists, g.n_list);
+        CFPQ_HIP(group_init(d_group, n_group, max_lists, s));
+        auto* rep = reinterpret_cast<GroupReport*>(img + rep_slots);
+        rep[0].loop = rep[1].loop = 0;
+        bool dd = p.group_dd;
+        int32_t t = 0;
+        for (int slot = 0;; slot ^= 1) {
+            for (int q = 0; q < kGroupLoops; ++q) CFPQ_HIP(group_loop(d_group, maps, ++t, dd, s));
+            CFPQ_HIP(group_report(d_group, n_group, t, &rep[slot], s));
+            if (t == kGroupLoops) continue;
+            const GroupReport* r = &rep[slot ^ 1];
+            CFPQ_HIP(await_report(r, t - kGroupLoops, s));
+            if (r->running == 0) break;
+            dd = dd && r->running_dd > 0;
+        }
+        CFPQ_HIP(group_finish(d_group, n_group, b.states, s));
     }
 
     // Large instances: captured loops over the shared work list.
@@ -564,6 +687,7 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
     CFPQ_HIP(hipEventRecord(ev1, s));
     CFPQ_HIP(hipMemcpyAsync(hstates.data(), b.states, sizeof(SlotState) * hstates.size(), hipMemcpyDeviceToHost, s));
     CFPQ_HIP(hipStreamSynchronize(s));
+    drain.armed = false;
     for (int32_t i = 0; i < n_instances; ++i)
         if (hstates[i].bad_edges)
             return fail(CFPQ_EINVAL, "instance " + std::to_string(i) + ": " + std::to_string(hstates[i].bad_edges) +

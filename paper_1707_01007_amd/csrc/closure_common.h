@@ -1,5 +1,7 @@
-// Pieces of the closure drivers shared by closure.hip and closure_sweep.hip.
+// Pieces shared by the closure and batch drivers.
 #pragma once
+
+#include <immintrin.h>
 
 #include <cstdio>
 #include <cstdlib>
@@ -50,6 +52,31 @@ inline const char* path_name(int32_t path) {
         default: return "auto";
     }
 }
+
+// Waits until the report for loop t has been written (or the stream failed).
+template <typename Report>
+hipError_t await_report(const Report* rep, int32_t t, hipStream_t s) {
+    for (uint32_t spin = 1;; ++spin) {
+        if (__atomic_load_n(&rep->loop, __ATOMIC_ACQUIRE) >= t) return hipSuccess;
+        _mm_pause();
+        if ((spin & 0xFFFF) == 0) {  // a few ms of spinning: is the stream still at work?
+            const hipError_t e = hipStreamQuery(s);
+            if (e == hipErrorNotReady) continue;
+            if (e != hipSuccess) return e;
+            return __atomic_load_n(&rep->loop, __ATOMIC_ACQUIRE) >= t ? hipSuccess : hipErrorUnknown;
+        }
+    }
+}
+
+// Waits for the stream when destroyed while armed: whatever ends a call early,
+// no queued report outlives its use of the pinned buffer.
+struct Drain {
+    hipStream_t s;
+    bool armed = true;
+    ~Drain() {
+        if (armed) (void)hipStreamSynchronize(s);
+    }
+};
 
 // AUTO: the autotuned kernel of the size bucket, else the fp4 MFMA while fp32 sums
 // are exact.  *tile is only changed for an autotuned choice.

@@ -9,7 +9,6 @@
 // on a dense product costs more than a round trip, so those rules' products
 // are chosen per loop by the cost model from the reported counts.
 #include <hip/hip_runtime.h>
-#include <immintrin.h>
 
 #include <algorithm>
 #include <chrono>
@@ -88,20 +87,6 @@ SweepPlan sweep_plan(const cfpq_graph* gr, const SweepGrammar& g) {
     p.off_flag = take(256);
     p.total = off;
     return p;
-}
-
-// Waits until the report for loop t has been written (or the stream failed).
-hipError_t await_report(const SweepReport* rep, int32_t t, hipStream_t s) {
-    for (uint32_t spin = 1;; ++spin) {
-        if (__atomic_load_n(&rep->loop, __ATOMIC_ACQUIRE) >= t) return hipSuccess;
-        _mm_pause();
-        if ((spin & 0xFFFF) == 0) {  // a few ms of spinning: is the stream still at work?
-            const hipError_t e = hipStreamQuery(s);
-            if (e == hipErrorNotReady) continue;
-            if (e != hipSuccess) return e;
-            return __atomic_load_n(&rep->loop, __ATOMIC_ACQUIRE) >= t ? hipSuccess : hipErrorUnknown;
-        }
-    }
 }
 
 }  // namespace
@@ -188,14 +173,7 @@ cfpq_status closure_sweep(const cfpq_graph* graph, const cfpq_grammar* grammar, 
     CFPQ_HIP(pinned_readback(2 * sizeof(SweepReport), &pb));
     auto* rep = static_cast<SweepReport*>(pb);
     rep[0].loop = rep[1].loop = 0;
-    // whatever ends the call early, no queued report may outlive this buffer's use
-    struct Drain {
-        hipStream_t s;
-        bool armed = true;
-        ~Drain() {
-            if (armed) (void)hipStreamSynchronize(s);
-        }
-    } drain{s};
+    Drain drain{s};
     CFPQ_HIP(hipEventRecord(ev0, s));
     CFPQ_HIP(launch_sweep_init(sg, b, L, d_edges, graph->n_edges, n_nt, grammar->n_terminals, s));
     if (sg.p_mask != 0) CFPQ_HIP(launch_zero(b.P, mw * __builtin_popcount(sg.p_mask), s));
