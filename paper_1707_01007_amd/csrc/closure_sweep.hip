@@ -31,7 +31,7 @@ constexpr int32_t kGroup = 4;
 struct SweepPlan {
     SweepGrammar g;
     Layout L;
-    size_t off_edges = 0, off_wg = 0, off_chg = 0, off_ctl = 0, off_cnt = 0, off_cur = 0, off_start = 0, off_idx = 0;
+    size_t off_edges = 0, off_wg = 0, off_chg = 0, off_ctl = 0, off_list = 0, off_cur = 0, off_near = 0, off_idx = 0;
     size_t off_d0 = 0, off_d1 = 0, off_p = 0, off_tt = 0, off_bt = 0, off_pt = 0, off_ct = 0, off_rowor = 0;
     size_t off_flag = 0, total = 0;
     bool hosted = false;  // dd products chosen on the host
@@ -53,13 +53,13 @@ SweepPlan sweep_plan(const cfpq_graph* gr, const SweepGrammar& g) {
         return at;
     };
     p.off_edges = take(gr->edges_on_device ? 0 : static_cast<size_t>(gr->n_edges) * sizeof(cfpq_edge));
-    const size_t lists = static_cast<size_t>(std::max(g.n_list, 1)) * std::max(L.n, 1) * 4;
+    const size_t lists = static_cast<size_t>(std::max(g.n_list, 1)) * std::max(L.n, 1);
     p.off_wg = take(static_cast<size_t>(2) * g.n_dyn * sweep_groups(L.n) * 4);
     p.off_chg = take(static_cast<size_t>(4) * g.n_dyn * L.W * 8);
     p.off_ctl = take(sizeof(SweepCtl));
-    p.off_cnt = take(lists);
-    p.off_cur = take(lists);
-    p.off_start = take(lists);
+    p.off_list = take(lists * 8);
+    p.off_cur = take(lists * 4);
+    p.off_near = take(lists * 16);
     // an edge enters the lists of its label's (distinct) terminal rules
     int32_t per_edge = 1;
     for (int32_t q = 0; q < g.n_term; ++q) {
@@ -135,9 +135,9 @@ cfpq_status closure_sweep(const cfpq_graph* graph, const cfpq_grammar* grammar, 
     b.chg = reinterpret_cast<uint64_t*>(ws + p.off_chg);
     b.ctl = reinterpret_cast<SweepCtl*>(ws + p.off_ctl);
     b.wg = reinterpret_cast<int32_t*>(ws + p.off_wg);
-    b.cnt = reinterpret_cast<int32_t*>(ws + p.off_cnt);
+    b.list = reinterpret_cast<int2*>(ws + p.off_list);
     b.cur = reinterpret_cast<int32_t*>(ws + p.off_cur);
-    b.start = reinterpret_cast<int32_t*>(ws + p.off_start);
+    b.near = reinterpret_cast<uint4*>(ws + p.off_near);
     b.idx = reinterpret_cast<int32_t*>(ws + p.off_idx);
     uint64_t* TT = reinterpret_cast<uint64_t*>(ws + p.off_tt);
     uint64_t* BT = reinterpret_cast<uint64_t*>(ws + p.off_bt);

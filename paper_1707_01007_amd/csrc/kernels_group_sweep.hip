@@ -4,6 +4,7 @@
 #include "batch_engine.h"
 #include "group_sweep.h"
 #include "mfma_tile.h"
+#include "near_list.h"
 
 namespace cfpq {
 namespace {
@@ -23,16 +24,6 @@ __global__ __launch_bounds__(256) void group_clear_kernel(const GroupSlot* __res
     for (int64_t i = at; i < pq; i += stride) p[i] = make_uint4(0, 0, 0, 0);
     if (at == 0) *d.ctl = GroupCtl{};
 }
-
-// A node's list in one 16-byte word: its entries as eight 16-bit numbers,
-// kNone past the last; with more than eight, kMore in the last place and all of
-// them in idx.
-constexpr uint32_t kNone = 0xFFFF, kMore = 0xFFFE;
-__device__ __forceinline__ uint32_t entry(const uint4& v, int u) {
-    const uint32_t w = u < 2 ? v.x : u < 4 ? v.y : u < 6 ? v.z : v.w;
-    return u & 1 ? w >> 16 : w & 0xFFFFu;
-}
-__device__ __forceinline__ bool has_more(const uint4& v) { return v.w >> 16 == kMore; }
 
 // Grid (list, slot), one list a workgroup: lengths, places and entries from
 // LDS counters; the workgroup after the last list sets the bits of Algorithm
@@ -111,9 +102,7 @@ __global__ __launch_bounds__(512) void group_lists_kernel(const GroupSlot* __res
     auto put = [&](int32_t i, int32_t start, int32_t k) {
         const int32_t at = atomicAdd(&cur[i], 1);
         d.idx[base + at] = k;
-        const int32_t nth = at - start;
-        if (nth < 7 || (nth == 7 && cnt[i] == 8)) near[8 * i + nth] = static_cast<uint16_t>(k);
-        if (nth == 7 && cnt[i] > 8) near[8 * i + 7] = static_cast<uint16_t>(kMore);
+        put_near(near + 8 * i, at - start, cnt[i], k);
     };
     for (int64_t e = tid; e < d.n_edges; e += 512) {
         const cfpq_edge ed = d.edges[e];
@@ -182,7 +171,6 @@ __global__ __launch_bounds__(512) void group_product_kernel(const GroupSlot* __r
         &d.ctl->spare);  // the sweep finds what changed
 }
 
-constexpr int32_t kLongList = 32;  // entries a lane walks itself in a scatter or gather
 
 // Bits a row, on average, from which the turned scatter is taken.
 constexpr int32_t kTurnBits = 8;
@@ -196,82 +184,6 @@ struct GroupShared {
     uint32_t gained[kSwMaxDyn];
     uint32_t any;
 };
-
-// The OR of in[k] over node i's list: in[k] lies at word (k % 64, k / 64).
-__device__ __forceinline__ uint64_t gather_words(const uint64_t* buf, int stride, int lane, bool have, int64_t i,
-                                                 const uint4* __restrict__ near, const int2* __restrict__ list,
-                                                 const int32_t* __restrict__ idx) {
-    uint64_t acc = 0;
-    auto word = [&](int32_t k) { return buf[(k & 63) * stride + (k >> 6)]; };
-    const uint4 v = have ? near[i] : make_uint4(~0u, ~0u, ~0u, ~0u);
-    const bool more = has_more(v);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const uint32_t k = entry(v, u);
-        if (__ballot(k < kMore) == 0) break;  // uniform: no lane has more than u entries
-        if (k < kMore) acc |= word(static_cast<int32_t>(k));
-    }
-    if (__ballot(more) == 0) return acc;
-    const int2 l = more ? list[i] : make_int2(0, 0);
-    for (int32_t e = 7, m = min(l.y, kLongList); e < m; ++e) acc |= word(idx[l.x + e]);
-    for (uint64_t m = __ballot(l.y > kLongList); m != 0; m &= m - 1) {
-        const int who = __ffsll(static_cast<unsigned long long>(m)) - 1;
-        const int32_t ls = __builtin_amdgcn_readlane(l.x, who), lc = __builtin_amdgcn_readlane(l.y, who);
-        uint64_t w = 0;
-        for (int32_t e = kLongList + lane; e < lc; e += 64) w |= word(idx[ls + e]);
-        for (int o = 32; o > 0; o >>= 1)
-            w |= static_cast<uint64_t>(__shfl_xor(static_cast<unsigned long long>(w), o, 64));
-        if (lane == who) acc |= w;
-    }
-    return acc;
-}
-
-// Sets, in this lane's LDS row x, the bits of node i's list.
-__device__ __forceinline__ void scatter_list(const uint4& v, bool have, int64_t i, const int2* __restrict__ list,
-                                             const int32_t* __restrict__ idx, uint32_t* lds, int32_t x, int lane) {
-    const bool more = have && has_more(v);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const uint32_t j = have ? entry(v, u) : kNone;
-        if (__ballot(j < kMore) == 0) break;
-        if (j < kMore) atomicOr(lds + x + (j >> 5), 1u << (j & 31));
-    }
-    if (__ballot(more) == 0) return;
-    const int2 l = more ? list[i] : make_int2(0, 0);
-    for (int32_t e = 7, m = min(l.y, kLongList); e < m; ++e) {
-        const int32_t j = idx[l.x + e];
-        atomicOr(lds + x + (j >> 5), 1u << (j & 31));
-    }
-    for (uint64_t m = __ballot(l.y > kLongList); m != 0; m &= m - 1) {
-        const int who = __ffsll(static_cast<unsigned long long>(m)) - 1;
-        const int32_t ls = __builtin_amdgcn_readlane(l.x, who), lc = __builtin_amdgcn_readlane(l.y, who);
-        const int32_t xw = __builtin_amdgcn_readlane(x, who);
-        for (int32_t e = kLongList + lane; e < lc; e += 64) {
-            const int32_t j = idx[ls + e];
-            atomicOr(lds + xw + (j >> 5), 1u << (j & 31));
-        }
-    }
-}
-
-// The same for the lists of base + k, every bit k of f; two bits a step.
-__device__ __forceinline__ void scatter_word(uint64_t f, int64_t base, const uint4* __restrict__ near,
-                                             const int2* __restrict__ list, const int32_t* __restrict__ idx,
-                                             uint32_t* lds, int32_t x, int lane) {
-    while (__ballot(f != 0) != 0) {
-        uint4 v[2];
-        bool have[2];
-        int64_t k[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            have[u] = f != 0;
-            k[u] = base + (have[u] ? __ffsll(static_cast<unsigned long long>(f)) - 1 : 0);
-            f &= f - 1;  // 0 stays 0
-            v[u] = have[u] ? near[k[u]] : make_uint4(~0u, ~0u, ~0u, ~0u);
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) scatter_list(v[u], have[u], k[u], list, idx, lds, x, lane);
-    }
-}
 
 // Loop t of 64 rows of one instance, LPR lanes a row (rows of at most LPR
 // words), as in sweep_kernel: pulls, then scatters, each row written by this

@@ -1,6 +1,7 @@
 // Kernels of the row sweeps (see sweep.h).
 #include <algorithm>
 
+#include "near_list.h"
 #include "rowor_device.h"
 #include "sweep.h"
 
@@ -32,7 +33,7 @@ struct InitArgs {
 // One thread per edge: the bits of Algorithm 1's matrix initialisation, and
 // the lengths of the adjacency lists.  Parallel edges may enter a list twice.
 __global__ __launch_bounds__(256) void sweep_scatter_kernel(const cfpq_edge* __restrict__ edges, int64_t m,
-                                                            InitArgs a, uint64_t* T, int32_t* cnt, SweepCtl* ctl) {
+                                                            InitArgs a, uint64_t* T, int2* list, SweepCtl* ctl) {
     const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (e >= m) return;
     const cfpq_edge ed = edges[e];
@@ -45,19 +46,19 @@ __global__ __launch_bounds__(256) void sweep_scatter_kernel(const cfpq_edge* __r
     for (int32_t q = 0; q < a.n_term; ++q) {
         if (a.term[q].label != ed.label) continue;
         atomicOr(reinterpret_cast<unsigned long long*>(T + a.term[q].nt * a.mat_words + off), bit);
-        if (a.term[q].out >= 0) atomicAdd(cnt + static_cast<int64_t>(a.term[q].out) * a.n + ed.src, 1);
-        if (a.term[q].in >= 0) atomicAdd(cnt + static_cast<int64_t>(a.term[q].in) * a.n + ed.dst, 1);
+        if (a.term[q].out >= 0) atomicAdd(&list[static_cast<int64_t>(a.term[q].out) * a.n + ed.src].y, 1);
+        if (a.term[q].in >= 0) atomicAdd(&list[static_cast<int64_t>(a.term[q].in) * a.n + ed.dst].y, 1);
     }
 }
 
 // Places of the lists in idx: a workgroup's lists are consecutive, the
 // workgroups' runs come in any order (one atomic each).
-__global__ __launch_bounds__(256) void sweep_place_kernel(const int32_t* __restrict__ cnt, int32_t* __restrict__ start,
-                                                          int32_t lists, SweepCtl* ctl) {
+__global__ __launch_bounds__(256) void sweep_place_kernel(int2* list, int32_t* __restrict__ cur,
+                                                          uint4* __restrict__ near, int32_t lists, SweepCtl* ctl) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     __shared__ int32_t wave_tot[4], base_s;
     const int32_t i = blockIdx.x * 256 + threadIdx.x;
-    const int32_t c = i < lists ? cnt[i] : 0;
+    const int32_t c = i < lists ? list[i].y : 0;
     int32_t x = c;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -70,27 +71,30 @@ __global__ __launch_bounds__(256) void sweep_place_kernel(const int32_t* __restr
     __syncthreads();
     int32_t at = base_s + x - c;
     for (int w = 0; w < wave; ++w) at += wave_tot[w];
-    if (i < lists) start[i] = at;
+    if (i >= lists) return;
+    list[i].x = at;
+    cur[i] = 0;
+    near[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
 }
 
 __global__ __launch_bounds__(256) void sweep_fill_kernel(const cfpq_edge* __restrict__ edges, int64_t m, InitArgs a,
-                                                         const int32_t* __restrict__ start, int32_t* cur,
-                                                         int32_t* __restrict__ idx) {
+                                                         const int2* __restrict__ list, int32_t* cur,
+                                                         uint4* near, int32_t* __restrict__ idx) {
     const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (e >= m) return;
     const cfpq_edge ed = edges[e];
     if (ed.src < 0 || ed.src >= a.n || ed.dst < 0 || ed.dst >= a.n || ed.label < 0 || ed.label >= a.n_terminals)
         return;  // counted by the scatter
+    auto put = [&](int64_t i, int32_t k) {
+        const int2 l = list[i];
+        const int32_t nth = atomicAdd(cur + i, 1);
+        idx[l.x + nth] = k;
+        put_near(reinterpret_cast<uint16_t*>(near + i), nth, l.y, k);
+    };
     for (int32_t q = 0; q < a.n_term; ++q) {
         if (a.term[q].label != ed.label) continue;
-        if (a.term[q].out >= 0) {
-            const int64_t l = static_cast<int64_t>(a.term[q].out) * a.n + ed.src;
-            idx[start[l] + atomicAdd(cur + l, 1)] = ed.dst;
-        }
-        if (a.term[q].in >= 0) {
-            const int64_t l = static_cast<int64_t>(a.term[q].in) * a.n + ed.dst;
-            idx[start[l] + atomicAdd(cur + l, 1)] = ed.src;
-        }
+        if (a.term[q].out >= 0) put(static_cast<int64_t>(a.term[q].out) * a.n + ed.src, ed.dst);
+        if (a.term[q].in >= 0) put(static_cast<int64_t>(a.term[q].in) * a.n + ed.dst, ed.src);
     }
 }
 
@@ -104,8 +108,8 @@ struct SweepArgs {
     SweepCtl* ctl;
     const int32_t* wg_prev;
     int32_t* wg_cur;
-    const int32_t* cnt;
-    const int32_t* start;
+    const int2* list;
+    const uint4* near;
     const int32_t* idx;
     int64_t W, mat_words;
     int32_t n, t, rows;  // rows of a workgroup: 16, 32 or 64
@@ -113,116 +117,48 @@ struct SweepArgs {
     int32_t count, dense_dd;
 };
 
-// Lists longer than this are walked by the whole wavefront (scatter, gather)
-// or workgroup (pull) instead of one lane or wavefront.
-constexpr int32_t kLongList = 32, kLongPull = 256;
+// Lists longer than this are pulled by the whole workgroup instead of a wavefront.
+constexpr int32_t kLongPull = 256;
 
-// Sets the bits of the list entries of k in the LDS row x, for every bit k of
-// f (this lane's WPL words of a row).  Four bits a step, so that their list
-// lookups are in flight together.
-template <int WPL>
-__device__ __forceinline__ void scatter_bits(const uint64_t (&f)[WPL], int lane, const int32_t* __restrict__ cnt,
-                                             const int32_t* __restrict__ start, const int32_t* __restrict__ idx,
-                                             uint32_t* x) {
-#pragma unroll
-    for (int q = 0; q < WPL; ++q) {
-        uint64_t bits = f[q];
-        const int32_t base = (lane + 64 * q) * 64;
-        while (__ballot(bits != 0) != 0) {
-            int32_t c[4], s[4], j[4];
-            bool lng = false;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const bool have = bits != 0;
-                const int32_t k = have ? base + __ffsll(static_cast<unsigned long long>(bits)) - 1 : base;
-                bits &= bits - 1;  // 0 stays 0
-                c[u] = have ? cnt[k] : 0;
-                s[u] = have ? start[k] : 0;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) j[u] = c[u] > 0 ? idx[s[u]] : 0;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                lng = lng || c[u] > kLongList;
-                if (c[u] > 0) atomicOr(x + (j[u] >> 5), 1u << (j[u] & 31));
-                for (int32_t e = 1, m = min(c[u], kLongList); e < m; ++e) {
-                    const int32_t jj = idx[s[u] + e];
-                    atomicOr(x + (jj >> 5), 1u << (jj & 31));
-                }
-            }
-            if (__ballot(lng) == 0) continue;
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                for (uint64_t m = __ballot(c[u] > kLongList); m != 0; m &= m - 1) {
-                    const int l = __ffsll(static_cast<unsigned long long>(m)) - 1;
-                    const int32_t lc = __builtin_amdgcn_readlane(c[u], l), ls = __builtin_amdgcn_readlane(s[u], l);
-                    for (int32_t e = kLongList + lane; e < lc; e += 64) {
-                        const int32_t jj = idx[ls + e];
-                        atomicOr(x + (jj >> 5), 1u << (jj & 31));
-                    }
-                }
-        }
-    }
-}
-
-// The OR of in[k] over the list entries k of this lane's node (c of them from
-// idx[s]; c = 0 past the last node).  in[k] lies at word (k % 64, k / 64) of
-// the LDS buffer.
-__device__ __forceinline__ uint64_t gather_words(const uint64_t* buf, int64_t stride, int lane, int32_t c, int32_t s,
-                                                 const int32_t* __restrict__ idx) {
-    uint64_t acc = 0;
-    auto word = [&](int32_t k) { return buf[(k & 63) * stride + (k >> 6)]; };
-    for (int32_t e = 0, m = min(c, kLongList); e < m; e += 4) {
-        int32_t k[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) k[u] = idx[s + min(e + u, m - 1)];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc |= word(k[u]);
-    }
-    for (uint64_t m = __ballot(c > kLongList); m != 0; m &= m - 1) {
-        const int l = __ffsll(static_cast<unsigned long long>(m)) - 1;
-        const int32_t lc = __builtin_amdgcn_readlane(c, l), ls = __builtin_amdgcn_readlane(s, l);
-        uint64_t v = 0;
-        for (int32_t e = kLongList + lane; e < lc; e += 64) v |= word(idx[ls + e]);
-        for (int o = 32; o > 0; o >>= 1)
-            v |= static_cast<uint64_t>(__shfl_xor(static_cast<unsigned long long>(v), o, 64));
-        if (lane == l) acc |= v;
-    }
-    return acc;
-}
-
-// ORs into acc the rows `src[k, :]` of the list entries k for which live(k):
-// entries part * 64 + [0, 64), then every parts * 64 on.  Returns whether
-// there was one.  Rows are read four at a time (a missing one repeats the last).
+// ORs into acc the rows src[k, :] of the lanes' k (kNone: none) for which
+// live(k).  Returns whether there was one.  Rows are read four at a time (a
+// missing one repeats the last).
 template <int WPL, typename Live>
-__device__ __forceinline__ bool pull_rows(const uint64_t* src, int64_t W, const uint32_t (&off)[WPL], int lane,
-                                          int32_t s, int32_t c, int part, int parts,
-                                          const int32_t* __restrict__ idx, Live live, uint64_t (&acc)[WPL]) {
-    bool got = false;
-    for (int32_t b = part * 64; b < c; b += parts * 64) {
-        const int32_t k = b + lane < c ? idx[s + b + lane] : -1;
-        uint64_t m = __ballot(k >= 0 && live(k));
-        got = got || m != 0;
-        while (m != 0) {
-            const uint64_t* row[4];
-            int l = 0;
+__device__ __forceinline__ bool pull_lanes(const uint64_t* src, int64_t W, const uint32_t (&off)[WPL], uint32_t k,
+                                           Live live, uint64_t (&acc)[WPL]) {
+    uint64_t m = __ballot(k < kMore && live(static_cast<int32_t>(k)));
+    const bool got = m != 0;
+    while (m != 0) {
+        const uint64_t* row[4];
+        int l = 0;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (m != 0) l = __ffsll(static_cast<unsigned long long>(m)) - 1;
-                m &= m - 1;
-                row[u] = src + static_cast<int64_t>(__builtin_amdgcn_readlane(k, l)) * W;
-            }
-            uint64_t v[4][WPL];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int q = 0; q < WPL; ++q) v[u][q] = row[u][off[q]];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int q = 0; q < WPL; ++q) acc[q] |= v[u][q];
+        for (int u = 0; u < 4; ++u) {
+            if (m != 0) l = __ffsll(static_cast<unsigned long long>(m)) - 1;
+            m &= m - 1;
+            row[u] = src + static_cast<int64_t>(__builtin_amdgcn_readlane(static_cast<int>(k), l)) * W;
         }
+        uint64_t v[4][WPL];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int q = 0; q < WPL; ++q) v[u][q] = row[u][off[q]];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int q = 0; q < WPL; ++q) acc[q] |= v[u][q];
     }
+    return got;
+}
+
+// The rows of a whole list: entries part * 64 + [0, 64), then every parts * 64 on.
+template <int WPL, typename Live>
+__device__ __forceinline__ bool pull_list(const uint64_t* src, int64_t W, const uint32_t (&off)[WPL], int lane, int2 l,
+                                          int part, int parts, const int32_t* __restrict__ idx, Live live,
+                                          uint64_t (&acc)[WPL]) {
+    bool got = false;
+    for (int32_t b = part * 64; b < l.y; b += parts * 64)
+        got |= pull_lanes<WPL>(src, W, off, b + lane < l.y ? static_cast<uint32_t>(idx[l.x + b + lane]) : kNone, live,
+                               acc);
     return got;
 }
 
@@ -247,13 +183,14 @@ __device__ __forceinline__ bool pull_rows(const uint64_t* src, int64_t W, const 
 // more rows in flight a SIMD), active ones move rows of D and T.
 template <int WPL, bool kFirst>
 __global__ __launch_bounds__(1024) void sweep_kernel(SweepArgs a) {
-    extern __shared__ __align__(16) uint64_t buf[];  // 64 rows of W + 1 words
+    extern __shared__ __align__(16) uint64_t buf[];  // 64 rows of W + 1 words, n_dyn bitmaps of W
     __shared__ uint32_t any_s;
     __shared__ unsigned long long gained_s[kSwMaxDyn], rows_s[kSwMaxDyn];  // this loop's bits and changed rows
     __shared__ unsigned long long long_s;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
-    const int64_t W = a.W, stride = W + 1;
+    const int64_t W = a.W;
+    const int stride = static_cast<int>(W) + 1;
     const int n_dyn = a.g.n_dyn;
     const int cur = a.t & 3, prev = (a.t - 1) & 3, next = (a.t + 1) & 3;
     SweepCtl* ctl = a.ctl;
@@ -288,9 +225,11 @@ __global__ __launch_bounds__(1024) void sweep_kernel(SweepArgs a) {
         gained_s[threadIdx.x] = 0;
         rows_s[threadIdx.x] = 0;
     }
+    // the last loop's changed rows
+    uint64_t* marks = buf + 64 * stride;
+    if (!kFirst)
+        for (int64_t x = threadIdx.x; x < n_dyn * W; x += blockDim.x) marks[x] = a.chg[prev * n_dyn * W + x];
     __syncthreads();
-
-    const uint64_t* chg_prev = a.chg + prev * n_dyn * W;
     uint64_t* chg_cur = a.chg + cur * n_dyn * W;
     const int32_t row0 = static_cast<int32_t>(blockIdx.x) * a.rows;
     const int32_t nrows = min(a.rows, a.n - row0);
@@ -332,34 +271,47 @@ __global__ __launch_bounds__(1024) void sweep_kernel(SweepArgs a) {
             atomicAdd(&gained_s[h], c);
         }
     };
-    auto pull_head = [&](int h, int lr, int part, int parts, uint64_t (&acc)[WPL]) {
+    // this lane's entry of node list i's 16-byte form, and whether there are more
+    auto near_entry = [&](int64_t i) -> uint32_t {
+        return lane < 8 ? reinterpret_cast<const uint16_t*>(a.near)[8 * i + lane] : kNone;
+    };
+    auto more_than_near = [&](uint32_t k) {
+        return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(k), 7)) == kMore;
+    };
+    // the rows head h pulls into row lr, but for lists past kLongPull (their rows
+    // are noted); or, whole, this wavefront's part of all lists
+    bool lng = false;
+    auto pull_head = [&](int h, int lr, bool whole, uint64_t (&acc)[WPL]) {
         bool got = false;
         for (int r = 0; r < a.g.n_lf; ++r) {
             const int c = a.g.lf[r].right;
             if (a.g.lf[r].head != h) continue;
             if (kFirst ? !((a.g.init_mask >> c) & 1u) : !((any_prev >> c) & 1u)) continue;
-            const int64_t l = static_cast<int64_t>(a.g.lf[r].left) * a.n + row0 + lr;
+            const int64_t i = static_cast<int64_t>(a.g.lf[r].left) * a.n + row0 + lr;
             const uint64_t* src = kFirst ? a.T + a.g.dyn_nt[c] * a.mat_words : a.Dprev + c * a.mat_words;
-            const uint64_t* marks = chg_prev + c * W;
-            got |= pull_rows<WPL>(
-                src, W, off, lane, a.start[l], a.cnt[l], part, parts, a.idx,
-                [&](int32_t k) { return kFirst || ((marks[k >> 6] >> (k & 63)) & 1ull) != 0; }, acc);
+            auto live = [&](int32_t k) { return kFirst || ((marks[c * W + (k >> 6)] >> (k & 63)) & 1ull) != 0; };
+            const uint32_t k = near_entry(i);
+            if (!whole && !more_than_near(k)) {
+                got |= pull_lanes<WPL>(src, W, off, k, live, acc);
+                continue;
+            }
+            const int2 l = a.list[i];
+            if (whole || l.y <= kLongPull)
+                got |= pull_list<WPL>(src, W, off, lane, l, whole ? wave : 0, whole ? 16 : 1, a.idx, live, acc);
+            else
+                lng = true;
         }
         return got;
     };
 
     // ---- 1. pulls
     for (int lr = wave; lr < nrows; lr += 16) {
-        int32_t most = 0;
-        for (int r = 0; r < a.g.n_lf; ++r)
-            most = max(most, a.cnt[static_cast<int64_t>(a.g.lf[r].left) * a.n + row0 + lr]);
-        const bool lng = most > kLongPull;  // left to the whole workgroup, below
-        if (lng && lane == 0) atomicOr(&long_s, 1ull << lr);
+        lng = false;
         for (int h = 0; h < n_dyn; ++h) {
             uint64_t acc[WPL];
 #pragma unroll
             for (int q = 0; q < WPL; ++q) acc[q] = 0;
-            bool got = lng ? false : pull_head(h, lr, 0, 1, acc);
+            bool got = pull_head(h, lr, false, acc);
             if ((a.p_mask >> h) & 1u) {
                 const int slot = __popc(a.g.p_mask & ((1u << h) - 1));
                 const uint64_t* prow = a.P + slot * a.mat_words + static_cast<int64_t>(row0 + lr) * W;
@@ -369,6 +321,7 @@ __global__ __launch_bounds__(1024) void sweep_kernel(SweepArgs a) {
             }
             if (got) commit(h, lr, acc);
         }
+        if (lng && lane == 0) atomicOr(&long_s, 1ull << lr);  // left to the whole workgroup, below
     }
     __syncthreads();
     for (uint64_t lm = long_s; lm != 0; lm &= lm - 1) {  // uniform over the workgroup
@@ -379,7 +332,7 @@ __global__ __launch_bounds__(1024) void sweep_kernel(SweepArgs a) {
             uint64_t acc[WPL];
 #pragma unroll
             for (int q = 0; q < WPL; ++q) acc[q] = 0;
-            if (pull_head(h, lr, wave, 16, acc)) {
+            if (pull_head(h, lr, true, acc)) {
 #pragma unroll
                 for (int q = 0; q < WPL; ++q)
                     if (valid[q] && acc[q] != 0)
@@ -402,7 +355,7 @@ __global__ __launch_bounds__(1024) void sweep_kernel(SweepArgs a) {
     auto late = [&](int h) { return ((a.g.rf_mask >> h) & 1u) != 0; };
     auto feed_rows = [&](int h) -> uint64_t {
         if (kFirst) return (a.g.init_mask >> h) & 1u ? all_rows : rows_s[h];
-        return late(h) ? (chg_prev[h * W + (row0 >> 6)] >> (row0 & 63)) & all_rows : rows_s[h];
+        return late(h) ? (marks[h * W + (row0 >> 6)] >> (row0 & 63)) & all_rows : rows_s[h];
     };
     auto feed_row = [&](int h, int lr) -> const uint64_t* {
         if (kFirst) return T_row(h, lr);
@@ -437,7 +390,7 @@ __global__ __launch_bounds__(1024) void sweep_kernel(SweepArgs a) {
             for (int lr = wave; lr < nrows; lr += 16) {
                 if (!((fed >> lr) & 1ull)) continue;
                 uint64_t* xrow = buf + lr * stride;
-                uint32_t* x = reinterpret_cast<uint32_t*>(xrow);
+                uint32_t* lds32 = reinterpret_cast<uint32_t*>(buf);
 #pragma unroll
                 for (int q = 0; q < WPL; ++q)
                     if (valid[q]) xrow[off[q]] = 0;
@@ -451,22 +404,22 @@ __global__ __launch_bounds__(1024) void sweep_kernel(SweepArgs a) {
 #pragma unroll
                     for (int q = 0; q < WPL; ++q) f[q] = valid[q] ? frow[off[q]] : 0;
                     const int64_t l = static_cast<int64_t>(a.g.rf[r].right) * a.n;
-                    scatter_bits<WPL>(f, lane, a.cnt + l, a.start + l, a.idx, x);
+#pragma unroll
+                    for (int q = 0; q < WPL; ++q)
+                        scatter_word(f[q], l + (lane + 64 * q) * 64, a.near, a.list, a.idx, lds32, lr * stride * 2,
+                                     lane);
                 }
                 if (kFirst) {
                     // A -> B C with both fixed: the edges k -> j of C for the edges row -> k of B
                     for (int r = 0; r < a.g.n_ll; ++r) {
                         if (a.g.ll[r].head != th) continue;
-                        const int64_t lb = static_cast<int64_t>(a.g.ll[r].left) * a.n + row0 + lr;
-                        const int64_t lc = static_cast<int64_t>(a.g.ll[r].right) * a.n;
-                        const int32_t s = a.start[lb], c = a.cnt[lb];
-                        for (int32_t b = lane; b < c; b += 64) {
-                            const int32_t k = a.idx[s + b];
-                            const int32_t sc = a.start[lc + k], cc = a.cnt[lc + k];
-                            for (int32_t e = 0; e < cc; ++e) {
-                                const int32_t j = a.idx[sc + e];
-                                atomicOr(x + (j >> 5), 1u << (j & 31));
-                            }
+                        const int64_t cb = static_cast<int64_t>(a.g.ll[r].right) * a.n;
+                        const int2 l = a.list[static_cast<int64_t>(a.g.ll[r].left) * a.n + row0 + lr];
+                        for (int32_t b = 0; b < l.y; b += 64) {
+                            const bool have = b + lane < l.y;
+                            const int64_t k = cb + (have ? a.idx[l.x + b + lane] : 0);
+                            const uint4 v = have ? a.near[k] : make_uint4(~0u, ~0u, ~0u, ~0u);
+                            scatter_list(v, have, k, a.list, a.idx, lds32, lr * stride * 2, lane);
                         }
                     }
                 }
@@ -509,8 +462,7 @@ __global__ __launch_bounds__(1024) void sweep_kernel(SweepArgs a) {
 #pragma unroll
             for (int i = 0; i < 4 * WPL; ++i) {
                 const int32_t j = (wave + 16 * i) * 64 + lane;
-                const bool in = j < a.n;
-                acc[i] |= gather_words(buf, stride, lane, in ? a.cnt[l + j] : 0, in ? a.start[l + j] : 0, a.idx);
+                acc[i] |= gather_words(buf, stride, lane, j < a.n, l + j, a.near, a.list, a.idx);
             }
         }
         __syncthreads();  // every read of the turned operands is done
@@ -652,9 +604,9 @@ bool sweep_grammar(const cfpq_grammar* gr, SweepGrammar* result) {
 
 hipError_t launch_sweep_init(const SweepGrammar& g, const SweepBuffers& b, const Layout& L, const cfpq_edge* edges,
                              int64_t m, int32_t n_nt, int32_t n_terminals, hipStream_t s) {
-    // bitmaps, counters, cursors and the control block lie together from chg on
+    // bitmaps, the control block and the lists lie together from chg to cur
     const size_t tq = static_cast<size_t>(L.mat_words) * n_nt / 2;
-    const size_t cq = static_cast<size_t>(reinterpret_cast<char*>(b.start) - reinterpret_cast<char*>(b.chg)) / 16;
+    const size_t cq = static_cast<size_t>(reinterpret_cast<char*>(b.cur) - reinterpret_cast<char*>(b.chg)) / 16;
     const size_t blocks = std::min<size_t>((tq + cq + 1023) / 1024, 4096);
     sweep_clear_kernel<<<dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s>>>(
         reinterpret_cast<uint4*>(b.T), tq, reinterpret_cast<uint4*>(b.chg), cq);
@@ -668,12 +620,12 @@ hipError_t launch_sweep_init(const SweepGrammar& g, const SweepBuffers& b, const
     a.W = L.W;
     a.mat_words = L.mat_words;
     const dim3 eg(static_cast<unsigned>((m + 255) / 256));
-    sweep_scatter_kernel<<<eg, dim3(256), 0, s>>>(edges, m, a, b.T, b.cnt, b.ctl);
+    sweep_scatter_kernel<<<eg, dim3(256), 0, s>>>(edges, m, a, b.T, b.list, b.ctl);
     if (g.n_list > 0) {
         const int32_t lists = g.n_list * L.n;
-        sweep_place_kernel<<<dim3(static_cast<unsigned>((lists + 255) / 256)), dim3(256), 0, s>>>(b.cnt, b.start, lists,
-                                                                                                 b.ctl);
-        sweep_fill_kernel<<<eg, dim3(256), 0, s>>>(edges, m, a, b.start, b.cur, b.idx);
+        sweep_place_kernel<<<dim3(static_cast<unsigned>((lists + 255) / 256)), dim3(256), 0, s>>>(b.list, b.cur, b.near,
+                                                                                                 lists, b.ctl);
+        sweep_fill_kernel<<<eg, dim3(256), 0, s>>>(edges, m, a, b.list, b.cur, b.near, b.idx);
     }
     return hipGetLastError();
 }
@@ -688,8 +640,8 @@ hipError_t launch_sweep(const SweepGrammar& g, const SweepBuffers& b, const Layo
     a.P = b.P;
     a.chg = b.chg;
     a.ctl = b.ctl;
-    a.cnt = b.cnt;
-    a.start = b.start;
+    a.list = b.list;
+    a.near = b.near;
     a.idx = b.idx;
     a.W = L.W;
     a.mat_words = L.mat_words;
@@ -703,7 +655,7 @@ hipError_t launch_sweep(const SweepGrammar& g, const SweepBuffers& b, const Layo
     a.wg_prev = b.wg + static_cast<size_t>((t + 1) & 1) * g.n_dyn * groups;
     a.wg_cur = b.wg + static_cast<size_t>(t & 1) * g.n_dyn * groups;
     const dim3 grid(static_cast<unsigned>(groups));
-    const size_t lds = static_cast<size_t>(64) * (L.W + 1) * 8;
+    const size_t lds = (static_cast<size_t>(64) * (L.W + 1) + static_cast<size_t>(g.n_dyn) * L.W) * 8;
     if (L.W <= 64) return t == 1 ? sweep_launch<1, true>(a, grid, lds, s) : sweep_launch<1, false>(a, grid, lds, s);
     if (L.W <= 128) return t == 1 ? sweep_launch<2, true>(a, grid, lds, s) : sweep_launch<2, false>(a, grid, lds, s);
     return t == 1 ? sweep_launch<4, true>(a, grid, lds, s) : sweep_launch<4, false>(a, grid, lds, s);

@@ -15,10 +15,10 @@
 // device, so the host queues loops ahead of their results.
 //
 // Measured (in place of the product loops, which took a launch or more per
-// rule and loop and whole-matrix passes): a^n b^n on G(7001, 28004), 2667 ->
-// 627 us; same-generation on G(1500, 6000), 1963 -> 273 us, and on a
-// 4096-node hierarchy, 370 -> 94 us; Dyck on G(16384, 65536), 5609 -> 4188 us.
-// A dense a^n b^n loop at 7001 nodes takes about 36 us for some 60 MB.
+// rule and loop and whole-matrix passes): a^n b^n on G(7001, 28004), 2480 ->
+// 550 us; same-generation on G(1500, 6000), 1870 -> 242 us, and on a
+// 4096-node hierarchy, 334 -> 87 us; Dyck on G(16384, 65536), 5540 -> 4070 us.
+// A dense a^n b^n loop at 7001 nodes takes about 35 us for some 60 MB.
 //
 // A rule whose two operands both grow (S -> S S) is multiplied by the product
 // kernels into a matrix P of its head, which the sweep ORs in like a pulled
@@ -106,9 +106,9 @@ struct SweepBuffers {
     uint64_t* chg = nullptr;      // changed-row bitmaps [4][n_dyn][W], by loop & 3
     SweepCtl* ctl = nullptr;
     int32_t* wg = nullptr;        // [2][n_dyn][sweep_groups] bits a workgroup's rows gained, by loop parity
-    int32_t* cnt = nullptr;       // [n_list][n] list lengths
+    int2* list = nullptr;         // [n_list][n] start and length
     int32_t* cur = nullptr;       // [n_list][n] fill cursors
-    int32_t* start = nullptr;     // [n_list][n] list starts
+    uint4* near = nullptr;        // [n_list][n] the 16-byte form (near_list.h)
     int32_t* idx = nullptr;       // targets
 };
 
