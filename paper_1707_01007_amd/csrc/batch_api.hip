@@ -594,7 +594,7 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
         CFPQ_HIP(hipStreamWaitEvent(side, fork, 0));
     }
     if (any_small) {
-        for (int32_t cls : {5, 4, 2, 1, 3, 0}) {
+        for (int32_t cls : {5, 4, 2, 1, 3, 0, 7, 6}) {
             size_t at = 0;
             for (int32_t q = 0; q < cls; ++q) at += p.sweep[q].size();
             CFPQ_HIP(resident_sweep(b, reinterpret_cast<int32_t*>(ws + p.off_sweep) + at,

@@ -16,7 +16,7 @@
 // whole matrices every loop (engine_resident_kernel, still used for the Jacobi
 // schedule, for grammars beyond the tables and for lists that do not fit): two
 // cycles of 64 and 63 nodes, 4033 loops, 17.95 -> 5.57 ms (1.4 us a loop); Dyck
-// on G(450, 1800) 596 -> 227 us; same-generation on 100 nodes 124 -> 67 us.
+// on G(450, 1800) 607 -> 225 us; same-generation on 100 nodes 124 -> 67 us.
 #include <algorithm>
 
 #include "mfma_tile.h"
@@ -46,18 +46,21 @@ constexpr int threads_for(int lanes) { return lanes == 1 ? 128 : lanes == 2 ? 51
 // Bits of the dd masks of a loop from which the product runs on the matrix
 // cores: a walked bit costs the LDS of a row of C (64 bytes at four lanes a
 // row, about 1.2 cycles), the tiles and the transposes about 20000 cycles
-// (four lanes) or 5000 (two).
+// (four lanes), 5000 (two) or 3000 (one).
 template <int L>
-constexpr int32_t kTileBits = L == 4 ? 16384 : 8192;
+constexpr int32_t kTileBits = L == 4 ? 16384 : L == 2 ? 8192 : 4096;
 
-// Bits a loop's rows gained from which its scatters run turned (transposed in
-// LDS, rows of 64 bytes ORed along the incoming lists, turned back): some 5000
-// cycles a rule, where a lane scatters four bits in about 800.
+// Bits a row gained, on average, from which a loop's scatters run turned
+// (transposed in LDS, columns ORed along the incoming lists, turned back): some
+// 5000 cycles a rule (1800 with one lane a row), where a lane scatters four
+// bits in about 800 and the longest lane counts.  With 12 bits, a^n b^n on
+// G(200, 600) took 210 us and Dyck on G(400, 1200) 289; with 4, 154 and 243;
+// with 3 the same.
 template <int L>
-constexpr int32_t kTurnBits = L == 4 ? 6144 : 3072;
+constexpr int32_t kTurnBits = L == 1 ? 1 : 4;
 
-// kDD: the slots have dd rules.
-template <int L, bool kDD>
+// kDD: the slots have dd rules.  kTurn: their LDS may hold transposed operands.
+template <int L, bool kDD, bool kTurn>
 __global__ __launch_bounds__(threads_for(L)) void resident_sweep_kernel(const SlotDesc* __restrict__ descs,
                                                                         SlotState* states,
                                                                         const int32_t* __restrict__ rules_tab,
@@ -94,7 +97,7 @@ __global__ __launch_bounds__(threads_for(L)) void resident_sweep_kernel(const Sl
         bad_s = 0;
     }
     __syncthreads();
-    const bool turned = L > 1 && d.tile != 0;
+    const bool turned = kTurn && d.tile != 0;
     const ResidentLds lay = resident_lds(n, G, 0, turned);
     auto uni = [](int32_t x) { return __builtin_amdgcn_readfirstlane(x); };
     auto uni64 = [&](uint64_t x) {
@@ -390,11 +393,14 @@ __global__ __launch_bounds__(threads_for(L)) void resident_sweep_kernel(const Sl
                             for (int e = 0; e < 16; ++e) acc[jb][e] = 0.0f;
 #pragma unroll 1
                         for (int kc = 0; kc < (L + 1) / 2; ++kc) {  // 256 k a chunk: this half's four words
-                            const uint4 bv = reinterpret_cast<const uint4*>(Bm + i * RW)[2 * kc + g];
+                            // one lane a row: 128 k, the other half multiplies zeros
+                            const int at = L == 1 ? 0 : 2 * kc + g;
+                            uint4 bv = reinterpret_cast<const uint4*>(Bm + i * RW)[at];
+                            if (L == 1 && g == 1) bv = make_uint4(0, 0, 0, 0);
                             uint4 cv[4];
 #pragma unroll
                             for (int jb = 0; jb < 4; ++jb)
-                                cv[jb] = reinterpret_cast<const uint4*>(CT + (jc * 128 + jb * 32 + r32) * RW)[2 * kc + g];
+                                cv[jb] = reinterpret_cast<const uint4*>(CT + (jc * 128 + jb * 32 + r32) * RW)[at];
 #pragma unroll
                             for (int s = 0; s < 4; ++s) {
                                 const mfma::v4i bb = mfma::spread4(mfma::word_of(bv, s));
@@ -436,7 +442,7 @@ __global__ __launch_bounds__(threads_for(L)) void resident_sweep_kernel(const Sl
 
         // rows: pulls, then scatters -- at once, or where the rows may be
         // turned once the bits of all rows are counted
-        const bool later = L > 1 && turned && src >= 0 && !first;
+        const bool later = turned && src >= 0 && !first;
         uint4 held[kPasses];
         int32_t fed = 0;
 #pragma unroll
@@ -522,14 +528,14 @@ __global__ __launch_bounds__(threads_for(L)) void resident_sweep_kernel(const Sl
                 if ((tid & 63) == 0) atomicAdd(&fed_s[t & 1], fed);
             }
             __syncthreads();
-            turn = uni(fed_s[t & 1]) >= kTurnBits<L>;
+            turn = uni(fed_s[t & 1]) >= kTurnBits<L> * n;
             if (!turn) {
 #pragma unroll
                 for (int ps = 0; ps < kPasses; ++ps)
                     if (any4(held[ps])) scatter(group + ps * kGroups, src, held[ps], cc, any);
             }
         }
-        if (L > 1 && turn) {
+        if (turn) {
             const int lane = tid & 63, wave = tid >> 6, nb = lay.rows / 64;
             for (int r = 0; r < n_rf; ++r) {
                 const int h = rs_left(rf, r), x = rs_head(rf, r);
@@ -542,23 +548,25 @@ __global__ __launch_bounds__(threads_for(L)) void resident_sweep_kernel(const Sl
                     *reinterpret_cast<uint64_t*>(TT + (64 * bc + lane) * RW + 2 * br) = v;
                 }
                 __syncthreads();
-                // column j of the result: the columns of its incoming edges; two threads a column
-                const int j = tid / 2, c0 = (tid & 1) * (L / 2);
-                uint4 acc[(L + 1) / 2];
+                // column j of the result: the columns of its incoming edges; two
+                // threads a column, or one
+                constexpr int kPer = (L + 1) / 2;
+                const int j = L == 1 ? tid : tid / 2, c0 = L == 1 ? 0 : (tid & 1) * kPer;
+                uint4 acc[kPer];
 #pragma unroll
-                for (int q = 0; q < L / 2; ++q) acc[q] = make_uint4(0, 0, 0, 0);
+                for (int q = 0; q < kPer; ++q) acc[q] = make_uint4(0, 0, 0, 0);
                 if (j < n) {
                     const uint32_t* e0 = end + G.rf_in[r] * n + j;
                     for (uint32_t e = e0[0]; e < e0[1]; ++e) {
                         const uint4* col = reinterpret_cast<const uint4*>(TT + idx[e] * RW) + c0;
 #pragma unroll
-                        for (int q = 0; q < L / 2; ++q) acc[q] = or4(acc[q], col[q]);
+                        for (int q = 0; q < kPer; ++q) acc[q] = or4(acc[q], col[q]);
                     }
                 }
                 __syncthreads();
                 if (j < lay.rows) {
 #pragma unroll
-                    for (int q = 0; q < L / 2; ++q) reinterpret_cast<uint4*>(TT + j * RW)[c0 + q] = acc[q];
+                    for (int q = 0; q < kPer; ++q) reinterpret_cast<uint4*>(TT + j * RW)[c0 + q] = acc[q];
                 }
                 __syncthreads();
                 for (int b = wave; b < nb * nb; b += kThreads / 64) {
@@ -609,14 +617,14 @@ __global__ __launch_bounds__(threads_for(L)) void resident_sweep_kernel(const Sl
     }
 }
 
-template <int L, bool kDD>
+template <int L, bool kDD, bool kTurn = true>
 hipError_t launch(const EngineBuffers& b, const int32_t* ids, int32_t count, int32_t lds, hipStream_t s) {
     if (lds > 64 * 1024) {  // more dynamic LDS than a launch gets unasked
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&resident_sweep_kernel<L, kDD>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&resident_sweep_kernel<L, kDD, kTurn>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
     }
-    resident_sweep_kernel<L, kDD><<<dim3(static_cast<unsigned>(count)), dim3(threads_for(L)),
+    resident_sweep_kernel<L, kDD, kTurn><<<dim3(static_cast<unsigned>(count)), dim3(threads_for(L)),
                                     static_cast<size_t>(lds), s>>>(b.descs, b.states, b.rules_tab, b.term_tab, ids);
     return hipGetLastError();
 }
@@ -647,12 +655,17 @@ bool resident_plan(const cfpq_bin_rule* bin, int32_t n_bin, const cfpq_term_rule
     }
     // an edge enters at most two lists (outgoing, incoming) per terminal rule of its label
     const int64_t entries = 2 * n_edges * per_edge;
-    const bool want = resident_lanes(n) > 1 && (plan->g.n_dd > 0 || plan->g.n_rf > 0);
+    // one lane a row: with two edges a node and more.  On sparser graphs a loop
+    // sets few bits, and the kernel without the turned code takes a fifth less a
+    // loop (two cycles of 64 and 63 nodes: 5.6 against 6.9 ms; same-generation
+    // on G(100, 300), where the turned code runs: 265 against 161 us)
+    const bool one = resident_lanes(n) == 1;
+    const bool want = (plan->g.n_dd > 0 || plan->g.n_rf > 0) && (!one || n_edges >= 2 * static_cast<int64_t>(n));
     ResidentLds l = resident_lds(n, plan->g, entries, want);
     plan->turned = want && l.total <= kResidentMaxLds ? 1 : 0;
     if (!plan->turned) l = resident_lds(n, plan->g, entries, false);
     if (l.total > kResidentMaxLds) return false;
-    plan->cls = resident_lanes(n) / 2 + (plan->g.n_dd > 0 ? 3 : 0);
+    plan->cls = one && plan->turned ? (plan->g.n_dd > 0 ? 7 : 6) : resident_lanes(n) / 2 + (plan->g.n_dd > 0 ? 3 : 0);
     plan->lds = l.total;
     return true;
 }
@@ -661,12 +674,14 @@ hipError_t resident_sweep(const EngineBuffers& b, const int32_t* ids, int32_t co
                           hipStream_t s) {
     if (count <= 0) return hipSuccess;
     switch (cls) {
-        case 0: return launch<1, false>(b, ids, count, lds, s);
+        case 0: return launch<1, false, false>(b, ids, count, lds, s);
         case 1: return launch<2, false>(b, ids, count, lds, s);
         case 2: return launch<4, false>(b, ids, count, lds, s);
-        case 3: return launch<1, true>(b, ids, count, lds, s);
+        case 3: return launch<1, true, false>(b, ids, count, lds, s);
         case 4: return launch<2, true>(b, ids, count, lds, s);
-        default: return launch<4, true>(b, ids, count, lds, s);
+        case 5: return launch<4, true>(b, ids, count, lds, s);
+        case 6: return launch<1, false>(b, ids, count, lds, s);
+        default: return launch<1, true>(b, ids, count, lds, s);
     }
 }
 

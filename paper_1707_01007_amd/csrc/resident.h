@@ -110,7 +110,7 @@ __host__ __device__ inline int resident_lanes(int32_t n) { return n <= 128 ? 1 :
 
 // LDS of a slot in bytes (offsets from the start of the dynamic LDS): T of
 // the growing nonterminals, the kept gained bits, transposed operands (with
-// `turned`: two lanes a row or more, and room), changed-row bitmaps of three
+// `turned`: where there is room), changed-row bitmaps of three
 // loops, list ends, list entries.
 struct ResidentLds {
     int32_t rows, mat;  // rows of a matrix (a multiple of 128 where it is multiplied by tiles), bytes
@@ -135,8 +135,9 @@ __host__ __device__ inline ResidentLds resident_lds(int32_t n, const ResidentGra
 }
 constexpr int32_t kResidentMaxLds = 158 * 1024;  // of 160 KiB; the rest is the kernel's own
 
-// Launch classes: lanes a row (1, 2, 4), without and with dd rules.
-constexpr int32_t kResidentClasses = 6;
+// Launch classes: lanes a row (1, 2, 4), without and with dd rules; then one
+// lane a row with transposed operands, without and with dd rules.
+constexpr int32_t kResidentClasses = 8;
 
 // Whether the resident sweep takes a graph of n nodes and this grammar, and for
 // its launch: the grammar as the kernel reads it (kept where the slot's rule

@@ -395,7 +395,7 @@ bool turn(cfpq_server* srv, std::vector<Request*>& admitted) {
             SRV_HIP(hipEventRecord(ready, s));
             SRV_HIP(hipStreamWaitEvent(srv->side, ready, 0));
             (void)hipEventDestroy(ready);
-            for (int32_t c : {5, 4, 2, 1, 3, 0})  // the longest launches first
+            for (int32_t c : {5, 4, 2, 1, 3, 0, 7, 6})  // the longest launches first
                 SRV_HIP(resident_sweep(srv->b, list + sweep_at[c], static_cast<int32_t>(sweep[c].size()), c,
                                        sweep_lds[c], srv->side));
             SRV_HIP(engine_resident(srv->b, list + s8.size(), static_cast<int32_t>(s16.size()), 16, srv->side));

@@ -64,6 +64,16 @@ def test_resident_dense(cfpq, n, name):
     assert np.array_equal(cfpq.result_bits(res), worklist.closure(n, e, g))
 
 
+@pytest.mark.parametrize("g", GRAMMARS, ids=lambda g: g.name)
+def test_resident_one_lane_dense(cfpq, g):
+    """One lane a row with transposed operands: from two edges a node on."""
+    for n, degree in ((1, 2), (5, 3), (32, 2), (33, 4), (63, 6), (64, 2), (65, 3), (127, 5), (128, 2)):
+        e = _graph(n, degree, 40 + n)
+        print("[gpu-case] resident one lane", g.name, n, len(e), file=sys.stderr, flush=True)
+        res = cfpq.closure(n, e, g)
+        assert np.array_equal(cfpq.result_bits(res), worklist.closure(n, e, g)), n
+
+
 def test_resident_batch_and_limits(cfpq):
     import torch
     items, want = [], []
