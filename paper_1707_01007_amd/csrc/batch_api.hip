@@ -27,6 +27,7 @@ struct BatchPlan {
     std::vector<int32_t> rules, modes, trans, term, large, small8, small16;
     std::vector<int32_t> sweep[kResidentClasses];  // slots of the resident sweep, by launch class
     int32_t sweep_lds[kResidentClasses] = {};
+    ResidentPlan solo;  // of the last of them
     std::vector<int32_t> group;  // slots of the group sweep
     std::vector<GroupGrammar> group_grammars;
     std::vector<int32_t> group_rows[2], group_tiles, group_trans;  // its launches' blocks
@@ -199,6 +200,7 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
             std::memcpy(p.rules.data() + 3 * grammar_at, &rp.g, sizeof(rp.g));
             d.tile = rp.turned;
             p.sweep[rp.cls].push_back(i);
+            p.solo = rp;
             p.sweep_lds[rp.cls] = std::max(p.sweep_lds[rp.cls], rp.lds);
             continue;  // initialised by its workgroup
         } else if (d.W == 4) {
@@ -288,6 +290,14 @@ cfpq_options resolve_batch(const cfpq_options* opt) {
     cfpq_default_options(&o);
     if (opt) o = *opt;
     return o;
+}
+
+// Rate of wall_clock64(), per millisecond.
+int wall_clock_khz() {
+    int dev = 0, khz = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 100000;
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || khz <= 0) return 100000;
+    return khz;
 }
 
 int device_cus() {
@@ -436,6 +446,46 @@ cfpq_status cfpq_batch_autotune(int32_t n_instances, const cfpq_instance* instan
 
 namespace cfpq {
 
+// A single instance by the resident sweep: one launch that reads no table and
+// reports to pinned host memory.  Up to kSoloEdgeBytes of host edges are read
+// from there as well; more are copied first.
+static cfpq_status solo_run(BatchPlan& p, const cfpq_instance& inst, hipStream_t s, char* ws, cfpq_stats* stats) {
+    constexpr size_t kSoloEdgeBytes = 32 * 1024;
+    SlotDesc& d = p.descs[0];
+    const size_t edge_bytes = inst.graph.edges_on_device ? 0 : static_cast<size_t>(d.n_edges) * sizeof(cfpq_edge);
+    const bool by_copy = edge_bytes > kSoloEdgeBytes;
+    const size_t at = align_up(sizeof(ResidentReport), 256);
+    void* pb = nullptr;
+    CFPQ_HIP(pinned_readback(at + kSoloEdgeBytes, &pb));
+    auto* report = static_cast<ResidentReport*>(pb);
+    report->loop = 0;
+    d.T = inst.d_result;
+    d.edges = inst.graph.edges;
+    if (by_copy) {
+        d.edges = reinterpret_cast<const cfpq_edge*>(ws + p.off_edges);
+        CFPQ_HIP(hipMemcpyAsync(ws + p.off_edges, inst.graph.edges, edge_bytes, hipMemcpyHostToDevice, s));
+    } else if (edge_bytes > 0) {
+        d.edges = reinterpret_cast<const cfpq_edge*>(static_cast<char*>(pb) + at);
+        std::memcpy(static_cast<char*>(pb) + at, inst.graph.edges, edge_bytes);
+    }
+    CFPQ_HIP(resident_solo(d, p.solo, report, s));
+    CFPQ_HIP(await_report(report, 1, s));
+    CFPQ_HIP(hipStreamSynchronize(s));
+    if (report->bad_edges)
+        return fail(CFPQ_EINVAL, "instance 0: " + std::to_string(report->bad_edges) + " device edges out of range");
+    if (stats) {
+        std::memset(stats, 0, sizeof(*stats));
+        stats->iterations = report->iterations;
+        stats->products = report->products;
+        stats->bitops = 2.0 * static_cast<double>(d.npad) * d.npad * d.npad * static_cast<double>(report->products);
+        stats->device_ms = static_cast<double>(report->ticks) / wall_clock_khz();
+        stats->path_used = CFPQ_PATH_BITS;
+        stats->converged = report->capped == 0 ? 1 : 0;
+    }
+    if (report->capped) return fail(CFPQ_ENOTCONV, "max_iters reached before the fixpoint in some instance");
+    return CFPQ_OK;
+}
+
 cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instances, const cfpq_options& o,
                               void* stream, void* d_workspace, size_t workspace_bytes, cfpq_stats* stats,
                               bool allow_jacobi, const RouteMap* overrides) {
@@ -449,6 +499,8 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
     if (n_instances == 0) return CFPQ_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(d_workspace);
+    if (n_instances == 1 && p.large.empty() && p.group.empty() && p.all_ids.empty() && p.solo.g.n_term >= 0)
+        return solo_run(p, instances[0], s, ws, stats);
     EngineBuffers b;
     b.descs = reinterpret_cast<SlotDesc*>(ws + p.off_descs);
     b.states = reinterpret_cast<SlotState*>(ws + p.off_states);

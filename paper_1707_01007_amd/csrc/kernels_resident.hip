@@ -60,12 +60,10 @@ template <int L>
 constexpr int32_t kTurnBits = L == 1 ? 1 : 4;
 
 // kDD: the slots have dd rules.  kTurn: their LDS may hold transposed operands.
+// d: the slot's descriptor, grammar: where its rules would be, out: its state.
 template <int L, bool kDD, bool kTurn>
-__global__ __launch_bounds__(threads_for(L)) void resident_sweep_kernel(const SlotDesc* __restrict__ descs,
-                                                                        SlotState* states,
-                                                                        const int32_t* __restrict__ rules_tab,
-                                                                        const int32_t* __restrict__ term_tab,
-                                                                        const int32_t* __restrict__ ids) {
+__device__ __forceinline__ void resident_closure(const SlotDesc& d, const int32_t* __restrict__ grammar,
+                                                 const int32_t* __restrict__ term_tab, SlotState* out) {
     constexpr int kThreads = threads_for(L);
     constexpr int kGroups = kThreads / L;
     constexpr int RW = 4 * L;  // dwords of a row
@@ -77,8 +75,6 @@ __global__ __launch_bounds__(threads_for(L)) void resident_sweep_kernel(const Sl
     __shared__ uint32_t any_s[3];
     __shared__ int32_t bits_s, bad_s, fed_s[2];  // fed: bits the scatters' operand gained, by loop parity
     const int tid = threadIdx.x;
-    const int slot = ids[blockIdx.x];
-    const SlotDesc& d = descs[slot];
     const int32_t n = d.n;
     const size_t mdw = static_cast<size_t>(d.npad) * d.W * 2;
     uint32_t* gT = reinterpret_cast<uint32_t*>(d.T);
@@ -89,7 +85,7 @@ __global__ __launch_bounds__(threads_for(L)) void resident_sweep_kernel(const Sl
         if (tid + u * kThreads < d.n_edges) kept[u] = d.edges[tid + u * kThreads];
     constexpr int kGramWords = static_cast<int>(sizeof(ResidentGrammar) / 4);
     for (int q = tid; q < kGramWords; q += kThreads)
-        reinterpret_cast<int32_t*>(&G)[q] = rules_tab[3 * d.rule_off + q];
+        reinterpret_cast<int32_t*>(&G)[q] = grammar[q];
     if (tid < 3) any_s[tid] = 0;
     if (tid < 2) fed_s[tid] = 0;
     if (tid == 0) {
@@ -607,14 +603,56 @@ __global__ __launch_bounds__(threads_for(L)) void resident_sweep_kernel(const Sl
         }
     }
     if (tid == 0) {
-        SlotState* st = states + slot;
-        st->iterations = t;
-        st->products = products;
-        st->capped = capped;
-        st->bad_edges = bad_s;
-        st->done = 1;
-        st->active = 0;
+        out->iterations = t;
+        out->products = products;
+        out->capped = capped;
+        out->bad_edges = bad_s;
+        out->done = 1;
+        out->active = 0;
     }
+}
+
+template <int L, bool kDD, bool kTurn>
+__global__ __launch_bounds__(threads_for(L)) void resident_sweep_kernel(const SlotDesc* __restrict__ descs,
+                                                                        SlotState* states,
+                                                                        const int32_t* __restrict__ rules_tab,
+                                                                        const int32_t* __restrict__ term_tab,
+                                                                        const int32_t* __restrict__ ids) {
+    const int slot = ids[blockIdx.x];
+    const SlotDesc& d = descs[slot];
+    resident_closure<L, kDD, kTurn>(d, rules_tab + 3 * d.rule_off, term_tab, states + slot);
+}
+
+// One closure by itself: what the host knows comes as kernel arguments, its
+// state and clock go to pinned host memory (ResidentReport), so the call takes
+// one launch and no copy.
+template <int L, bool kDD, bool kTurn>
+__global__ __launch_bounds__(threads_for(L)) void resident_solo_kernel(SlotDesc d, ResidentGrammar g,
+                                                                       ResidentReport* report) {
+    __shared__ SlotState st;
+    const uint64_t begin = wall_clock64();
+    resident_closure<L, kDD, kTurn>(d, reinterpret_cast<const int32_t*>(&g), nullptr, &st);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    report->iterations = st.iterations;
+    report->products = st.products;
+    report->capped = st.capped;
+    report->bad_edges = st.bad_edges;
+    report->ticks = wall_clock64() - begin;
+    __threadfence_system();
+    __hip_atomic_store(&report->loop, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+template <int L, bool kDD, bool kTurn = true>
+hipError_t launch_solo(const SlotDesc& d, const ResidentPlan& p, ResidentReport* report, hipStream_t s) {
+    if (p.lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&resident_solo_kernel<L, kDD, kTurn>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, p.lds);
+        if (e != hipSuccess) return e;
+    }
+    resident_solo_kernel<L, kDD, kTurn><<<dim3(1), dim3(threads_for(L)), static_cast<size_t>(p.lds), s>>>(d, p.g,
+                                                                                                      report);
+    return hipGetLastError();
 }
 
 template <int L, bool kDD, bool kTurn = true>
@@ -668,6 +706,19 @@ bool resident_plan(const cfpq_bin_rule* bin, int32_t n_bin, const cfpq_term_rule
     plan->cls = one && plan->turned ? (plan->g.n_dd > 0 ? 7 : 6) : resident_lanes(n) / 2 + (plan->g.n_dd > 0 ? 3 : 0);
     plan->lds = l.total;
     return true;
+}
+
+hipError_t resident_solo(const SlotDesc& d, const ResidentPlan& p, ResidentReport* report, hipStream_t s) {
+    switch (p.cls) {
+        case 0: return launch_solo<1, false, false>(d, p, report, s);
+        case 1: return launch_solo<2, false>(d, p, report, s);
+        case 2: return launch_solo<4, false>(d, p, report, s);
+        case 3: return launch_solo<1, true, false>(d, p, report, s);
+        case 4: return launch_solo<2, true>(d, p, report, s);
+        case 5: return launch_solo<4, true>(d, p, report, s);
+        case 6: return launch_solo<1, false>(d, p, report, s);
+        default: return launch_solo<1, true>(d, p, report, s);
+    }
 }
 
 hipError_t resident_sweep(const EngineBuffers& b, const int32_t* ids, int32_t count, int32_t cls, int32_t lds,

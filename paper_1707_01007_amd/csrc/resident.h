@@ -150,6 +150,17 @@ struct ResidentPlan {
 bool resident_plan(const cfpq_bin_rule* bin, int32_t n_bin, const cfpq_term_rule* term, int32_t n_term, int32_t n_nt,
                    int32_t n, int64_t n_edges, ResidentPlan* plan);
 
+// What resident_solo leaves in pinned host memory; loop = 1 comes last.
+struct ResidentReport {
+    int64_t iterations, products;
+    uint64_t ticks;  // of the constant clock, from start to end
+    int32_t capped, bad_edges, loop, pad;
+};
+
+// One slot by itself, without tables on the device; its terminal rules have to
+// be in the grammar (g.n_term >= 0).
+hipError_t resident_solo(const SlotDesc& d, const ResidentPlan& p, ResidentReport* report, hipStream_t s);
+
 // One workgroup per listed slot of class cls, with `lds` bytes of LDS (the
 // most any of them needs).  It initialises the slot's matrices itself, from
 // the edges, and counts edges out of range in the slot's state.
