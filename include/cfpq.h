@@ -555,7 +555,9 @@ CFPQ_API cfpq_status cfpq_batch_closure(int32_t n_instances, const cfpq_instance
  * queries in arrival order whenever a slot is free and the query's footprint
  * fits the arena, keeps their matrices resident until their fixpoint, and
  * runs every admitted query's loops together with the others in flight
- * (the batched engine of cfpq_batch_closure).  On completion the query's
+ * (the batched engine of cfpq_batch_closure; queries of 513 to 4096 nodes that
+ * it would run as row sweeps do so while the arena has room for them and the
+ * sweeps' tables, otherwise as tiles).  On completion the query's
  * matrices are copied to its d_result and its latency is recorded.
  * Queries with a padded side of at least 4096 go instead, in arrival order,
  * to `hybrid_lanes` lane threads, each running one query at a time with the

@@ -29,11 +29,9 @@ struct BatchPlan {
     int32_t sweep_lds[kResidentClasses] = {};
     ResidentPlan solo;  // of the last of them
     std::vector<int32_t> group;  // slots of the group sweep
-    std::vector<GroupGrammar> group_grammars;
-    std::vector<int32_t> group_rows[2], group_tiles, group_trans;  // its launches' blocks
-    std::vector<size_t> group_off;                              // and its slots' workspace in the tt region
-    size_t group_lds[2] = {};
-    bool group_dd = false;
+    std::vector<GroupSlot> group_slots;  // their descriptors, pointers still to come
+    std::vector<size_t> group_off;       // their workspace in the tt region
+    GroupLists group_lists;
     std::vector<int32_t> all_ids;  // the slots whose matrices the batch initialises (not the resident sweep's)
     std::vector<int64_t> edge_begin;
     std::vector<size_t> edge_copy_off;  // per slot: byte offset in the edge region, or SIZE_MAX (device edges)
@@ -44,48 +42,6 @@ struct BatchPlan {
     size_t off_group = 0, off_group_maps = 0, off_edge_begin = 0, off_es = 0, off_edges = 0, off_tt = 0, total = 0;
     std::vector<size_t> tt_off;  // per slot: byte offset of its transposes (large) in the tt region
 };
-
-// Blocks of the group sweep's launches.  Workgroups go to the eight XCDs in
-// turn by their number, so an instance's row groups are placed eight apart:
-// the rows they pull from each other then come through one XCD's L2.  The
-// widest instances go first, each to the XCD with the fewest words so far.
-void group_maps(BatchPlan& p) {
-    constexpr int kXcds = 8;
-    std::vector<size_t> order(p.group.size());
-    std::iota(order.begin(), order.end(), size_t{0});
-    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) {
-        return p.descs[p.group[a]].W > p.descs[p.group[b]].W;
-    });
-    for (int wide = 0; wide < 2; ++wide) {
-        std::vector<int32_t> per[kXcds];
-        int64_t words[kXcds] = {};
-        for (size_t k : order) {
-            const SlotDesc& d = p.descs[p.group[k]];
-            if ((d.W > 32) != (wide == 1)) continue;
-            const auto x = std::min_element(words, words + kXcds) - words;
-            words[x] += static_cast<int64_t>(d.n) * d.W;
-            for (int32_t r = 0; r < (d.n + kGsRows - 1) / kGsRows; ++r)
-                per[x].push_back(static_cast<int32_t>(k) << 16 | r);
-            p.group_lds[wide] = std::max(p.group_lds[wide], group_lds(d.W, p.group_grammars[k].n_dyn));
-        }
-        size_t most = 0;
-        for (const auto& v : per) most = std::max(most, v.size());
-        p.group_rows[wide].assign(most * kXcds, -1);
-        for (int x = 0; x < kXcds; ++x)
-            for (size_t q = 0; q < per[x].size(); ++q) p.group_rows[wide][q * kXcds + x] = per[x][q];
-    }
-    for (size_t k : order) {
-        const GroupGrammar& g = p.group_grammars[k];
-        const int32_t base = static_cast<int32_t>(k) << 16, side = p.descs[p.group[k]].npad / 256;
-        for (int32_t ij = 0; ij < side * side; ++ij) {
-            const int32_t tile = (ij / side) << 4 | (ij % side);
-            for (int32_t r = 0; r < g.n_dd; ++r) p.group_tiles.push_back(base | r << 8 | tile);
-            for (int32_t c = 0; c < g.n_dyn; ++c)
-                if (g.tt_slot[c] >= 0) p.group_trans.push_back(base | c << 8 | tile);
-        }
-        p.group_dd = p.group_dd || g.n_dd > 0;
-    }
-}
 
 // Tables and workspace layout of a batch.  Each instance takes its route
 // from batch_route (forced, or the tuning table); the workspace reserves the
@@ -155,7 +111,7 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
                            p.group.size() < kGroupMaxSlots && group_grammar(gr, d.n, g.n_edges, &gg);
         if (swept) {
             p.group.push_back(i);
-            p.group_grammars.push_back(gg);
+            p.group_slots.push_back(group_slot(gg, d.n));
             p.group_off.push_back(tt_bytes);
             tt_bytes += group_layout(gg, d.n, nullptr, nullptr);
         } else if (d.n_rules > 0) {
@@ -236,10 +192,9 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
     p.off_sweep = take(4 * static_cast<size_t>(n));
     p.off_all = take(4 * static_cast<size_t>(n));
     p.off_edge_begin = take(8 * (static_cast<size_t>(n) + 1));
-    group_maps(p);
+    p.group_lists.add(p.group_slots.data(), 0, static_cast<int32_t>(p.group.size()));
     p.off_group = take(sizeof(GroupSlot) * p.group.size());
-    p.off_group_maps = take(4 * (p.group_rows[0].size() + p.group_rows[1].size() + p.group_tiles.size() +
-                                 p.group_trans.size()));
+    p.off_group_maps = take(4 * p.group_lists.size());
     p.off_es = take(sizeof(EngineState));
     p.off_edges = take(edge_bytes);
     p.off_tt = take(tt_bytes);
@@ -585,8 +540,8 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
     auto* d_group = reinterpret_cast<GroupSlot*>(ws + p.off_group);
     for (int32_t k = 0; k < n_group; ++k) {
         const SlotDesc& sd = p.descs[p.group[k]];
-        GroupSlot q{};
-        group_layout(p.group_grammars[k], sd.n, ws + p.off_tt + p.group_off[k], &q);
+        GroupSlot& q = p.group_slots[k];
+        group_layout(q.g, sd.n, ws + p.off_tt + p.group_off[k], &q);
         q.T = sd.T;
         q.edges = sd.edges;
         q.n_edges = sd.n_edges;
@@ -597,21 +552,8 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
         put(p.off_group + sizeof(GroupSlot) * k, &q, sizeof(q));
     }
     GroupMaps maps;
-    {
-        size_t at = p.off_group_maps;
-        auto list = [&](const std::vector<int32_t>& v, const int32_t** where, int32_t* count) {
-            put(at, v.data(), 4 * v.size());
-            *where = reinterpret_cast<const int32_t*>(ws + at);
-            *count = static_cast<int32_t>(v.size());
-            at += 4 * v.size();
-        };
-        for (int wide = 0; wide < 2; ++wide) {
-            list(p.group_rows[wide], &maps.rows[wide], &maps.n_rows[wide]);
-            maps.lds[wide] = p.group_lds[wide];
-        }
-        list(p.group_tiles, &maps.tiles, &maps.n_tiles);
-        list(p.group_trans, &maps.trans, &maps.n_trans);
-    }
+    p.group_lists.put(reinterpret_cast<int32_t*>(img + (p.off_group_maps - tab_begin)),
+                      reinterpret_cast<const int32_t*>(ws + p.off_group_maps), &maps);
     EngineState es0;
     std::memset(&es0, 0, sizeof(es0));
     es0.n_large = static_cast<int32_t>(p.large.size());
@@ -662,14 +604,14 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
     Drain drain{s, n_group > 0};
     if (n_group > 0) {
         int32_t max_lists = 0;
-        for (const GroupGrammar& g : p.group_grammars) max_lists = std::max(max_lists, g.n_list);
+        for (const GroupSlot& q : p.group_slots) max_lists = std::max(max_lists, q.g.n_list);
         CFPQ_HIP(group_init(d_group, n_group, max_lists, s));
         auto* rep = reinterpret_cast<GroupReport*>(img + rep_slots);
         rep[0].loop = rep[1].loop = 0;
-        bool dd = p.group_dd;
+        bool dd = maps.n_tiles > 0;
         int32_t t = 0;
         for (int slot = 0;; slot ^= 1) {
-            for (int q = 0; q < kGroupLoops; ++q) CFPQ_HIP(group_loop(d_group, maps, ++t, dd, s));
+            for (int q = 0; q < kGroupLoops; ++q, ++t) CFPQ_HIP(group_loop(d_group, maps, t + 1, t == 0, dd, s));
             CFPQ_HIP(group_report(d_group, n_group, t, &rep[slot], s));
             if (t == kGroupLoops) continue;
             const GroupReport* r = &rep[slot ^ 1];
@@ -677,7 +619,7 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
             if (r->running == 0) break;
             dd = dd && r->running_dd > 0;
         }
-        CFPQ_HIP(group_finish(d_group, n_group, b.states, s));
+        CFPQ_HIP(group_finish(d_group, n_group, t, b.states, s));
     }
 
     // Large instances: captured loops over the shared work list.

@@ -17,6 +17,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <vector>
 
 #include "sweep.h"
 
@@ -61,6 +62,7 @@ struct GroupSlot {
     int64_t n_edges, max_iters, mat_words;
     int32_t n, W, n_nt, n_terminals, groups;
     int32_t slot;   // the engine's slot whose SlotState gets the result
+    uint32_t base;  // loops of the group before the instance joined: its own t = loop - base
 };
 
 // Work of a launch, a block each: slot << 16 | what (row group, tile), -1: none.
@@ -72,24 +74,42 @@ struct GroupMaps {
     size_t lds[2] = {};
 };
 
+// The blocks of slots [begin, end) of a table.  Workgroups go to the eight XCDs
+// in turn by their number, so an instance's row groups are placed eight apart:
+// the rows they pull from each other then come through one XCD's L2.  The
+// widest instances go first, each to the XCD with the fewest words so far.
+struct GroupLists {
+    std::vector<int32_t> rows[2], tiles, trans;
+    size_t lds[2] = {};
+    void add(const GroupSlot* slots, int32_t begin, int32_t end);
+    size_t size() const { return rows[0].size() + rows[1].size() + tiles.size() + trans.size(); }
+    // Writes the lists to host, as they will lie at device; the entries written.
+    size_t put(int32_t* host, const int32_t* device, GroupMaps* m) const;
+};
+
 // What the host reads while loops are in flight (pinned host memory).
 struct GroupReport {
     int32_t loop, running, running_dd, pad;
 };
 
-// Whether an instance may run here, its packed grammar, and the workspace it
-// needs from ws on (the pointers of *d are set when ws is not null).
+// Whether an instance may run here, its packed grammar, its descriptor without
+// pointers, and the workspace it needs from ws on (the pointers of *d into it
+// are set when ws is not null).
 bool group_grammar(const cfpq_grammar* gr, int32_t n_nodes, int64_t n_edges, GroupGrammar* g);
+GroupSlot group_slot(const GroupGrammar& g, int32_t n_nodes);
 size_t group_layout(const GroupGrammar& g, int32_t n_nodes, char* ws, GroupSlot* d);
 
 // Clears what must be clear, sets the edges' bits and builds the lists.
 hipError_t group_init(const GroupSlot* slots, int32_t count, int32_t max_lists, hipStream_t s);
-// Loop t (1, 2, ...) of every slot; with_dd: some slot that still runs has dd rules.
-hipError_t group_loop(const GroupSlot* slots, const GroupMaps& m, int32_t t, bool with_dd, hipStream_t s);
-hipError_t group_report(const GroupSlot* slots, int32_t count, int32_t t, GroupReport* out, hipStream_t s);
-// The slots' loops, products, caps and bad edges into the engine's states.
+// Loop `loop` of the group (an instance's own loop is loop - base; first: that is
+// 1 for all of them).  with_dd: some slot that still runs has dd rules.
+hipError_t group_loop(const GroupSlot* slots, const GroupMaps& m, uint32_t loop, bool first, bool with_dd,
+                      hipStream_t s);
+hipError_t group_report(const GroupSlot* slots, int32_t count, uint32_t loop, GroupReport* out, hipStream_t s);
+// The slots' loops, products, caps and bad edges into the engine's states;
+// those that `loop` did not change are done.
 struct SlotState;
-hipError_t group_finish(const GroupSlot* slots, int32_t count, SlotState* states, hipStream_t s);
+hipError_t group_finish(const GroupSlot* slots, int32_t count, uint32_t loop, SlotState* states, hipStream_t s);
 
 // LDS bytes of a workgroup for rows of W words.
 inline size_t group_lds(int64_t W, int32_t n_dyn) {

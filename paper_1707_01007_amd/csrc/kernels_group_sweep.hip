@@ -1,5 +1,6 @@
 // Kernels of the group sweep (see group_sweep.h).
 #include <algorithm>
+#include <numeric>
 
 #include "batch_engine.h"
 #include "group_sweep.h"
@@ -122,6 +123,11 @@ __device__ __forceinline__ int left_of(uint32_t r) { return (r >> 8) & 255u; }
 __device__ __forceinline__ int right_of(uint32_t r) { return (r >> 16) & 255u; }
 __device__ __forceinline__ int in_of(uint32_t r) { return r >> 24; }
 
+// The instance's own number of the group's loop.
+__device__ __forceinline__ int32_t own_loop(const GroupSlot& d, uint32_t loop) {
+    return static_cast<int32_t>(loop - d.base);
+}
+
 // The change mask loop t starts from: before the first loop, what the edges set.
 __device__ __forceinline__ uint32_t mask_before(const GroupSlot& d, int32_t t) {
     return t == 1 ? d.g.init_mask : d.ctl->any[(t - 1) & 3];
@@ -132,12 +138,13 @@ __device__ __forceinline__ uint32_t mask_before(const GroupSlot& d, int32_t t) {
 // 256 x 256 tile.
 __global__ __launch_bounds__(256) void group_transpose_kernel(const GroupSlot* __restrict__ slots,
                                                               const int32_t* __restrict__ map, int32_t count,
-                                                              int32_t t) {
+                                                              uint32_t loop) {
     const int32_t item = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     if (item >= count) return;
     const int32_t m = map[item];
     const GroupSlot& d = slots[m >> 16];
     const int c = (m >> 8) & 255;
+    const int32_t t = own_loop(d, loop);
     if (t > d.max_iters || (t > 1 && !((mask_before(d, t) >> c) & 1u))) return;
     const int64_t br0 = ((m >> 4) & 15) * 4, bc0 = (m & 15) * 4;
     const int lane = threadIdx.x & 63;
@@ -156,9 +163,10 @@ __global__ __launch_bounds__(256) void group_transpose_kernel(const GroupSlot* _
 // workgroup (eight wavefronts of 64 x 128, two a SIMD: the few chunks of these
 // products are latency that the other wavefront hides).
 __global__ __launch_bounds__(512) void group_product_kernel(const GroupSlot* __restrict__ slots,
-                                                            const int32_t* __restrict__ map, int32_t t) {
+                                                            const int32_t* __restrict__ map, uint32_t loop) {
     const int32_t m = map[blockIdx.x];
     const GroupSlot& d = slots[m >> 16];
+    const int32_t t = own_loop(d, loop);
     const uint32_t rule = d.g.rule[d.g.n_lf + d.g.n_rf + d.g.n_ll + ((m >> 8) & 255)];
     const uint32_t before = mask_before(d, t);
     if (t > d.max_iters || !(((before >> left_of(rule)) | (before >> right_of(rule))) & 1u)) return;
@@ -544,13 +552,14 @@ __device__ __forceinline__ void group_rows(const GroupSlot& d, int32_t t, int32_
 // wavefronts' registers.
 template <bool kFirst, bool kWide>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWide ? 3 : 6))) void group_sweep_kernel(const GroupSlot* __restrict__ slots,
-                                                          const int32_t* __restrict__ map, int32_t t) {
+                                                          const int32_t* __restrict__ map, uint32_t loop) {
     extern __shared__ __align__(16) uint64_t buf[];
     __shared__ GroupShared sh;
     const int32_t m = map[blockIdx.x];
     if (m < 0) return;
     const GroupSlot& d = slots[m >> 16];
     const int32_t grp = m & 0xFFFF;
+    const int32_t t = own_loop(d, loop);
     GroupCtl* ctl = d.ctl;
     const uint32_t before = mask_before(d, t);
     const bool run = (kFirst || before != 0) && t <= d.max_iters;
@@ -582,26 +591,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWide ? 3 :
 }
 
 template <bool kWide>
-hipError_t sweep_launch(const GroupSlot* slots, const int32_t* map, int32_t blocks, int32_t t, size_t lds,
-                        hipStream_t s) {
+hipError_t sweep_launch(const GroupSlot* slots, const int32_t* map, int32_t blocks, uint32_t loop, bool first,
+                        size_t lds, hipStream_t s) {
     if (blocks == 0) return hipSuccess;
     const dim3 grid(static_cast<unsigned>(blocks));
-    if (t == 1)
-        group_sweep_kernel<true, kWide><<<grid, dim3(256), lds, s>>>(slots, map, t);
+    if (first)
+        group_sweep_kernel<true, kWide><<<grid, dim3(256), lds, s>>>(slots, map, loop);
     else
-        group_sweep_kernel<false, kWide><<<grid, dim3(256), lds, s>>>(slots, map, t);
+        group_sweep_kernel<false, kWide><<<grid, dim3(256), lds, s>>>(slots, map, loop);
     return hipGetLastError();
 }
 
 // One workgroup: how many instances changed in loop t.
 __global__ __launch_bounds__(256) void group_report_kernel(const GroupSlot* __restrict__ slots, int32_t count,
-                                                           int32_t t, GroupReport* out) {
+                                                           uint32_t loop, GroupReport* out) {
     __shared__ int32_t run_s, dd_s;
     if (threadIdx.x == 0) run_s = dd_s = 0;
     __syncthreads();
     int32_t run = 0, dd = 0;
     for (int32_t i = threadIdx.x; i < count; i += 256) {
-        const bool on = slots[i].ctl->any[t & 3] != 0;
+        const bool on = slots[i].ctl->any[own_loop(slots[i], loop) & 3] != 0;
         run += on ? 1 : 0;
         dd += on && slots[i].g.n_dd > 0 ? 1 : 0;
     }
@@ -612,11 +621,11 @@ __global__ __launch_bounds__(256) void group_report_kernel(const GroupSlot* __re
     out->running = run_s;
     out->running_dd = dd_s;
     __threadfence_system();
-    __hip_atomic_store(&out->loop, t, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&out->loop, static_cast<int32_t>(loop), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 __global__ __launch_bounds__(64) void group_finish_kernel(const GroupSlot* __restrict__ slots, int32_t count,
-                                                          SlotState* states) {
+                                                          uint32_t loop, SlotState* states) {
     const int32_t i = blockIdx.x * 64 + threadIdx.x;
     if (i >= count) return;
     const GroupCtl& c = *slots[i].ctl;
@@ -625,8 +634,8 @@ __global__ __launch_bounds__(64) void group_finish_kernel(const GroupSlot* __res
     st.products = c.products;
     st.capped = c.capped;
     st.bad_edges = c.bad_edges;
-    st.done = 1;
-    st.active = 0;
+    st.done = c.any[own_loop(slots[i], loop) & 3] == 0 ? 1 : 0;
+    st.active = 1 - st.done;
 }
 
 }  // namespace
@@ -668,6 +677,17 @@ bool group_grammar(const cfpq_grammar* gr, int32_t n_nodes, int64_t n_edges, Gro
     return true;
 }
 
+GroupSlot group_slot(const GroupGrammar& g, int32_t n_nodes) {
+    const Layout L = layout_for(n_nodes);
+    GroupSlot d{};
+    d.g = g;
+    d.mat_words = L.mat_words;
+    d.n = n_nodes;
+    d.W = static_cast<int32_t>(L.W);
+    d.groups = (n_nodes + kGsRows - 1) / kGsRows;
+    return d;
+}
+
 size_t group_layout(const GroupGrammar& g, int32_t n_nodes, char* ws, GroupSlot* d) {
     const Layout L = layout_for(n_nodes);
     const size_t mat = static_cast<size_t>(L.mat_words) * 8;
@@ -698,7 +718,6 @@ size_t group_layout(const GroupGrammar& g, int32_t n_nodes, char* ws, GroupSlot*
     const size_t list = take(lists * 8), near = take(lists * 16);
     const size_t idx = take(static_cast<size_t>(sweep_max_edges(L)) * per_edge * 4);
     if (ws != nullptr) {
-        d->g = g;
         d->D[0] = reinterpret_cast<uint64_t*>(ws + d0);
         d->D[1] = reinterpret_cast<uint64_t*>(ws + d1);
         d->P = reinterpret_cast<uint64_t*>(ws + p);
@@ -709,10 +728,6 @@ size_t group_layout(const GroupGrammar& g, int32_t n_nodes, char* ws, GroupSlot*
         d->list = reinterpret_cast<int2*>(ws + list);
         d->near = reinterpret_cast<uint4*>(ws + near);
         d->idx = reinterpret_cast<int32_t*>(ws + idx);
-        d->mat_words = L.mat_words;
-        d->n = n_nodes;
-        d->W = static_cast<int32_t>(L.W);
-        d->groups = groups;
     }
     return off;
 }
@@ -724,26 +739,82 @@ hipError_t group_init(const GroupSlot* slots, int32_t count, int32_t max_lists, 
     return hipGetLastError();
 }
 
-hipError_t group_loop(const GroupSlot* slots, const GroupMaps& m, int32_t t, bool with_dd, hipStream_t s) {
+hipError_t group_loop(const GroupSlot* slots, const GroupMaps& m, uint32_t loop, bool first, bool with_dd,
+                      hipStream_t s) {
     if (with_dd && m.n_tiles > 0) {
         group_transpose_kernel<<<dim3(static_cast<unsigned>((m.n_trans + 3) / 4)), dim3(256), 0, s>>>(slots, m.trans,
-                                                                                                    m.n_trans, t);
-        group_product_kernel<<<dim3(static_cast<unsigned>(m.n_tiles)), dim3(512), 0, s>>>(slots, m.tiles, t);
+                                                                                                    m.n_trans, loop);
+        group_product_kernel<<<dim3(static_cast<unsigned>(m.n_tiles)), dim3(512), 0, s>>>(slots, m.tiles, loop);
     }
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = sweep_launch<false>(slots, m.rows[0], m.n_rows[0], t, m.lds[0], s);
-    if (e == hipSuccess) e = sweep_launch<true>(slots, m.rows[1], m.n_rows[1], t, m.lds[1], s);
+    if (e == hipSuccess) e = sweep_launch<false>(slots, m.rows[0], m.n_rows[0], loop, first, m.lds[0], s);
+    if (e == hipSuccess) e = sweep_launch<true>(slots, m.rows[1], m.n_rows[1], loop, first, m.lds[1], s);
     return e;
 }
 
-hipError_t group_report(const GroupSlot* slots, int32_t count, int32_t t, GroupReport* out, hipStream_t s) {
-    group_report_kernel<<<dim3(1), dim3(256), 0, s>>>(slots, count, t, out);
+hipError_t group_report(const GroupSlot* slots, int32_t count, uint32_t loop, GroupReport* out, hipStream_t s) {
+    group_report_kernel<<<dim3(1), dim3(256), 0, s>>>(slots, count, loop, out);
     return hipGetLastError();
 }
 
-hipError_t group_finish(const GroupSlot* slots, int32_t count, SlotState* states, hipStream_t s) {
-    group_finish_kernel<<<dim3(static_cast<unsigned>((count + 63) / 64)), dim3(64), 0, s>>>(slots, count, states);
+hipError_t group_finish(const GroupSlot* slots, int32_t count, uint32_t loop, SlotState* states, hipStream_t s) {
+    group_finish_kernel<<<dim3(static_cast<unsigned>((count + 63) / 64)), dim3(64), 0, s>>>(slots, count, loop,
+                                                                                         states);
     return hipGetLastError();
+}
+
+void GroupLists::add(const GroupSlot* slots, int32_t begin, int32_t end) {
+    constexpr int kXcds = 8;
+    std::vector<int32_t> order(end - begin);
+    std::iota(order.begin(), order.end(), begin);
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return slots[a].W > slots[b].W; });
+    for (int wide = 0; wide < 2; ++wide) {
+        std::vector<int32_t> per[kXcds];
+        int64_t words[kXcds] = {};
+        lds[wide] = 0;
+        for (int32_t k : order) {
+            const GroupSlot& d = slots[k];
+            if ((d.W > 32) != (wide == 1)) continue;
+            const auto x = std::min_element(words, words + kXcds) - words;
+            words[x] += static_cast<int64_t>(d.n) * d.W;
+            for (int32_t r = 0; r < d.groups; ++r) per[x].push_back(k << 16 | r);
+            lds[wide] = std::max(lds[wide], group_lds(d.W, d.g.n_dyn));
+        }
+        size_t most = 0;
+        for (const auto& v : per) most = std::max(most, v.size());
+        rows[wide].assign(most * kXcds, -1);
+        for (int x = 0; x < kXcds; ++x)
+            for (size_t q = 0; q < per[x].size(); ++q) rows[wide][q * kXcds + x] = per[x][q];
+    }
+    tiles.clear();
+    trans.clear();
+    for (int32_t k : order) {
+        const GroupGrammar& g = slots[k].g;
+        const int32_t side = slots[k].W / 4;
+        for (int32_t ij = 0; g.n_dd > 0 && ij < side * side; ++ij) {
+            const int32_t tile = (ij / side) << 4 | (ij % side);
+            for (int32_t r = 0; r < g.n_dd; ++r) tiles.push_back(k << 16 | r << 8 | tile);
+            for (int32_t c = 0; c < g.n_dyn; ++c)
+                if (g.tt_slot[c] >= 0) trans.push_back(k << 16 | c << 8 | tile);
+        }
+    }
+}
+
+size_t GroupLists::put(int32_t* host, const int32_t* device, GroupMaps* m) const {
+    size_t at = 0;
+    auto list = [&](const std::vector<int32_t>& v, const int32_t** where, int32_t* count) {
+        std::copy(v.begin(), v.end(), host + at);
+        *where = device + at;
+        *count = static_cast<int32_t>(v.size());
+        at += v.size();
+    };
+    for (int wide = 0; wide < 2; ++wide) {
+        list(rows[wide], &m->rows[wide], &m->n_rows[wide]);
+        m->lds[wide] = lds[wide];
+    }
+    list(tiles, &m->tiles, &m->n_tiles);
+    list(trans, &m->trans, &m->n_trans);
+    return at;
 }
 
 }  // namespace cfpq

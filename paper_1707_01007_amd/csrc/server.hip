@@ -6,8 +6,10 @@
 //  1. admits queued requests in arrival order while a slot is free and the
 //     request's HBM footprint fits the arena (first fit),
 //  2. initialises the admitted requests' matrices; small ones start their
-//     resident fixpoint on a side stream, large ones join the shared work list,
-//  3. replays the captured loops of the large engine once (K loops),
+//     resident fixpoint on a side stream, those of 513 to 4096 nodes join the
+//     group sweep (group_sweep.h), the other large ones the shared work list,
+//  3. queues K loops of the group sweep and replays the K captured loops of the
+//     large engine once,
 //  4. retires every request that reached its fixpoint: copies its matrices to
 //     the caller's buffer, frees its slot and arena block, stamps its latency.
 // Requests that arrive while others are on the GPU therefore join at the next
@@ -35,6 +37,7 @@
 #include <vector>
 
 #include "batch_engine.h"
+#include "group_sweep.h"
 #include "resident.h"
 
 namespace cfpq {
@@ -83,6 +86,20 @@ __global__ __launch_bounds__(256) void upload_slots_kernel(const uint32_t* __res
     }
 }
 
+// The group sweep's tables, in an arena block while it has requests: a slot
+// each, and the launches' block lists (of all its requests, and of the new
+// ones: together at most kGroupEntries).
+constexpr int64_t kGroupEntries = 128 * 1024;
+inline size_t group_table_bytes(int32_t slots) {
+    return align_up(sizeof(GroupSlot) * static_cast<size_t>(slots), 256) + 4 * kGroupEntries;
+}
+// Most list entries one request takes.
+inline int64_t group_entries(const GroupGrammar& g, const Layout& L) {
+    int64_t per_tile = g.n_dd;
+    for (int c = 0; c < g.n_dyn; ++c) per_tile += g.tt_slot[c] >= 0 ? 1 : 0;
+    return 8 * L.W + (g.n_dd > 0 ? per_tile * (L.W / 4) * (L.W / 4) : 0);
+}
+
 double now_s() {
     using namespace std::chrono;
     return duration<double>(steady_clock::now().time_since_epoch()).count();
@@ -103,6 +120,10 @@ struct Request {
     bool lane = false;   // runs on a lane thread (hybrid closure)
     bool swept = false;  // small: by the resident sweep, launched as planned
     ResidentPlan sweep;
+    bool group_fits = false;  // may run in the group sweep
+    bool grouped = false;     // does (decided at admission)
+    GroupGrammar group;
+    size_t group_footprint = 0;
     int32_t n_right = 0;
     std::vector<int32_t> modes;  // per binary rule: engine product mode (large slots)
     size_t footprint = 0;
@@ -186,6 +207,16 @@ struct cfpq_server {
     std::vector<cfpq::Request*> slot_req;
     std::map<int64_t, cfpq::SmallBatch> small_batches;
     int64_t next_batch = 0;
+    // the group sweep: its requests' slots in the order of its table, how many
+    // of them have begun, the loops it has run, its table's arena block
+    std::vector<cfpq::GroupSlot> group;
+    int32_t group_begun = 0;
+    bool group_changed = false;
+    uint32_t group_loop = 0;
+    int64_t group_entries = 0;
+    bool group_table = false;
+    size_t group_table_off = 0;
+    cfpq::GroupMaps group_maps;
     std::mutex mu;
     std::condition_variable cv, done_cv;
     std::deque<cfpq::Request*> pending;
@@ -247,6 +278,13 @@ size_t footprint_of(const Request& r) {
     return f;
 }
 
+// In the group sweep: the matrices, its workspace, the edges.
+size_t group_footprint_of(const Request& r) {
+    return align_up(static_cast<size_t>(r.L.mat_words) * 8 * r.n_nt, 256) +
+           align_up(group_layout(r.group, r.n, nullptr, nullptr), 256) +
+           align_up(r.host_edges.size() * sizeof(cfpq_edge), 256);
+}
+
 #define SRV_HIP(call)                                                                              \
     do {                                                                                           \
         hipError_t e_ = (call);                                                                    \
@@ -266,7 +304,10 @@ void fill_slot(cfpq_server* srv, Request& r, SlotDesc& d, std::vector<int32_t>& 
     d.T = reinterpret_cast<uint64_t*>(base);
     size_t off = align_up(mat * r.n_nt, 256);
     d.TT = reinterpret_cast<uint64_t*>(base + off);
-    if (!r.small) off += align_up(mat * r.n_right, 256);
+    if (r.grouped)
+        off += align_up(group_layout(r.group, r.n, nullptr, nullptr), 256);
+    else if (!r.small)
+        off += align_up(mat * r.n_right, 256);
     d.edges = r.dev_edges ? r.dev_edges : reinterpret_cast<const cfpq_edge*>(base + off);
     d.n_edges = r.n_edges;
     d.n = r.n;
@@ -316,17 +357,19 @@ bool turn(cfpq_server* srv, std::vector<Request*>& admitted) {
     // states read back at retirement.  The last turn ended synchronised, so
     // no copy still reads it.
     const size_t up_bytes = static_cast<size_t>(S) * kUpWords * 4;
+    const size_t state_bytes = align_up(sizeof(SlotState) * S, 256);
     void* pin = nullptr;
-    SRV_HIP(pinned_readback(up_bytes + sizeof(SlotState) * S, &pin));
+    SRV_HIP(pinned_readback(up_bytes + state_bytes + group_table_bytes(S), &pin));
     uint32_t* up = static_cast<uint32_t*>(pin);
     void* pin_states = static_cast<char*>(pin) + up_bytes;
+    char* pin_group = static_cast<char*>(pin) + up_bytes + state_bytes;
     // ---- 2. initialise admitted requests ----
     if (!admitted.empty()) {
         std::vector<int32_t> s8, s16, sweep[kResidentClasses];
         int32_t sweep_lds[kResidentClasses] = {};
-        // the resident sweep initialises its own slots: the others come first
+        // the resident and the group sweep initialise their own slots: the others come first
         const auto own = std::stable_partition(admitted.begin(), admitted.end(),
-                                               [](const Request* r) { return !r->swept; });
+                                               [](const Request* r) { return !r->swept && !r->grouped; });
         const int32_t k_init = static_cast<int32_t>(own - admitted.begin());
         int64_t edges_end = 0, edges_init = 0;
         const int32_t k = static_cast<int32_t>(admitted.size());
@@ -355,7 +398,19 @@ bool turn(cfpq_server* srv, std::vector<Request*>& admitted) {
             std::memcpy(rec + kUpTrans, trans.data(), 4 * trans.size());
             std::memcpy(rec + kUpTerm, term.data(), 4 * term.size());
             std::memcpy(rec + kUpState, &st, sizeof(st));
-            if (x >= k_init) {
+            if (r->grouped) {
+                GroupSlot q = group_slot(r->group, r->n);
+                group_layout(r->group, r->n, reinterpret_cast<char*>(d.TT), &q);
+                q.T = d.T;
+                q.edges = d.edges;
+                q.n_edges = d.n_edges;
+                q.max_iters = d.max_iters;
+                q.n_nt = d.n_nt;
+                q.n_terminals = d.n_terminals;
+                q.slot = r->slot;
+                srv->group.push_back(q);
+                srv->group_changed = true;
+            } else if (x >= k_init) {
                 sweep[r->sweep.cls].push_back(r->slot);
                 sweep_lds[r->sweep.cls] = std::max(sweep_lds[r->sweep.cls], r->sweep.lds);
             } else if (d.n_rules > 0 && r->small) {
@@ -372,7 +427,9 @@ bool turn(cfpq_server* srv, std::vector<Request*>& admitted) {
         // scatter; the request runs on the rest and fails when it retires (the
         // count comes back with the states, no round trip here).
         SRV_HIP(engine_scatter(srv->b, srv->ids_init, k_init, edges_init, s));
-        if (!s8.empty() || !s16.empty() || k_init < k) {
+        bool resident = !s8.empty() || !s16.empty();
+        for (const auto& v : sweep) resident = resident || !v.empty();
+        if (resident) {
             // The slot list of a launch sits at one of 64 ring positions in
             // device memory; the batch that used the position before must have
             // finished reading it.
@@ -406,12 +463,49 @@ bool turn(cfpq_server* srv, std::vector<Request*>& admitted) {
             srv->small_batches.emplace(id, sb);
         }
     }
-    // ---- 3. large slots: the current list (new ones included), their first
+    // ---- 3a. the group sweep: the new requests' first loop, then K loops of all
+    const int32_t ng = static_cast<int32_t>(srv->group.size());
+    if (ng > 0) {
+        auto* table = reinterpret_cast<GroupSlot*>(srv->arena_base + srv->group_table_off);
+        const size_t lists_at = align_up(sizeof(GroupSlot) * static_cast<size_t>(S), 256);
+        auto* d_lists = reinterpret_cast<const int32_t*>(srv->arena_base + srv->group_table_off + lists_at);
+        auto* h_lists = reinterpret_cast<int32_t*>(pin_group + lists_at);
+        const int32_t begun = srv->group_begun;
+        GroupMaps fresh;
+        if (srv->group_changed) {
+            int32_t max_lists = 0;
+            for (int32_t q = begun; q < ng; ++q) {
+                srv->group[q].base = srv->group_loop - 1;  // its first loop carries the last one's number
+                max_lists = std::max(max_lists, srv->group[q].g.n_list);
+            }
+            GroupLists all, added;
+            all.add(srv->group.data(), 0, ng);
+            size_t entries = all.put(h_lists, d_lists, &srv->group_maps);
+            if (begun < ng) {
+                added.add(srv->group.data(), begun, ng);
+                entries += added.put(h_lists + entries, d_lists + entries, &fresh);
+            }
+            std::memcpy(pin_group, srv->group.data(), sizeof(GroupSlot) * ng);
+            SRV_HIP(hipMemcpyAsync(table, pin_group, sizeof(GroupSlot) * ng, hipMemcpyHostToDevice, s));
+            SRV_HIP(hipMemcpyAsync(srv->arena_base + srv->group_table_off + lists_at, h_lists, 4 * entries,
+                                   hipMemcpyHostToDevice, s));
+            if (begun < ng) {
+                SRV_HIP(group_init(table + begun, ng - begun, max_lists, s));
+                SRV_HIP(group_loop(table, fresh, srv->group_loop, true, true, s));
+            }
+            srv->group_begun = ng;
+            srv->group_changed = false;
+        }
+        for (int32_t q = 0; q < srv->cfg.capture; ++q)
+            SRV_HIP(group_loop(table, srv->group_maps, ++srv->group_loop, false, true, s));
+        SRV_HIP(group_finish(table, ng, srv->group_loop, srv->b.states, s));
+    }
+    // ---- 3b. large slots: the current list (new ones included), their first
     //         transposes, then one replay of the captured loops ----
     std::vector<int32_t> large;
     for (int32_t q = 0; q < S; ++q) {
         Request* r = srv->slot_req[q];
-        if (r && !r->small && r->status == CFPQ_OK && srv->hstates[q].active && !srv->hstates[q].done)
+        if (r && !r->small && !r->grouped && r->status == CFPQ_OK && srv->hstates[q].active && !srv->hstates[q].done)
             large.push_back(q);
     }
     std::stable_sort(large.begin(), large.end(), [&](int32_t a, int32_t c) {
@@ -482,10 +576,21 @@ bool turn(cfpq_server* srv, std::vector<Request*>& admitted) {
             if (r->status == CFPQ_OK && st.capped) r->status = CFPQ_ENOTCONV;
             r->state = 2;
             if (r->small && r->small_batch >= 0) srv->small_batches.at(r->small_batch).live -= 1;
+            if (r->grouped) {
+                srv->group.erase(std::find_if(srv->group.begin(), srv->group.end(),
+                                              [&](const GroupSlot& x) { return x.slot == q; }));
+                srv->group_begun = static_cast<int32_t>(srv->group.size());
+                srv->group_changed = true;
+                srv->group_entries -= group_entries(r->group, r->L);
+            }
             srv->arena.release(r->arena_off, r->footprint);
             srv->slot_req[q] = nullptr;
             srv->free_slots.push_back(q);
             srv->completed.fetch_add(1);
+        }
+        if (srv->group.empty() && srv->group_table) {
+            srv->arena.release(srv->group_table_off, group_table_bytes(S));
+            srv->group_table = false;
         }
         srv->done_cv.notify_all();
         srv->lane_cv.notify_all();
@@ -603,6 +708,30 @@ void lane_main(cfpq_server* srv, int idx) {
     }
 }
 
+// Room in the arena for a request to join the group sweep; otherwise it runs
+// in the engine, whose footprint is smaller.
+bool admit_group(cfpq_server* srv, Request& r, size_t* off) {
+    if (!r.group_fits) return false;
+    const int64_t entries = group_entries(r.group, r.L);
+    if (2 * (srv->group_entries + entries) > kGroupEntries) return false;
+    const size_t table = group_table_bytes(srv->cfg.max_slots);
+    size_t at = 0;
+    if (!srv->group_table && !srv->arena.alloc(table, &at)) return false;
+    if (!srv->arena.alloc(r.group_footprint, off)) {
+        if (!srv->group_table) srv->arena.release(at, table);
+        return false;
+    }
+    if (!srv->group_table) {
+        srv->group_table = true;
+        srv->group_table_off = at;
+        srv->group_changed = true;
+    }
+    srv->group_entries += entries;
+    r.grouped = true;
+    r.footprint = r.group_footprint;
+    return true;
+}
+
 void worker_main(cfpq_server* srv) {
     if (hipSetDevice(srv->device) != hipSuccess) {
         fail_all(srv, "hipSetDevice failed in the server's worker");
@@ -634,7 +763,7 @@ void worker_main(cfpq_server* srv) {
             while (!srv->pending.empty() && !srv->free_slots.empty()) {
                 Request* r = srv->pending.front();
                 size_t off = 0;
-                if (!srv->arena.alloc(r->footprint, &off)) break;
+                if (!admit_group(srv, *r, &off) && !srv->arena.alloc(r->footprint, &off)) break;
                 srv->pending.pop_front();
                 r->arena_off = off;
                 r->slot = srv->free_slots.back();
@@ -819,6 +948,8 @@ cfpq_status cfpq_server_submit(cfpq_server* srv, const cfpq_graph* graph, const 
         r->n_right = engine_trans_slots(r->bin.data(), nb, r->modes.data(), r->n_nt, false, tr.data());
     }
     r->footprint = footprint_of(*r);
+    r->group_fits = !r->small && !r->lane && group_grammar(grammar, r->n, r->n_edges, &r->group);
+    if (r->group_fits) r->group_footprint = group_footprint_of(*r);
     if (r->footprint > srv->arena_size)
         return fail(CFPQ_ENOMEM, "request needs " + std::to_string(r->footprint) +
                                      " bytes, more than the server's arena");

@@ -88,3 +88,27 @@ def test_group_cut_short_is_sound(cfpq, iters):
         got = cfpq.result_bits(res)
         assert res.status == -4 and res.stats["converged"] == 0 and res.stats["iterations"] == iters
         assert np.array_equal(got | want, want) and not np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("budget", [1 << 30, 14 << 20])
+def test_group_in_a_server(cfpq, budget):
+    """Requests that join a running group, leave it in another order, and (the
+    small arena) fall back to the engine when their workspace does not fit."""
+    import torch
+    rng = np.random.default_rng(5)
+    items = []
+    for q in range(24):
+        n = int(rng.integers(513, 1400))
+        e = graphs.erdos_renyi(n, int(rng.integers(1, 4)) * n, 60 + q, labels=2)[1]
+        items.append((n, torch.from_numpy(e).cuda() if q % 2 else e, GRAMMARS[q % len(GRAMMARS)]))
+    items.append((2200, graphs.erdos_renyi(2200, 2200, 90, labels=2)[1], grammars.anbn()))
+    items.append((300, graphs.erdos_renyi(300, 600, 91, labels=2)[1], grammars.dyck()))
+    print("[gpu-case] group server", budget, file=sys.stderr, flush=True)
+    with cfpq.Server(hbm_budget=budget, max_slots=12, hybrid_lanes=0) as srv:
+        for wave in (items[:3], items[3:], items[::-1]):
+            tickets = [srv.submit(*it) for it in wave]
+            for it, t in zip(wave, tickets):
+                info = srv.wait(t)
+                assert info["status"] == 0
+                want = cfpq.closure(*it)
+                assert bool((info["result"].bits == want.bits).all()), it[0]
