@@ -15,8 +15,8 @@
 // LDS bandwidth of the walks.  Measured against the kernel that multiplied
 // whole matrices every loop (engine_resident_kernel, still used for the Jacobi
 // schedule, for grammars beyond the tables and for lists that do not fit): two
-// cycles of 64 and 63 nodes, 4033 loops, 17.95 -> 5.57 ms (1.4 us a loop); Dyck
-// on G(450, 1800) 607 -> 225 us; same-generation on 100 nodes 124 -> 67 us.
+// cycles of 64 and 63 nodes, 4033 loops, 17.9 -> 3.4 ms (0.8 us a loop); Dyck
+// on G(450, 1800) 627 -> 233 us; same-generation on 100 nodes 120 -> 48 us.
 #include <algorithm>
 
 #include "mfma_tile.h"
@@ -60,6 +60,135 @@ template <int L>
 constexpr int32_t kTurnBits = L == 1 ? 1 : 4;
 
 // kDD: the slots have dd rules.  kTurn: their LDS may hold transposed operands.
+// Following single facts: while a loop gains only a few bits (two cycles, a
+// chain: thousands of loops of one or two), one wavefront applies the rules to
+// those instead of to all rows: a bit (i, j) of C gives A -> B C the bits (k, j)
+// of the edges k -> i of B, a bit (i, j) of B gives A -> B C the bits (i, k) of
+// the edges j -> k of C.  Eight lanes a fact take one entry each of a list's
+// 8-byte form, so pulls and scatters are three dependent LDS operations each
+// (fact, entry, bit), without a barrier or a loop over entries.  More than
+// kFacts bits go back to the rows, whose loops cost the same however many.
+//
+// Two cycles of 64 and 63 nodes: 1.39 -> 0.83 us a loop (2130 cycles, a quarter
+// of them in LDS, the rest some 200 instructions and 30 branches of one
+// wavefront).  Keeping a lone fact in scalar registers measured 4% less and was
+// not worth its code.
+constexpr int32_t kFacts = 32, kRing = 512;
+constexpr uint32_t kNoFact = ~0u;
+__device__ __forceinline__ uint32_t fact(int h, int i, int j) {
+    return static_cast<uint32_t>(h) << 16 | static_cast<uint32_t>(i) << 8 | static_cast<uint32_t>(j);
+}
+
+struct FactQueue {
+    uint32_t q[kRing];
+    int32_t count, capped;
+    int64_t loops, products;
+};
+
+// One wavefront; the facts are in q.q[0, q.count).  Ends with q.count = 0 (the
+// fixpoint, or the cap) or with every pending fact's row marked in chg and any.
+template <typename Rules>
+__device__ __forceinline__ void follow_facts(const Rules& u, FactQueue& q, uint32_t* T, uint32_t* chg, uint32_t* any,
+                                             int64_t t, int64_t max_iters) {
+    const int lane = threadIdx.x & 63, g = lane >> 3, e = lane & 7;
+    const uint64_t below = (1ull << lane) - 1;
+    int64_t products = 0;
+    // positions in the ring: the pending facts from base on, those a pull can
+    // use from `pull_from` on, the next free one
+    uint32_t base = 0, at = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(q.count)), pull_from = 0;
+    uint32_t heads = 0;  // of the pending facts
+    bool lost = false, capped = false;
+    uint32_t pulled_heads = 0;  // heads that some lf rule reads
+    for (int r = 0; r < u.n_lf; ++r) pulled_heads |= 1u << rs_right(u.lf, r);
+    for (uint32_t b = 0; b < at; b += 64) {
+        const int h = b + lane < at ? static_cast<int>(q.q[b + lane] >> 16) : 31;
+        for (int x = 0; x < u.n_dyn; ++x) heads |= __ballot(h == x) != 0 ? 1u << x : 0;
+    }
+    auto mark = [&](uint32_t f) {
+        const int h = f >> 16, i = (f >> 8) & 255;
+        atomicOr(chg + h * u.words + (i >> 5), 1u << (i & 31));
+        atomicOr(any, 1u << h);
+    };
+    // the bits (i, j) of h on the lanes with `on`: the new ones are appended
+    auto add = [&](bool on, int h, int i, int j, uint32_t& seen) {
+        const uint32_t bit = 1u << (j & 31);
+        bool gained = false;
+        if (on) gained = !(atomicOr(T + h * u.mat + i * 4 + (j >> 5), bit) & bit);
+        const uint64_t m = __ballot(gained);
+        if (m == 0) return;
+        seen |= 1u << h;
+        const uint32_t f = fact(h, i, j);
+        const uint32_t more = static_cast<uint32_t>(__popcll(m));
+        if (at + more - base <= kRing) {
+            if (gained) q.q[(at + static_cast<uint32_t>(__popcll(m & below))) % kRing] = f;
+            at += more;
+        } else {  // the loop ends the following
+            if (gained) mark(f);
+            lost = true;
+        }
+    };
+    // put(on, k) for this lane's entry k of list l's node i, then the entries past the eighth
+    auto each = [&](bool on, int l, int i, auto put) {
+        const int node = l * u.n + i;
+        const int k = on ? reinterpret_cast<const uint8_t*>(u.near)[8 * node + e] : 0xFF;
+        put(k < 0xFE, k);
+        const bool more = k == 0xFE;
+        if (__ballot(more) == 0) return;
+        uint32_t x = more ? u.end[node] + 7 : 0;
+        const uint32_t stop = more ? u.end[node + 1] : 0;
+        for (; __ballot(x < stop) != 0; ++x) put(x < stop, x < stop ? static_cast<int>(u.idx[x]) : 0);
+    };
+    auto take = [&](uint32_t from, uint32_t to) { return from + g < to ? q.q[(from + g) % kRing] : kNoFact; };
+    while (true) {
+        if (t >= max_iters) {
+            capped = true;
+            break;
+        }
+        ++t;
+        for (uint32_t m = heads; m != 0; m &= m - 1) products += (u.runs >> (8 * (__ffs(m) - 1))) & 0xFF;
+        const uint32_t end0 = at;
+        uint32_t seen0 = 0, seen1 = 0;
+        for (uint32_t b = pull_from; b < end0; b += 8) {
+            const uint32_t f = take(b, end0);
+            const int h = f >> 16;
+            for (int r = 0; r < u.n_lf; ++r) {
+                const bool on = h == rs_right(u.lf, r);
+                if (__ballot(on) == 0) continue;
+                each(on, static_cast<int>(u.lf_in >> (8 * r)) & 255, (f >> 8) & 255,
+                     [&](bool x, int k) { add(x, rs_head(u.lf, r), k, f & 255, seen0); });
+            }
+        }
+        wave_order();
+        const uint32_t end1 = at;
+        for (uint32_t b = end0; b < end1; b += 8) {
+            const uint32_t f = take(b, end1);
+            const int h = f >> 16;
+            for (int r = 0; r < u.n_rf; ++r) {
+                const bool on = h == rs_left(u.rf, r);
+                if (__ballot(on) == 0) continue;
+                each(on, rs_right(u.rf, r), f & 255,
+                     [&](bool x, int k) { add(x, rs_head(u.rf, r), (f >> 8) & 255, k, seen1); });
+            }
+        }
+        wave_order();
+        base = end0;
+        pull_from = (seen0 & pulled_heads) != 0 ? end0 : end1;
+        heads = seen0 | seen1;
+        if (heads == 0) break;  // the fixpoint
+        if (lost || at - base > kFacts) {
+            for (uint32_t x = base + lane; x < at; x += 64) mark(q.q[x % kRing]);
+            lost = true;
+            break;
+        }
+    }
+    if (lane == 0) {
+        q.count = lost ? 1 : 0;
+        q.capped = capped ? 1 : 0;
+        q.loops = t;
+        q.products = products;
+    }
+}
+
 // d: the slot's descriptor, grammar: where its rules would be, out: its state.
 template <int L, bool kDD, bool kTurn>
 __device__ __forceinline__ void resident_closure(const SlotDesc& d, const int32_t* __restrict__ grammar,
@@ -68,6 +197,7 @@ __device__ __forceinline__ void resident_closure(const SlotDesc& d, const int32_
     constexpr int kGroups = kThreads / L;
     constexpr int RW = 4 * L;  // dwords of a row
     constexpr int kPasses = L == 4 ? 2 : 1;  // rows of a group
+    constexpr bool kQueue = L == 1 && !kDD && !kTurn;
     constexpr int kKept = 2;  // edges a thread keeps between the two passes over them
     extern __shared__ __align__(16) uint32_t lds[];
     __shared__ ResidentGrammar G;
@@ -112,6 +242,7 @@ __device__ __forceinline__ void resident_closure(const SlotDesc& d, const int32_
     uint32_t* D = lds + lay.off_d / 4;
     uint32_t* TT = lds + lay.off_tt / 4;
     uint32_t* chg = lds + lay.off_chg / 4;  // [3][n_dyn][words]
+    uint64_t* near = reinterpret_cast<uint64_t*>(lds) + lay.off_near / 8;
     uint32_t* end = lds + lay.off_end / 4;  // end[q] = start of list q; after the fill its end is end[q + 1]
     uint16_t* idx = reinterpret_cast<uint16_t*>(lds) + lay.off_idx / 2;
 
@@ -205,6 +336,15 @@ __device__ __forceinline__ void resident_closure(const SlotDesc& d, const int32_
         }
     }
     __syncthreads();
+    if (kQueue && G.queued)  // read after the first loop's barriers
+        for (int q = tid; q < n_lists; q += kThreads) {
+            const int c = static_cast<int>(end[q + 1] - end[q]);
+            uint64_t v = ~0ull;
+            for (int e = 0; e < min(c, 8); ++e)
+                v = (v & ~(0xFFull << (8 * e))) | static_cast<uint64_t>(idx[end[q] + e]) << (8 * e);
+            if (c > 8) v = (v & ~(0xFFull << 56)) | 0xFEull << 56;
+            near[q] = v;
+        }
     // the lists of the first two lf rules at this group's rows: start, length, first entry
     uint32_t l0[kPasses][2], ln[kPasses][2];
     int lk[kPasses][2];
@@ -272,13 +412,14 @@ __device__ __forceinline__ void resident_closure(const SlotDesc& d, const int32_
     int64_t products = 0, t = 0;
     int capped = 0;
     int prev = 0, cur = 1, next = 2;  // t % 3 of the last, this and the next loop
+    bool refeed = false;  // this loop scatters all bits of T, as the first one does
     while (true) {
         if (t >= d.max_iters) {
             capped = 1;
             break;
         }
         ++t;
-        const bool first = t == 1;
+        const bool first = t == 1 || refeed;
         const uint32_t any_prev = __builtin_amdgcn_readfirstlane(static_cast<int>(any_s[prev]));
         const uint32_t* cp = chg + prev * n_dyn * words;
         uint32_t* cc = chg + cur * n_dyn * words;
@@ -590,6 +731,49 @@ __device__ __forceinline__ void resident_closure(const SlotDesc& d, const int32_
         prev = cur;
         cur = next;
         next = p;
+        refeed = false;
+        if (kQueue && t == 1 && G.queued) {
+            // the bits of the rows the first loop changed, if they are few: old
+            // ones among them add nothing
+            __shared__ FactQueue queue;
+            uint32_t* marks = chg + prev * n_dyn * words;
+            if (tid == 0) queue.count = 0;
+            __syncthreads();
+            for (int h = 0; h < n_dyn && tid < n; ++h) {
+                if (!((marks[h * words + (tid >> 5)] >> (tid & 31)) & 1u)) continue;
+                const uint4 row = reinterpret_cast<const uint4*>(T + h * mat + tid * RW)[0];
+                const int c = __popc(row.x) + __popc(row.y) + __popc(row.z) + __popc(row.w);
+                int at = atomicAdd(&queue.count, c);
+                if (at + c > kFacts) continue;
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+                    for (uint32_t m = w == 0 ? row.x : w == 1 ? row.y : w == 2 ? row.z : row.w; m != 0; m &= m - 1)
+                        queue.q[at++] = fact(h, tid, 32 * w + __ffs(m) - 1);
+            }
+            __syncthreads();
+            if (queue.count <= kFacts) {
+                for (int x = tid; x < n_dyn * words; x += kThreads) marks[x] = 0;
+                if (tid == 0) any_s[prev] = 0;
+                __syncthreads();
+                if (tid < 64) {
+                    struct {
+                        const uint64_t* near;
+                        const uint32_t* end;
+                        const uint16_t* idx;
+                        uint64_t lf, rf, runs, lf_in;
+                        int n, mat, words, n_dyn, n_lf, n_rf;
+                    } u = {near, end, idx, lf, rf, runs, 0, n, mat, words, n_dyn, n_lf, n_rf};
+                    for (int r = 0; r < n_lf; ++r) u.lf_in |= static_cast<uint64_t>(uni(G.lf_in[r])) << (8 * r);
+                    follow_facts(u, queue, T, marks, &any_s[prev], t, d.max_iters);
+                }
+                __syncthreads();
+                t = queue.loops;
+                products += queue.products;
+                capped = queue.capped;
+                if (queue.count == 0) break;
+                refeed = true;  // bits lost to the queue have not been scattered
+            }
+        }
     }
 
     // ---- results
@@ -678,7 +862,9 @@ bool resident_plan(const cfpq_bin_rule* bin, int32_t n_bin, const cfpq_term_rule
         rules[3 * r + 1] = bin[r].left;
         rules[3 * r + 2] = bin[r].right;
     }
-    if (!resident_grammar(rules, n_bin, n_nt, &plan->g)) return false;
+    // sparse graphs of one lane a row: see follow_facts
+    const bool one = resident_lanes(n) == 1, sparse = n_edges < 2 * static_cast<int64_t>(n);
+    if (!resident_grammar(rules, n_bin, n_nt, one && sparse, &plan->g)) return false;
     int32_t per_edge = 1;  // the most terminal rules of one label
     bool fits = n_term <= kRsMaxTerm;
     for (int32_t r = 0; r < n_term; ++r) {
@@ -695,10 +881,10 @@ bool resident_plan(const cfpq_bin_rule* bin, int32_t n_bin, const cfpq_term_rule
     const int64_t entries = 2 * n_edges * per_edge;
     // one lane a row: with two edges a node and more.  On sparser graphs a loop
     // sets few bits, and the kernel without the turned code takes a fifth less a
-    // loop (two cycles of 64 and 63 nodes: 5.6 against 6.9 ms; same-generation
-    // on G(100, 300), where the turned code runs: 265 against 161 us)
-    const bool one = resident_lanes(n) == 1;
-    const bool want = (plan->g.n_dd > 0 || plan->g.n_rf > 0) && (!one || n_edges >= 2 * static_cast<int64_t>(n));
+    // loop over rows (two cycles of 64 and 63 nodes, without follow_facts: 5.6
+    // against 6.9 ms; same-generation on G(100, 300), where the turned code runs:
+    // 265 against 161 us)
+    const bool want = (plan->g.n_dd > 0 || plan->g.n_rf > 0) && !(one && sparse);
     ResidentLds l = resident_lds(n, plan->g, entries, want);
     plan->turned = want && l.total <= kResidentMaxLds ? 1 : 0;
     if (!plan->turned) l = resident_lds(n, plan->g, entries, false);

@@ -38,14 +38,16 @@ struct ResidentGrammar {
     // by nonterminal, or -1: the growing ones' numbers, the fixed ones' lists (in: of rf operands)
     int8_t dyn[CFPQ_MAX_NONTERMINALS], list[CFPQ_MAX_NONTERMINALS], in[CFPQ_MAX_NONTERMINALS];
     int8_t rf_in[kRsMaxRules];  // by rf rule: its operand's incoming list
+    int8_t lf_in[kRsMaxRules];  // and by lf rule, with `queued`
+    int8_t queued;              // the kernel may follow single facts (all lf_in exist)
     int8_t dyn_nt[kRsMaxDyn], tt[kRsMaxDyn];                          // by growing nonterminal
 };
 
 // Sorts n_rules (lhs, left, right) triples; false when the grammar is beyond
 // the kernel: its tables, a scatter head that is itself scattered from, or dd
 // rules with different left operands (or a head that is scattered from and is
-// not that operand).
-inline bool resident_grammar(const int32_t* rules, int32_t n_rules, int32_t n_nt, ResidentGrammar* g) {
+// not that operand).  queue: with the lists that following single facts takes.
+inline bool resident_grammar(const int32_t* rules, int32_t n_rules, int32_t n_nt, bool queue, ResidentGrammar* g) {
     std::memset(g, 0, sizeof(*g));
     g->n_term = -1;
     g->n_dyn = g->n_list = g->n_lf = g->n_rf = g->n_ll = g->n_dd = g->n_tt = 0;
@@ -102,6 +104,14 @@ inline bool resident_grammar(const int32_t* rules, int32_t n_rules, int32_t n_nt
         g->runs += uint64_t{1} << (8 * rs_right(g->lf, r));
         g->pull_mask |= 1 << rs_head(g->lf, r);
     }
+    g->queued = queue && g->n_dd == 0;
+    for (int r = 0, lf = 0; r < n_rules && g->queued; ++r) {
+        const int b = rules[3 * r + 1];
+        if (g->dyn[b] >= 0 || g->dyn[rules[3 * r + 2]] < 0) continue;
+        if (g->in[b] < 0 && g->n_list < kRsMaxLists) g->in[b] = static_cast<int8_t>(g->n_list++);
+        g->lf_in[lf++] = g->in[b];
+        if (g->in[b] < 0) g->queued = 0;
+    }
     return true;
 }
 
@@ -111,10 +121,11 @@ __host__ __device__ inline int resident_lanes(int32_t n) { return n <= 128 ? 1 :
 // LDS of a slot in bytes (offsets from the start of the dynamic LDS): T of
 // the growing nonterminals, the kept gained bits, transposed operands (with
 // `turned`: where there is room), changed-row bitmaps of three
-// loops, list ends, list entries.
+// loops, list ends, with `queued` the lists' first eight entries in 8 bytes, list
+// entries.
 struct ResidentLds {
     int32_t rows, mat;  // rows of a matrix (a multiple of 128 where it is multiplied by tiles), bytes
-    int32_t off_d, off_tt, off_chg, off_end, off_idx, total;
+    int32_t off_d, off_tt, off_chg, off_end, off_near, off_idx, total;
 };
 __host__ __device__ inline ResidentLds resident_lds(int32_t n, const ResidentGrammar& g, int64_t entries,
                                                     bool turned) {
@@ -128,7 +139,8 @@ __host__ __device__ inline ResidentLds resident_lds(int32_t n, const ResidentGra
     l.off_chg = l.off_tt + (turned ? (g.n_tt > 0 ? g.n_tt : 1) * l.mat : 0);
     // every part starts on 16 bytes: the kernel clears up to off_idx in such pieces
     l.off_end = l.off_chg + (3 * g.n_dyn * (l.rows / 32) * 4 + 15) / 16 * 16;
-    l.off_idx = l.off_end + ((g.n_list * n + 1) * 4 + 15) / 16 * 16;
+    l.off_near = l.off_end + ((g.n_list * n + 1) * 4 + 15) / 16 * 16;
+    l.off_idx = l.off_near + (g.queued ? (g.n_list * n * 8 + 15) / 16 * 16 : 0);
     const int64_t t = l.off_idx + (entries * 2 + 15) / 16 * 16;
     l.total = t > (1 << 30) ? 1 << 30 : static_cast<int32_t>(t);
     return l;

@@ -109,3 +109,28 @@ def test_resident_batch_and_limits(cfpq):
     with pytest.raises(cfpq.CfpqError) as ei:
         cfpq.closure(inst.n, torch.from_numpy(bad).cuda(), inst.grammar)
     assert ei.value.status == -1
+
+
+@pytest.mark.parametrize("g", GRAMMARS, ids=lambda g: g.name)
+def test_resident_follows_facts(cfpq, g):
+    """Sparse graphs of one lane a row: chains and cycles (one or two bits a
+    loop), hubs on both ends (lists past eight entries, many bits from one),
+    and random trees, whose loops outgrow the facts one wavefront holds."""
+    rng = np.random.default_rng(3)
+    cases = []
+    for n in (2, 33, 64, 128):
+        chain = [(i, 0 if i < n // 2 else 1, i + 1) for i in range(n - 1)]
+        cases.append((n, chain))
+        cases.append((n, [(i, int(rng.integers(2)), int(rng.integers(n))) for i in range(n)]))
+        cases.append((n, [(i, int(rng.integers(2)), (i + 1) % n) for i in range(n)]
+                      + [(int(rng.integers(n)), int(rng.integers(2)), int(rng.integers(n))) for _ in range(n // 3)]))
+    n = 100
+    cases.append((n, [(0, 0, j) for j in range(1, 40)] + [(j, 1, 99) for j in range(1, 40)]
+                  + [(99, 1, 50), (50, 1, 51), (51, 1, 52), (60, 0, 0), (61, 0, 60)]))
+    for n, e in cases:
+        e = np.asarray(e, np.int32)
+        print("[gpu-case] resident facts", g.name, n, len(e), file=sys.stderr, flush=True)
+        want = worklist.closure(n, e, g)
+        res = cfpq.closure(n, e, g)
+        assert np.array_equal(cfpq.result_bits(res), want), (n, len(e))
+        assert res.stats["converged"] == 1
