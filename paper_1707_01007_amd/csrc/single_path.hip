@@ -20,10 +20,11 @@
 //     step only: a new cell of B written by this loop is never read).  A rule
 //     whose B is a fixed sparse edge matrix walks the set bits of B's rows
 //     (minplus_rows_kernel); one whose C is, C's columns through a column
-//     index built once (minplus_cols_kernel); the others take the row walk
-//     or minplus_kernel over the 64 x 64 output tiles that hold new cells of
-//     A (split along k when they are few) -- while the lengths are at most 16
-//     minplus_pow_kernel on the matrix cores -- whichever a cost model from the
+//     index built once (minplus_cols_kernel); the others take the row walk,
+//     minplus_kernel over the 64 x 64 output tiles that hold new cells of
+//     A (split along k when they are few), while the lengths are at most 16
+//     minplus_pow_kernel on the matrix cores, or while they are at most 127
+//     minplus_cells_kernel by single cells, whichever a cost model from the
 //     counts prefers;
 //  4. X = Y.
 // Lengths are uint32 in cells of a |N| x npad x npad array (0 = absent); sums
@@ -301,6 +302,9 @@ __global__ __launch_bounds__(256) void minplus_kernel(const uint64_t* __restrict
 // v_perm_b32 per two cells on the way to LDS.
 constexpr int32_t kPowMaxLength = 16;
 constexpr int kPowStep = 8, kPowBias = 67;
+constexpr uint32_t kCellsMaxLength = 127;  // of minplus_cells_kernel, below
+constexpr int kCellsWords = 16;
+typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 
 // The high byte of bf16 2^(kPowBias - kPowStep * l), 0 unless 1 <= l <= 16.
 __device__ __forceinline__ uint32_t power_byte(uint32_t l) {
@@ -309,26 +313,45 @@ __device__ __forceinline__ uint32_t power_byte(uint32_t l) {
 
 // Operand bytes of one matrix of lengths, cells without the previous step's
 // bit X left out: rows[i][k] as it lies, cols[j][k] transposed (either may be
-// null).  One workgroup per 64 x 64 tile; thread t holds 16 cells of row t / 4.
+// null).  kPowers: powers of two as above; else the lengths themselves, 255 for
+// an absent cell, and only rows and columns in whose tiles a new cell lies
+// (tflag).  One workgroup per 64 x 64 tile; thread t holds 16 cells of row t / 4.
+template <bool kPowers>
 __global__ __launch_bounds__(256) void length_bytes_kernel(const uint32_t* __restrict__ L,
                                                            const uint64_t* __restrict__ X, uint8_t* __restrict__ rows,
-                                                           uint8_t* __restrict__ cols, int64_t W, int64_t npad) {
+                                                           uint8_t* __restrict__ cols, int64_t W, int64_t npad,
+                                                           const int32_t* __restrict__ tflag) {
     __shared__ uint32_t tile[64][17];  // 64 bytes a row, padded
     const int t = threadIdx.x;
     const int64_t ti = blockIdx.x / W, tj = blockIdx.x % W;
+    if (!kPowers) {  // rows and columns in which no new cell lies stay out
+        bool in_row = false, in_col = false;
+        for (int64_t x = t; x < W; x += 256) {
+            in_row = in_row || tflag[ti * W + x] != 0;
+            in_col = in_col || tflag[x * W + tj] != 0;
+        }
+        if (!__syncthreads_or(rows != nullptr && in_row)) rows = nullptr;
+        if (!__syncthreads_or(cols != nullptr && in_col)) cols = nullptr;
+        if (rows == nullptr && cols == nullptr) return;
+    }
     const int r = t >> 2, c = (t & 3) * 16;
     const int64_t i = ti * 64 + r;
     const uint32_t bits = static_cast<uint32_t>(X[i * W + tj] >> c) & 0xFFFFu;
     const uint4* src = reinterpret_cast<const uint4*>(L + i * npad + tj * 64 + c);
-    uint32_t out[4] = {0, 0, 0, 0};
+    constexpr uint32_t kAbsent = kPowers ? 0u : 0xFFu;
+    uint32_t out[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[q] = kAbsent * 0x01010101u;
     if (bits != 0) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const uint4 v = src[q];
             const uint32_t l[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                out[q] |= ((bits >> (4 * q + u)) & 1u ? power_byte(l[u]) : 0u) << (8 * u);
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t b = kPowers ? power_byte(l[u]) : l[u] & 0xFFu;
+                out[q] ^= ((bits >> (4 * q + u)) & 1u ? b ^ kAbsent : 0u) << (8 * u);
+            }
         }
     }
     if (rows != nullptr)
@@ -474,6 +497,85 @@ __global__ __launch_bounds__(256) void minplus_pow_kernel(const uint8_t* __restr
                 if (s < *cell) *cell = s;
             }
         }
+}
+
+// Row by column min-plus of single new cells, operands as bytes holding the
+// lengths themselves (length_bytes_kernel<false>).  A wavefront holds 4096 k of row i in registers, each byte in
+// 16 bits of its own, and for every new cell (i, j) of its word of D reads the
+// same k of column j; absent cells are 255, so with lengths of at most
+// kCellsMaxLength a sum with one is at least 256 and none is masked.  A workgroup
+// takes kCellsWords words of D, apart by the number of workgroups (new cells
+// crowd in few rows), and its four wavefronts share the cells of each word.
+//
+// For steps of few new cells in many tiles, which the tile kernels take whole.
+// What bounds it: the columns from L2 (10 M cells at n = 4096 in 2.9 ms, 14
+// TB/s) while cells are many, the latency of a row and a column a word when few.
+// ER Dyck n = 4096, the step after a length passed 16 (35000 to 70000 new cells
+// in 700 to 1400 of 4096 tiles): 1206 -> 120 us; the closure 3.85 -> 3.43 ms
+// (degree 3: 8.4 -> 4.4).  Tried: the common k from the bit rows, 16-bit columns
+// behind them (287 us), taken word by word (702); eight wavefronts a workgroup
+// (141) and the next column loaded ahead (146).
+__global__ __launch_bounds__(256) void minplus_cells_kernel(const uint64_t* __restrict__ D,
+                                                            const uint8_t* __restrict__ B,
+                                                            const uint8_t* __restrict__ CT, uint32_t* LA, int64_t W,
+                                                            int64_t npad, int64_t words) {
+    constexpr uint32_t kEven = 0x00FF00FFu, kNone = 0xFFFFFFFFu;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t step = gridDim.x;
+    for (int64_t w0 = blockIdx.x; w0 < words; w0 += kCellsWords * step) {
+        const int64_t at = w0 + lane * step;
+        const uint64_t dw = lane < kCellsWords && at < words ? D[at] : 0;
+        for (uint64_t nz = __ballot(dw != 0); nz; nz &= nz - 1) {
+            const int src = __ffsll(static_cast<unsigned long long>(nz)) - 1;
+            const uint64_t all = rowor::readlane64(dw, src);
+            if (__popcll(all) <= ((wave - src) & 3)) continue;  // fewer cells than wavefronts
+            const int64_t w = w0 + src * step;
+            const int64_t i = w / W, j0 = 64 * (w % W);
+            for (int64_t k0 = 16 * lane; k0 - 16 * lane < npad; k0 += 4096) {
+                uint32_t even[16], odd[16];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int64_t k = k0 + 1024 * q;
+                    uint4 v = make_uint4(kNone, kNone, kNone, kNone);
+                    if (k < npad) v = *reinterpret_cast<const uint4*>(B + i * npad + k);
+                    const uint32_t x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        even[4 * q + u] = x[u] & kEven;
+                        odd[4 * q + u] = (x[u] >> 8) & kEven;
+                    }
+                }
+                int turn = src;
+                for (uint64_t cells = all; cells; cells &= cells - 1, ++turn) {
+                    if ((turn & 3) != wave) continue;
+                    const int64_t j = j0 + __ffsll(static_cast<unsigned long long>(cells)) - 1;
+                    uint4 c[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int64_t k = k0 + 1024 * q;
+                        c[q] = make_uint4(kNone, kNone, kNone, kNone);
+                        if (k < npad) c[q] = *reinterpret_cast<const uint4*>(CT + j * npad + k);
+                    }
+                    ushort2v best = {0xFFFF, 0xFFFF};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const uint32_t x[4] = {c[q].x, c[q].y, c[q].z, c[q].w};
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const uint32_t e = even[4 * q + u] + (x[u] & kEven);
+                            const uint32_t o = odd[4 * q + u] + ((x[u] >> 8) & kEven);
+                            best = __builtin_elementwise_min(best, __builtin_bit_cast(ushort2v, e));
+                            best = __builtin_elementwise_min(best, __builtin_bit_cast(ushort2v, o));
+                        }
+                    }
+                    uint32_t s = min<uint32_t>(best.x, best.y);
+                    for (int o = 32; o > 0; o >>= 1)
+                        s = min(s, static_cast<uint32_t>(__shfl_xor(static_cast<int>(s), o, 64)));
+                    if (lane == 0 && s <= 2 * kCellsMaxLength) atomicMin(LA + i * npad + j, s);
+                }
+            }
+        }
+    }
 }
 
 // Row walk min-plus: L_A(i, j) = min over the set bits k of X_B's row i of
@@ -1014,13 +1116,33 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
         // X_B in it) pair, against 20 T (i, j, k) terms/s over the active tiles
         // on the VALU or, while no operand length exceeds 16 (the longest so
         // far was read back with the flags), the matrix cores' time.
-        const bool powers = flags[n_nt + 1] <= kPowMaxLength;
+        const bool powers = p.any_tiles && flags[n_nt + 1] <= kPowMaxLength;
         // 128 x 128 tiles, 2 T terms/s a workgroup and at best 500 over the
         // chip, after a pass over the lengths (4 bytes a cell at 3 TB/s)
         auto pow_ms = [&](int32_t active) {
             const double wgs = std::min<double>(active, static_cast<double>(L.W) * L.W / 4);
             const double cells = static_cast<double>(L.npad) * L.npad;
             return std::max(kchunks * 524288.0 / 2e9, wgs * kchunks * 524288.0 / 5e11) + 0.02 + cells * 4 / 3e9;
+        };
+        // the cell walk: the operand bytes, the words of D, and 0.55 ns a cell
+        // at n = 4096 (0.3 to 0.5 where new cells fill words; n = 8192: 0.76)
+        const bool cells_fit = p.any_tiles && static_cast<uint32_t>(flags[n_nt + 1]) <= kCellsMaxLength;
+        auto cells_walk_ms = [&](unsigned long long cells) {
+            return 0.03 + static_cast<double>(L.npad) * L.npad * 3e-9 +
+                   static_cast<double>(cells) * (1.4e-7 + 1e-10 * L.npad);
+        };
+        // a rule's operand bytes: the left one's rows, the right one's columns
+        auto bytes = [&](const cfpq_bin_rule& br, bool powers_of_two) {
+            const auto kernel = powers_of_two ? length_bytes_kernel<true> : length_bytes_kernel<false>;
+            const dim3 grid(static_cast<unsigned>(L.W * L.W));
+            const int32_t* f = d_tflag + br.lhs * L.W * L.W;
+            const bool same = br.left == br.right;
+            kernel<<<grid, dim3(256), 0, s>>>(d_lengths + br.left * lmat, X + br.left * mw, d_bytes,
+                                              same ? d_bytes + lmat : nullptr, L.W, L.npad, f);
+            if (!same)
+                kernel<<<grid, dim3(256), 0, s>>>(d_lengths + br.right * lmat, X + br.right * mw, nullptr,
+                                                  d_bytes + lmat, L.W, L.npad, f);
+            return hipGetLastError();
         };
         const int64_t gather_items = static_cast<int64_t>(L.n) * ((L.W + kGatherWords - 1) / kGatherWords);
         const unsigned gather_grid = static_cast<unsigned>(std::min<int64_t>((gather_items + 3) / 4, 2048));
@@ -1036,7 +1158,19 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
                 const double rows_ms = active_rows * static_cast<double>(xcount[br.left]) / n * 1e-5;
                 const double tile_ms = static_cast<double>(tiles[br.lhs]) * kchunks * 131072.0 / 2e10;
                 const bool pow = powers && pow_ms(tiles[br.lhs]) < tile_ms;
-                rows = rows_ms < (pow ? pow_ms(tiles[br.lhs]) : tile_ms);
+                const double best_ms = pow ? pow_ms(tiles[br.lhs]) : tile_ms;
+                // (rows_ms is high by up to 6 where rows are short: 27 us
+                // against 164 at n = 4096 and 16 k bits)
+                if (cells_fit && cells_walk_ms(dcount[br.lhs]) < std::min(0.3 * rows_ms, best_ms)) {
+                    CFPQ_HIP(bytes(br, false));
+                    const int64_t wgs = (p.L.mat_words + kCellsWords - 1) / kCellsWords;
+                    minplus_cells_kernel<<<dim3(static_cast<unsigned>(std::min<int64_t>(wgs, 65536))), dim3(256), 0,
+                                           s>>>(D + br.lhs * mw, d_bytes, d_bytes + lmat, d_lengths + br.lhs * lmat,
+                                                L.W, L.npad, p.L.mat_words);
+                    CFPQ_HIP(hipGetLastError());
+                    continue;
+                }
+                rows = rows_ms < best_ms;
                 on_tiles[r] = rows ? 0 : pow ? 2 : 1;
             }
             if (rows) {
@@ -1072,18 +1206,10 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
             if (!on_tiles[r]) continue;
             const int64_t all_tiles = L.W * L.W;
             if (on_tiles[r] == 2) {
-                uint8_t* rows_b = d_bytes;
-                uint8_t* cols_b = d_bytes + lmat;
-                const bool same = br.left == br.right;
-                const dim3 bgrid(static_cast<unsigned>(all_tiles));
-                length_bytes_kernel<<<bgrid, dim3(256), 0, s>>>(d_lengths + br.left * lmat, X + br.left * mw, rows_b,
-                                                               same ? cols_b : nullptr, L.W, L.npad);
-                if (!same)
-                    length_bytes_kernel<<<bgrid, dim3(256), 0, s>>>(d_lengths + br.right * lmat, X + br.right * mw,
-                                                                   nullptr, cols_b, L.W, L.npad);
+                CFPQ_HIP(bytes(br, true));
                 const int64_t side = L.npad / kPowTile;
                 minplus_pow_kernel<<<dim3(static_cast<unsigned>(side * side)), dim3(256), 0, s>>>(
-                    rows_b, cols_b, D + br.lhs * mw, d_lengths + br.lhs * lmat, L.W, L.npad,
+                    d_bytes, d_bytes + lmat, D + br.lhs * mw, d_lengths + br.lhs * lmat, L.W, L.npad,
                     static_cast<int32_t>((L.n + kPowChunk - 1) / kPowChunk), d_tflag + br.lhs * all_tiles, d_cells);
                 CFPQ_HIP(hipGetLastError());
                 continue;
