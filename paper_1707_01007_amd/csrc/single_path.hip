@@ -35,6 +35,7 @@
 #include <cstdint>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <unordered_map>
 #include <vector>
 
@@ -288,12 +289,12 @@ __global__ __launch_bounds__(256) void minplus_kernel(const uint64_t* __restrict
 // ---- min-plus on the matrix cores, while every operand length is at most 16
 //
 // A length l becomes the power of two 2^(67 - 8 l), an absent cell 0.  A
-// product of two is 2^(134 - 8 s), s the sum of the lengths, so over 64 k the
-// sum of the products lies in [2^(134 - 8 s), 64 * 2^(134 - 8 s)], s being the
-// smallest sum: at most 6 of the 8 exponent steps to the next smaller sum are
+// product of two is 2^(134 - 8 s), s the sum of the lengths, so over 128 k the
+// sum of the products lies in [2^(134 - 8 s), 128 * 2^(134 - 8 s)], s being the
+// smallest sum: at most 7 of the 8 exponent steps to the next smaller sum are
 // used up, and the exponent alone gives s.  Powers of two, their products
 // (exponents -122 .. 118 for s = 32 .. 2) and every rounding of sums of positive
-// terms keep those bounds, so the lengths are exact.  Chunks of 64 k are
+// terms keep those bounds, so the lengths are exact.  Every 128 k are
 // combined by a maximum: the larger sum has the smaller s.
 //
 // In bf16 such a power has no mantissa and, with an odd bias, an even biased
@@ -375,12 +376,13 @@ __global__ __launch_bounds__(256) void length_bytes_kernel(const uint32_t* __res
 // L_A = min(L_A, min-plus product) on the new cells, 128 x 128 cells a
 // workgroup: four wavefronts of 64 x 64 (2 x 2 blocks of 32 x 32), chunks of
 // 64 k staged in two LDS buffers, the next chunk's bytes loaded while one is
-// multiplied.  Workgroups without a new cell return at once.
+// multiplied; two chunks are summed before the maximum.  Workgroups without a new cell return at once.
 //
 // What bounds it: LDS reads (16 KiB a wavefront and chunk for 16 MFMAs, even
-// with the matrix pipe) and the operand bytes from L2.  A full product at
-// n = 4096 (6.9e10 terms) takes 260 us = 264 T terms/s; the VALU kernel took
-// 2750 us for the same step (25 T terms/s).  The closure of ER Dyck n = 4096
+// with the matrix pipe, and as much again in stores for two).  A full product at
+// n = 4096 (6.9e10 terms) takes 224 us = 307 T terms/s (258 with the maximum and
+// cleared accumulators every 64 k); the VALU kernel took 2750 us for the same
+// step (25 T terms/s).  The closure of ER Dyck n = 4096
 // went from 9.7 to 4.5 ms with it and the column kernel below.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -437,21 +439,13 @@ __global__ __launch_bounds__(256) void minplus_pow_kernel(const uint8_t* __restr
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int e = 0; e < 16; ++e) best[a][b][e] = 0.0f;
-    load(0);
-    store(As[0][sr], ab);
-    store(Bs[0][sr], cb);
-    __syncthreads();
-    for (int32_t c = 0; c < chunks; ++c) {
-        const int cur = c & 1;
+    f32x16 acc[2][2];
+    const f32x16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    // chunk c of an even (first) or odd index: LDS buffer 0 or 1
+    auto multiply = [&](int32_t c, auto first) {
+        constexpr int cur = decltype(first)::value ? 0 : 1;
         const bool more = c + 1 < chunks;
         if (more) load(c + 1);
-        f32x16 acc[2][2];
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.0f;
 #pragma unroll
         for (int s = 0; s < kPowChunk / 16; ++s) {
             bf16x8 af[2], bf[2];
@@ -464,19 +458,28 @@ __global__ __launch_bounds__(256) void minplus_pow_kernel(const uint8_t* __restr
             for (int a = 0; a < 2; ++a)
 #pragma unroll
                 for (int b = 0; b < 2; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[a], bf[b], acc[a][b], 0, 0, 0);
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        af[a], bf[b], s == 0 && cur == 0 ? zero : acc[a][b], 0, 0, 0);
         }
+        if (more) {
+            store(As[cur ^ 1][sr], ab);  // last read a barrier ago
+            store(Bs[cur ^ 1][sr], cb);
+        }
+        __syncthreads();
+    };
+    load(0);
+    store(As[0][sr], ab);
+    store(Bs[0][sr], cb);
+    __syncthreads();
+    for (int32_t c = 0; c < chunks; c += 2) {
+        multiply(c, std::true_type());
+        if (c + 1 < chunks) multiply(c + 1, std::false_type());
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
             for (int b = 0; b < 2; ++b)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) best[a][b][e] = fmaxf(best[a][b][e], acc[a][b][e]);
-        if (more) {
-            store(As[cur ^ 1][sr], ab);  // last read a barrier ago
-            store(Bs[cur ^ 1][sr], cb);
-        }
-        __syncthreads();
     }
     if (t == 0) atomicAdd(cells, static_cast<unsigned long long>(chunks) * kPowChunk * kPowTile * kPowTile);
     // accumulator e of lane (g, r32): row 8 (e / 4) + 4 g + e % 4, column r32 of its block
