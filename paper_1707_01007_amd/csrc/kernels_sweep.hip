@@ -610,8 +610,8 @@ hipError_t launch_sweep_init(const SweepGrammar& g, const SweepBuffers& b, const
     const size_t blocks = std::min<size_t>((tq + cq + 1023) / 1024, 4096);
     sweep_clear_kernel<<<dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s>>>(
         reinterpret_cast<uint4*>(b.T), tq, reinterpret_cast<uint4*>(b.chg), cq);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || m == 0) return e;
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
     InitArgs a;
     std::copy(g.term, g.term + kSwMaxTerm, a.term);
     a.n_term = g.n_term;
@@ -620,12 +620,13 @@ hipError_t launch_sweep_init(const SweepGrammar& g, const SweepBuffers& b, const
     a.W = L.W;
     a.mat_words = L.mat_words;
     const dim3 eg(static_cast<unsigned>((m + 255) / 256));
-    sweep_scatter_kernel<<<eg, dim3(256), 0, s>>>(edges, m, a, b.T, b.list, b.ctl);
+    if (m > 0) sweep_scatter_kernel<<<eg, dim3(256), 0, s>>>(edges, m, a, b.T, b.list, b.ctl);
     if (g.n_list > 0) {
+        // also without edges: the sweeps read every node's 16-byte form, written here
         const int32_t lists = g.n_list * L.n;
         sweep_place_kernel<<<dim3(static_cast<unsigned>((lists + 255) / 256)), dim3(256), 0, s>>>(b.list, b.cur, b.near,
                                                                                                  lists, b.ctl);
-        sweep_fill_kernel<<<eg, dim3(256), 0, s>>>(edges, m, a, b.list, b.cur, b.near, b.idx);
+        if (m > 0) sweep_fill_kernel<<<eg, dim3(256), 0, s>>>(edges, m, a, b.list, b.cur, b.near, b.idx);
     }
     return hipGetLastError();
 }
