@@ -85,6 +85,12 @@ struct FactQueue {
     int64_t loops, products;
 };
 
+// A launch with the most dynamic LDS has room for what the kernel declares
+// itself: the grammar, resident_solo's state, some 100 bytes of counters, and
+// class 0's queue.
+static_assert(resident_max_lds(0) + sizeof(ResidentGrammar) + sizeof(SlotState) + 256 + sizeof(FactQueue) <= kLdsBytes &&
+              resident_max_lds(1) + sizeof(ResidentGrammar) + sizeof(SlotState) + 256 <= kLdsBytes);
+
 // One wavefront; the facts are in q.q[0, q.count).  Ends with q.count = 0 (the
 // fixpoint, or the cap) or with every pending fact's row marked in chg and any.
 template <typename Rules>
@@ -885,11 +891,15 @@ bool resident_plan(const cfpq_bin_rule* bin, int32_t n_bin, const cfpq_term_rule
     // against 6.9 ms; same-generation on G(100, 300), where the turned code runs:
     // 265 against 161 us)
     const bool want = (plan->g.n_dd > 0 || plan->g.n_rf > 0) && !(one && sparse);
+    const int32_t walked = resident_lanes(n) / 2 + (plan->g.n_dd > 0 ? 3 : 0);  // the class without turned operands
     ResidentLds l = resident_lds(n, plan->g, entries, want);
-    plan->turned = want && l.total <= kResidentMaxLds ? 1 : 0;
-    if (!plan->turned) l = resident_lds(n, plan->g, entries, false);
-    if (l.total > kResidentMaxLds) return false;
-    plan->cls = one && plan->turned ? (plan->g.n_dd > 0 ? 7 : 6) : resident_lanes(n) / 2 + (plan->g.n_dd > 0 ? 3 : 0);
+    plan->cls = one && want ? (plan->g.n_dd > 0 ? 7 : 6) : walked;
+    plan->turned = want && l.total <= resident_max_lds(plan->cls) ? 1 : 0;
+    if (!plan->turned) {
+        plan->cls = walked;
+        l = resident_lds(n, plan->g, entries, false);
+    }
+    if (l.total > resident_max_lds(plan->cls)) return false;
     plan->lds = l.total;
     return true;
 }

@@ -145,11 +145,15 @@ __host__ __device__ inline ResidentLds resident_lds(int32_t n, const ResidentGra
     l.total = t > (1 << 30) ? 1 << 30 : static_cast<int32_t>(t);
     return l;
 }
-constexpr int32_t kResidentMaxLds = 158 * 1024;  // of 160 KiB; the rest is the kernel's own
-
 // Launch classes: lanes a row (1, 2, 4), without and with dd rules; then one
 // lane a row with transposed operands, without and with dd rules.
 constexpr int32_t kResidentClasses = 8;
+
+// Most dynamic LDS of a launch.  The rest of the 160 KiB is the kernel's own: at
+// most 480 bytes, and in class 0, whose kernel may follow single facts, their
+// queue (2544 bytes in all).
+constexpr int32_t kLdsBytes = 160 * 1024;
+__host__ __device__ constexpr int32_t resident_max_lds(int32_t cls) { return cls == 0 ? 156 * 1024 : 158 * 1024; }
 
 // Whether the resident sweep takes a graph of n nodes and this grammar, and for
 // its launch: the grammar as the kernel reads it (kept where the slot's rule
