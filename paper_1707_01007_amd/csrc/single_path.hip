@@ -737,6 +737,7 @@ __global__ __launch_bounds__(256) void minplus_cols_kernel(const uint64_t* __res
 // the row).
 constexpr int32_t kColsRowMax = 16384;
 constexpr unsigned long long kColsRowCells = 128;
+constexpr size_t kColsRowStatic = 256;  // LDS of the workgroup-wide OR
 
 __global__ __launch_bounds__(256) void minplus_cols_row_kernel(const uint64_t* __restrict__ D,
                                                                const uint64_t* __restrict__ XB,
@@ -1183,8 +1184,12 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
             } else if (p.csc_slot[br.right] >= 0) {
                 const char* base = ws + p.off_csc + p.csc_bytes * p.csc_slot[br.right];
                 if (L.n <= kColsRowMax && dcount[br.lhs] >= kColsRowCells * L.n) {
-                    minplus_cols_row_kernel<<<dim3(static_cast<unsigned>(L.n)), dim3(256),
-                                              static_cast<size_t>(L.n) * 4, s>>>(
+                    const size_t lds = static_cast<size_t>(L.n) * 4;
+                    if (lds + kColsRowStatic > 64 * 1024)  // more LDS than a launch gets unasked
+                        CFPQ_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&minplus_cols_row_kernel),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     static_cast<int>(lds)));
+                    minplus_cols_row_kernel<<<dim3(static_cast<unsigned>(L.n)), dim3(256), lds, s>>>(
                         D + br.lhs * mw, X + br.left * mw, reinterpret_cast<const int32_t*>(base),
                         reinterpret_cast<const int32_t*>(base + p.off_csc_idx), d_lengths + br.left * lmat,
                         d_lengths + br.lhs * lmat, L.W, L.npad, L.n);
