@@ -214,7 +214,9 @@ CFPQ_API cfpq_status cfpq_workspace_bytes(const cfpq_graph* graph, const cfpq_gr
  *                    and the call returns CFPQ_EINVAL)
  *   opt              NULL = cfpq_default_options
  *   stream           hipStream_t or NULL
- *   d_workspace      device scratch of at least cfpq_workspace_bytes bytes
+ *   d_workspace      device scratch of at least cfpq_workspace_bytes bytes (less
+ *                    is accepted where it holds the product loops' matrices but
+ *                    not the row sweeps': the loops run then)
  *   d_result         device buffer of cfpq_result_bytes bytes; overwritten with
  *                    R in the bit layout
  *   stats            optional (NULL allowed)
@@ -562,7 +564,8 @@ CFPQ_API cfpq_status cfpq_batch_closure(int32_t n_instances, const cfpq_instance
  * Queries with a padded side of at least 4096 go instead, in arrival order,
  * to `hybrid_lanes` lane threads, each running one query at a time with the
  * hybrid closure of cfpq_closure on its own stream (workspace from the same
- * arena, admitted when it fits, result written straight to d_result), so
+ * arena, admitted when it fits -- for the row sweeps, or where only that
+ * fits for the product loops -- result written straight to d_result), so
  * their work overlaps the engine's on the device.
  * ------------------------------------------------------------------------ */
 

@@ -183,9 +183,10 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
 size_t batch_workspace_one(const cfpq_graph& graph, const cfpq_grammar* grammar, const cfpq_options& o);
 
 // cfpq_closure and its workspace for a server lane (closure.hip): as with
-// path AUTO, whatever dense kernel o.path names; CFPQ_PATH is not read.  The
+// path AUTO, whatever dense kernel o.path names; CFPQ_PATH is not read.  With
+// a workspace for the product loops only (sweeps false) it runs those.  The
 // graph and grammar must be valid.
-size_t lane_workspace(const cfpq_graph* graph, const cfpq_grammar* grammar, const cfpq_options& o);
+size_t lane_workspace(const cfpq_graph* graph, const cfpq_grammar* grammar, const cfpq_options& o, bool sweeps);
 cfpq_status lane_closure(const cfpq_graph* graph, const cfpq_grammar* grammar, const cfpq_options& o, void* stream,
                          void* d_workspace, size_t workspace_bytes, uint64_t* d_result, cfpq_stats* stats);
 

@@ -338,8 +338,8 @@ static size_t loop_workspace(const cfpq_graph* graph, const cfpq_grammar* gramma
     return sweeps && sweep_route(graph, grammar, o) ? std::max(loops, sweep_workspace(graph, grammar)) : loops;
 }
 
-size_t lane_workspace(const cfpq_graph* graph, const cfpq_grammar* grammar, const cfpq_options& o) {
-    return loop_workspace(graph, grammar, o, true);
+size_t lane_workspace(const cfpq_graph* graph, const cfpq_grammar* grammar, const cfpq_options& o, bool sweeps) {
+    return loop_workspace(graph, grammar, o, sweeps);
 }
 
 cfpq_status lane_closure(const cfpq_graph* graph, const cfpq_grammar* grammar, const cfpq_options& o, void* stream,
@@ -486,7 +486,10 @@ cfpq_status closure_impl(const cfpq_graph* graph, const cfpq_grammar* grammar, c
         }
         return rs;
     }
-    if (sweeps && sweep_route(graph, grammar, o) && graph->n_edges <= sweep_max_edges(layout_for(graph->n_nodes)))
+    // a workspace that holds the product loops' matrices but not the sweeps' (a
+    // server's arena; one sized for other options) gets those loops
+    if (sweeps && sweep_route(graph, grammar, o) && graph->n_edges <= sweep_max_edges(layout_for(graph->n_nodes)) &&
+        workspace_bytes >= loop_workspace(graph, grammar, o, true))
         return closure_sweep(graph, grammar, o, stream, d_workspace, workspace_bytes, d_result, stats);
     const Plan p = make_plan(graph, grammar, o);
     if (p.total > 0 && !d_workspace) return fail(CFPQ_EINVAL, "d_workspace is NULL");

@@ -124,6 +124,7 @@ struct Request {
     bool grouped = false;     // does (decided at admission)
     GroupGrammar group;
     size_t group_footprint = 0;
+    size_t lane_sweep_footprint = 0;
     int32_t n_right = 0;
     std::vector<int32_t> modes;  // per binary rule: engine product mode (large slots)
     size_t footprint = 0;
@@ -268,14 +269,21 @@ size_t footprint_of(const Request& r) {
         cfpq_graph g;
         cfpq_grammar gr;
         fill_lane_inputs(r, &g, &gr);
-        const cfpq_options o = lane_options();
-        return lane_workspace(&g, &gr, o);
+        return lane_workspace(&g, &gr, lane_options(), false);
     }
     const size_t mat = static_cast<size_t>(r.L.mat_words) * 8;
     size_t f = align_up(mat * r.n_nt, 256);
     if (!r.small) f += align_up(mat * r.n_right, 256);
     f += align_up(r.host_edges.size() * sizeof(cfpq_edge), 256);
     return f;
+}
+
+// A lane request with the row sweeps' workspace, which may be the larger one.
+size_t lane_sweep_footprint_of(const Request& r) {
+    cfpq_graph g;
+    cfpq_grammar gr;
+    fill_lane_inputs(r, &g, &gr);
+    return lane_workspace(&g, &gr, lane_options(), true);
 }
 
 // In the group sweep: the matrices, its workspace, the edges.
@@ -655,7 +663,8 @@ void abandon_slots(cfpq_server* srv) {
     srv->lane_cv.notify_all();
 }
 
-// One lane: oldest lane request first, admitted when its workspace fits.
+// One lane: oldest lane request first, admitted when its workspace fits (the
+// row sweeps', otherwise that of the product loops).
 void lane_main(cfpq_server* srv, int idx) {
     if (hipSetDevice(srv->device) != hipSuccess) {
         fail_all(srv, "hipSetDevice failed in a server lane");
@@ -675,7 +684,9 @@ void lane_main(cfpq_server* srv, int idx) {
                 if (!srv->lane_pending.empty()) {
                     Request* head = srv->lane_pending.front();
                     size_t off = 0;
-                    if (srv->arena.alloc(head->footprint, &off)) {
+                    const bool swept = srv->arena.alloc(head->lane_sweep_footprint, &off);
+                    if (swept || srv->arena.alloc(head->footprint, &off)) {
+                        if (swept) head->footprint = head->lane_sweep_footprint;
                         srv->lane_pending.pop_front();
                         head->arena_off = off;
                         head->state = 1;
@@ -948,6 +959,7 @@ cfpq_status cfpq_server_submit(cfpq_server* srv, const cfpq_graph* graph, const 
         r->n_right = engine_trans_slots(r->bin.data(), nb, r->modes.data(), r->n_nt, false, tr.data());
     }
     r->footprint = footprint_of(*r);
+    if (r->lane) r->lane_sweep_footprint = lane_sweep_footprint_of(*r);
     r->group_fits = !r->small && !r->lane && group_grammar(grammar, r->n, r->n_edges, &r->group);
     if (r->group_fits) r->group_footprint = group_footprint_of(*r);
     if (r->footprint > srv->arena_size)
