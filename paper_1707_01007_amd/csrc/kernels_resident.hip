@@ -584,8 +584,10 @@ __device__ __forceinline__ void resident_closure(const SlotDesc& d, const int32_
         }
 
         // rows: pulls, then scatters -- at once, or where the rows may be
-        // turned once the bits of all rows are counted
-        const bool later = turned && src >= 0 && !first;
+        // turned once the bits of all rows are counted (in the first loop too:
+        // a lane that scatters what a rule of two lists gave its row took Dyck
+        // on G(128, 2560) 330 us, 161 turned)
+        const bool later = turned && src >= 0;
         uint4 held[kPasses];
         int32_t fed = 0;
 #pragma unroll
@@ -900,6 +902,20 @@ bool resident_plan(const cfpq_bin_rule* bin, int32_t n_bin, const cfpq_term_rule
         l = resident_lds(n, plan->g, entries, false);
     }
     if (l.total > resident_max_lds(plan->cls)) return false;
+    // Lists are walked entry by entry: dense graphs go to the kernel that
+    // multiplies.  The lines, in edges a node, with both sides in us (that
+    // kernel, this one): pulls beside scatters or rules of two lists 12 (Dyck,
+    // n = 128: 136, 127; 24: 133, 177); pulls alone 24 (103, 94; 40: 106, 136);
+    // scatters without turned operands 8 (four heads, n = 512: 999, 732; 10:
+    // 685, 696), with products beside them 6 (three heads: 746, 707; 8: 657,
+    // 737); scatters from several nonterminals, which are never turned, 2 up
+    // to two lanes a row (n = 128: 163, 96; 3: 196, 224) and 5 beyond (n = 512,
+    // 6: 828, 793; 8: 613, 581; n = 400, 6: 621, 712).
+    const ResidentGrammar& g = plan->g;
+    int64_t most = g.n_ll > 0 || (g.n_lf > 0 && g.n_rf > 0) ? 12 : g.n_lf > 0 ? 24 : n_edges;
+    if (g.n_rf > 0 && !plan->turned) most = std::min<int64_t>(most, g.n_dd > 0 ? 6 : 8);
+    if (g.n_rf > 0 && g.src < 0) most = std::min<int64_t>(most, resident_lanes(n) < 4 ? 2 : 5);
+    if (n_edges > most * n) return false;
     plan->lds = l.total;
     return true;
 }

@@ -155,7 +155,8 @@ constexpr int32_t kResidentClasses = 8;
 constexpr int32_t kLdsBytes = 160 * 1024;
 __host__ __device__ constexpr int32_t resident_max_lds(int32_t cls) { return cls == 0 ? 156 * 1024 : 158 * 1024; }
 
-// Whether the resident sweep takes a graph of n nodes and this grammar, and for
+// Whether the resident sweep takes a graph of n nodes and n_edges edges and this
+// grammar (tables and lists fit, and the lists are short enough to pay), and for
 // its launch: the grammar as the kernel reads it (kept where the slot's rule
 // triples would be), class, LDS bytes, and whether those hold transposed
 // operands (SlotDesc::tile).
