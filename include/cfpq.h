@@ -154,7 +154,9 @@ typedef struct {
                                 initialisation is OR-ed into them and the loop continues from
                                 there.  The fixpoint is the same (R is the least fixpoint above the
                                 initial matrices, Theorem 2); only the loop count drops. */
-    int64_t max_iters;       /* loop cap; 0 = |V|^2 |N| + 1 (Theorem 3's bound) */
+    int64_t max_iters;       /* loop cap; 0 = |V|^2 |N| + 1 (Theorem 3's bound).  Where it ends a
+                                closure that runs as sweeps, which may take more loops, the closure
+                                runs again as products, and that run counts */
 } cfpq_options;
 
 typedef struct {

@@ -32,6 +32,7 @@ struct BatchPlan {
     std::vector<GroupSlot> group_slots;  // their descriptors, pointers still to come
     std::vector<size_t> group_off;       // their workspace in the tt region
     GroupLists group_lists;
+    std::vector<char> swept;       // by slot: runs in one of the two sweeps
     std::vector<int32_t> all_ids;  // the slots whose matrices the batch initialises (not the resident sweep's)
     std::vector<int64_t> edge_begin;
     std::vector<size_t> edge_copy_off;  // per slot: byte offset in the edge region, or SIZE_MAX (device edges)
@@ -46,10 +47,12 @@ struct BatchPlan {
 // Tables and workspace layout of a batch.  Each instance takes its route
 // from batch_route (forced, or the tuning table); the workspace reserves the
 // transposes and changed-row bitmaps of every instance with rules whatever its
-// route, so its size does not depend on the table.
+// route, so its size does not depend on the table.  sweeps: the resident and
+// the group sweep take the instances they can.
 cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options& o, BatchPlan& p,
-                       const RouteMap* overrides = nullptr, bool jacobi_resident = false) {
+                       const RouteMap* overrides = nullptr, bool jacobi_resident = false, bool sweeps = true) {
     p.n = n;
+    p.swept.assign(n, 0);
     p.descs.resize(n);
     p.edge_copy_off.assign(n, SIZE_MAX);
     p.tt_off.assign(n, 0);
@@ -107,7 +110,7 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
         // the group sweep takes its instances whatever tile the routes name: the
         // tiles are those of the dense rules, which it has fewer of
         GroupGrammar gg;
-        const bool swept = d.n_rules > 0 && d.dirty && !d.jacobi && o.hybrid == CFPQ_HYBRID_AUTO &&
+        const bool swept = sweeps && d.n_rules > 0 && d.dirty && !d.jacobi && o.hybrid == CFPQ_HYBRID_AUTO &&
                            p.group.size() < kGroupMaxSlots && group_grammar(gr, d.n, g.n_edges, &gg);
         if (swept) {
             p.group.push_back(i);
@@ -146,10 +149,11 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
         if (d.n_rules == 0) {
             // nothing to iterate: initialisation only
         } else if (swept) {
+            p.swept[i] = 1;
             continue;  // initialised by group_init
         } else if (d.kind == kSlotLarge) {
             p.large.push_back(i);
-        } else if (!d.jacobi && d.dirty &&
+        } else if (sweeps && !d.jacobi && d.dirty &&
                    resident_plan(gr->bin_rules, gr->n_bin_rules, gr->term_rules, gr->n_term_rules, d.n_nt, d.n,
                                  d.n_edges, &rp)) {
             d.rule_off = static_cast<int32_t>(grammar_at);
@@ -158,6 +162,7 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
             p.sweep[rp.cls].push_back(i);
             p.solo = rp;
             p.sweep_lds[rp.cls] = std::max(p.sweep_lds[rp.cls], rp.lds);
+            p.swept[i] = 1;
             continue;  // initialised by its workgroup
         } else if (d.W == 4) {
             p.small8.push_back(i);
@@ -204,11 +209,20 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
 
 }  // namespace
 
+// Workspace of a batch; with a loop cap also of the second run that instances
+// ended by it may take (batch_closure_run).
+static size_t batch_bytes(int32_t n, const cfpq_instance* inst, const cfpq_options& o, bool jacobi_resident) {
+    BatchPlan p;
+    plan_batch(n, inst, o, p, nullptr, jacobi_resident);
+    if (o.max_iters == 0) return p.total;
+    BatchPlan again;
+    plan_batch(n, inst, o, again, nullptr, jacobi_resident, false);
+    return std::max(p.total, again.total);
+}
+
 size_t batch_workspace_one(const cfpq_graph& graph, const cfpq_grammar* grammar, const cfpq_options& o) {
     const cfpq_instance inst{graph, grammar, nullptr};
-    BatchPlan p;
-    plan_batch(1, &inst, o, p, nullptr, true);
-    return p.total;
+    return batch_bytes(1, &inst, o, true);
 }
 
 namespace {
@@ -276,9 +290,7 @@ cfpq_status cfpq_batch_workspace_bytes(int32_t n_instances, const cfpq_instance*
     const cfpq_options o = resolve_batch(opt);
     cfpq_status st = validate_batch(n_instances, instances, o);
     if (st != CFPQ_OK) return st;
-    BatchPlan p;
-    plan_batch(n_instances, instances, o, p);
-    *bytes = p.total;
+    *bytes = batch_bytes(n_instances, instances, o, false);
     return CFPQ_OK;
 }
 
@@ -306,10 +318,9 @@ cfpq_status cfpq_batch_autotune(int32_t n_instances, const cfpq_instance* instan
     const cfpq_options o = resolve_batch(opt);
     cfpq_status st = validate_batch(n_instances, instances, o);
     if (st != CFPQ_OK) return st;
-    BatchPlan whole;
-    plan_batch(n_instances, instances, o, whole);
-    if (workspace_bytes < whole.total || (whole.total > 0 && !d_workspace))
-        return fail(CFPQ_ENOMEM, "workspace too small: need " + std::to_string(whole.total) + " bytes");
+    const size_t need = batch_bytes(n_instances, instances, o, false);
+    if (workspace_bytes < need || (need > 0 && !d_workspace))
+        return fail(CFPQ_ENOMEM, "workspace too small: need " + std::to_string(need) + " bytes");
     if (reps == 0) reps = 3;
     // The sample: the first max_per_bucket instances of every padded side (all
     // with max_per_bucket = 0) that have something to iterate, in input order.
@@ -441,21 +452,29 @@ static cfpq_status solo_run(BatchPlan& p, const cfpq_instance& inst, hipStream_t
     return CFPQ_OK;
 }
 
-cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instances, const cfpq_options& o,
-                              void* stream, void* d_workspace, size_t workspace_bytes, cfpq_stats* stats,
-                              bool allow_jacobi, const RouteMap* overrides) {
-    cfpq_status vst = validate_batch(n_instances, instances, o, allow_jacobi);
-    if (vst != CFPQ_OK) return vst;
+// One run of a validated batch.  cut: the instances that max_iters ended,
+// those of the sweeps first (*n_swept of them).
+static cfpq_status run_batch(int32_t n_instances, const cfpq_instance* instances, const cfpq_options& o, void* stream,
+                             void* d_workspace, size_t workspace_bytes, cfpq_stats* stats, bool jacobi_resident,
+                             const RouteMap* overrides, bool sweeps, std::vector<int32_t>* cut, size_t* n_swept) {
     BatchPlan p;
-    // cfpq_closure's small closures (allow_jacobi) always run resident
-    plan_batch(n_instances, instances, o, p, overrides, allow_jacobi);
+    // cfpq_closure's small closures (jacobi_resident) always run resident
+    plan_batch(n_instances, instances, o, p, overrides, jacobi_resident, sweeps);
+    cut->clear();
+    *n_swept = 0;
     if (workspace_bytes < p.total || (p.total > 0 && !d_workspace))
         return fail(CFPQ_ENOMEM, "workspace too small: need " + std::to_string(p.total) + " bytes");
     if (n_instances == 0) return CFPQ_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(d_workspace);
-    if (n_instances == 1 && p.large.empty() && p.group.empty() && p.all_ids.empty() && p.solo.g.n_term >= 0)
-        return solo_run(p, instances[0], s, ws, stats);
+    if (n_instances == 1 && p.large.empty() && p.group.empty() && p.all_ids.empty() && p.solo.g.n_term >= 0) {
+        const cfpq_status st = solo_run(p, instances[0], s, ws, stats);
+        if (st == CFPQ_ENOTCONV) {
+            cut->push_back(0);
+            *n_swept = 1;
+        }
+        return st;
+    }
     EngineBuffers b;
     b.descs = reinterpret_cast<SlotDesc*>(ws + p.off_descs);
     b.states = reinterpret_cast<SlotState*>(ws + p.off_states);
@@ -688,11 +707,10 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
                                          " device edges out of range");
     float ms = 0.f;
     CFPQ_HIP(hipEventElapsedTime(&ms, ev0, ev1));
-    bool all_conv = true;
     for (int32_t i = 0; i < n_instances; ++i) {
         const SlotDesc& d = p.descs[i];
         const bool conv = hstates[i].capped == 0;
-        all_conv = all_conv && conv;
+        if (!conv) cut->push_back(i);
         if (stats) {
             cfpq_stats& st = stats[i];
             st.iterations = hstates[i].iterations;
@@ -709,8 +727,43 @@ cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instance
             st.sparse_ms = 0.0;
         }
     }
-    if (!all_conv) return fail(CFPQ_ENOTCONV, "max_iters reached before the fixpoint in some instance");
-    return CFPQ_OK;
+    if (cut->empty()) return CFPQ_OK;
+    const auto swept_end = std::stable_partition(cut->begin(), cut->end(), [&](int32_t i) { return p.swept[i] != 0; });
+    *n_swept = static_cast<size_t>(swept_end - cut->begin());
+    return fail(CFPQ_ENOTCONV, "max_iters reached before the fixpoint in some instance");
+}
+
+cfpq_status batch_closure_run(int32_t n_instances, const cfpq_instance* instances, const cfpq_options& o,
+                              void* stream, void* d_workspace, size_t workspace_bytes, cfpq_stats* stats,
+                              bool allow_jacobi, const RouteMap* overrides) {
+    cfpq_status st = validate_batch(n_instances, instances, o, allow_jacobi);
+    if (st != CFPQ_OK) return st;
+    std::vector<int32_t> cut;
+    size_t n_swept = 0;
+    st = run_batch(n_instances, instances, o, stream, d_workspace, workspace_bytes, stats, allow_jacobi, overrides,
+                   true, &cut, &n_swept);
+    if (st != CFPQ_ENOTCONV || n_swept == 0) return st;
+    // A loop of the products may reach more than one of the sweeps: their
+    // kernels decide about the instances of the sweeps that max_iters ended.
+    std::vector<cfpq_instance> again;
+    for (size_t k = 0; k < n_swept; ++k) again.push_back(instances[cut[k]]);
+    std::vector<cfpq_stats> part(stats ? n_swept : 0);
+    const bool others = n_swept < cut.size();
+    std::vector<int32_t> still;
+    size_t unused = 0;
+    clear_last_error();
+    st = run_batch(static_cast<int32_t>(n_swept), again.data(), o, stream, d_workspace, workspace_bytes,
+                   stats ? part.data() : nullptr, allow_jacobi, overrides, false, &still, &unused);
+    if (st == CFPQ_ENOMEM)  // sized without a loop cap: the first run's results stand
+        return fail(CFPQ_ENOTCONV, "max_iters reached before the fixpoint in some instance");
+    if (stats && (st == CFPQ_OK || st == CFPQ_ENOTCONV)) {
+        const double first_ms = stats[0].device_ms, both_ms = first_ms + part[0].device_ms;
+        for (size_t k = 0; k < n_swept; ++k) stats[cut[k]] = part[k];
+        for (int32_t i = 0; i < n_instances; ++i) stats[i].device_ms = both_ms;
+    }
+    if (st == CFPQ_OK && others)
+        return fail(CFPQ_ENOTCONV, "max_iters reached before the fixpoint in some instance");
+    return st;
 }
 
 }  // namespace cfpq

@@ -489,8 +489,13 @@ cfpq_status closure_impl(const cfpq_graph* graph, const cfpq_grammar* grammar, c
     // a workspace that holds the product loops' matrices but not the sweeps' (a
     // server's arena; one sized for other options) gets those loops
     if (sweeps && sweep_route(graph, grammar, o) && graph->n_edges <= sweep_max_edges(layout_for(graph->n_nodes)) &&
-        workspace_bytes >= loop_workspace(graph, grammar, o, true))
-        return closure_sweep(graph, grammar, o, stream, d_workspace, workspace_bytes, d_result, stats);
+        workspace_bytes >= loop_workspace(graph, grammar, o, true)) {
+        const cfpq_status rs = closure_sweep(graph, grammar, o, stream, d_workspace, workspace_bytes, d_result, stats);
+        // ended by max_iters: a product loop may reach more than a sweep (its
+        // products read what the rules before them added), so those decide
+        if (rs != CFPQ_ENOTCONV) return rs;
+        clear_last_error();
+    }
     const Plan p = make_plan(graph, grammar, o);
     if (p.total > 0 && !d_workspace) return fail(CFPQ_EINVAL, "d_workspace is NULL");
     if (workspace_bytes < p.total)
