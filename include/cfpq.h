@@ -568,7 +568,9 @@ CFPQ_API cfpq_status cfpq_batch_closure(int32_t n_instances, const cfpq_instance
  * hybrid closure of cfpq_closure on its own stream (workspace from the same
  * arena, admitted when it fits -- for the row sweeps, or where only that
  * fits for the product loops -- result written straight to d_result), so
- * their work overlaps the engine's on the device.
+ * their work overlaps the engine's on the device.  Smaller queries that the
+ * row sweeps take and that have a rule over two growing operands go there too
+ * while a lane is idle (or, with one such rule, next to be) and has room.
  * ------------------------------------------------------------------------ */
 
 typedef struct cfpq_server cfpq_server;

@@ -20,6 +20,8 @@
 // the oldest such request whose closure workspace fits the arena and runs the
 // hybrid closure of cfpq_closure on its own stream, writing the result straight
 // to the caller's buffer.  Lanes and the engine share the arena and the GPU.
+// Smaller requests with rules over two growing operands take idle lanes
+// (take_idle_lane).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -118,6 +120,8 @@ struct Request {
     bool small = false;  // resident route (batch tuning table at submit)
     int32_t tile = 256;  // tile route: 256 or 128 tiles
     bool lane = false;   // runs on a lane thread (hybrid closure)
+    bool lane_held = false;  // queued for a lane with its arena block taken
+    int32_t pairs = 0;   // rules over two growing operands, where the row sweeps may run it
     bool swept = false;  // small: by the resident sweep, launched as planned
     ResidentPlan sweep;
     bool group_fits = false;  // may run in the group sweep
@@ -233,6 +237,7 @@ struct cfpq_server {
     int cus = 256;
     // lanes for large requests
     std::deque<cfpq::Request*> lane_pending;
+    int32_t lanes_busy = 0;
     std::condition_variable lane_cv;  // a lane request queued, arena space released, or stop
     std::vector<std::thread> lanes;
     std::vector<hipStream_t> lane_streams;
@@ -264,26 +269,22 @@ void fill_lane_inputs(const Request& r, cfpq_graph* g, cfpq_grammar* gr) {
     gr->bin_rules = r.bin.data();
 }
 
+// Of a lane request: with the row sweeps' workspace, which may be the larger
+// one, or that of the product loops.
+size_t lane_footprint_of(const Request& r, bool sweeps) {
+    cfpq_graph g;
+    cfpq_grammar gr;
+    fill_lane_inputs(r, &g, &gr);
+    return lane_workspace(&g, &gr, lane_options(), sweeps);
+}
+
 size_t footprint_of(const Request& r) {
-    if (r.lane) {
-        cfpq_graph g;
-        cfpq_grammar gr;
-        fill_lane_inputs(r, &g, &gr);
-        return lane_workspace(&g, &gr, lane_options(), false);
-    }
+    if (r.lane) return lane_footprint_of(r, false);
     const size_t mat = static_cast<size_t>(r.L.mat_words) * 8;
     size_t f = align_up(mat * r.n_nt, 256);
     if (!r.small) f += align_up(mat * r.n_right, 256);
     f += align_up(r.host_edges.size() * sizeof(cfpq_edge), 256);
     return f;
-}
-
-// A lane request with the row sweeps' workspace, which may be the larger one.
-size_t lane_sweep_footprint_of(const Request& r) {
-    cfpq_graph g;
-    cfpq_grammar gr;
-    fill_lane_inputs(r, &g, &gr);
-    return lane_workspace(&g, &gr, lane_options(), true);
 }
 
 // In the group sweep: the matrices, its workspace, the edges.
@@ -684,11 +685,12 @@ void lane_main(cfpq_server* srv, int idx) {
                 if (!srv->lane_pending.empty()) {
                     Request* head = srv->lane_pending.front();
                     size_t off = 0;
-                    const bool swept = srv->arena.alloc(head->lane_sweep_footprint, &off);
-                    if (swept || srv->arena.alloc(head->footprint, &off)) {
+                    const bool swept = !head->lane_held && srv->arena.alloc(head->lane_sweep_footprint, &off);
+                    if (head->lane_held || swept || srv->arena.alloc(head->footprint, &off)) {
                         if (swept) head->footprint = head->lane_sweep_footprint;
+                        if (!head->lane_held) head->arena_off = off;
                         srv->lane_pending.pop_front();
-                        head->arena_off = off;
+                        ++srv->lanes_busy;
                         head->state = 1;
                         head->t_admit = now_s();
                         r = head;
@@ -712,11 +714,33 @@ void lane_main(cfpq_server* srv, int idx) {
         r->t_done = t;
         r->state = 2;
         srv->arena.release(r->arena_off, r->footprint);
+        --srv->lanes_busy;
         srv->completed.fetch_add(1);
         srv->done_cv.notify_all();
         srv->lane_cv.notify_all();
         srv->cv.notify_all();
     }
+}
+
+// A request of the worker's loops with rules over two growing operands takes a
+// lane that is idle (with one such rule also the place after the request that a
+// lane runs), when its workspace is free too.  A few of them leave most of the
+// chip idle in the group sweep, 64 rows a workgroup, and between its products;
+// cfpq_closure's sweeps take 16 rows.  Dyck on G(2000, 8000), us in the tile
+// engine / group sweep / lanes: alone 454 / 538 / 360, four together 990 / 1090 /
+// 684; two such rules on G(3000, 12000): 1968 / 2747 / 2055 and 4123 / 5638 /
+// 3940.
+bool take_idle_lane(cfpq_server* srv, Request& r) {
+    if (r.lane || r.lane_sweep_footprint == 0) return false;
+    const int32_t deep = r.pairs == 1 ? 2 : 1;
+    if (srv->lanes_busy + static_cast<int32_t>(srv->lane_pending.size()) >= deep * srv->cfg.hybrid_lanes) return false;
+    // a queued request without its block may be waiting for all of the arena
+    for (const Request* q : srv->lane_pending)
+        if (!q->lane_held) return false;
+    if (!srv->arena.alloc(r.lane_sweep_footprint, &r.arena_off)) return false;
+    r.lane = r.lane_held = true;
+    r.footprint = r.lane_sweep_footprint;
+    return true;
 }
 
 // Room in the arena for a request to join the group sweep; otherwise it runs
@@ -959,8 +983,15 @@ cfpq_status cfpq_server_submit(cfpq_server* srv, const cfpq_graph* graph, const 
         r->n_right = engine_trans_slots(r->bin.data(), nb, r->modes.data(), r->n_nt, false, tr.data());
     }
     r->footprint = footprint_of(*r);
-    if (r->lane) r->lane_sweep_footprint = lane_sweep_footprint_of(*r);
-    r->group_fits = !r->small && !r->lane && group_grammar(grammar, r->n, r->n_edges, &r->group);
+    // (several products a loop: as in group_grammar, from fewer nodes on, since
+    // here the engine's loops are captured already; eight of 2000 nodes and 4
+    // edges a node 3328 us there, 3791 in the group sweep, of 1000 1979 and 1664)
+    r->group_fits = !r->small && !r->lane && group_grammar(grammar, r->n, r->n_edges, &r->group) &&
+                    !(r->group.n_dd > 1 && r->L.W > 16 && r->n_edges > 2 * static_cast<int64_t>(r->n));
+    SweepGrammar sg;
+    if (!r->small && r->L.npad > kSmallMaxPad && r->n_edges <= sweep_max_edges(r->L) && sweep_grammar(grammar, &sg))
+        r->pairs = sg.n_dd;
+    if (r->lane || (r->pairs > 0 && srv->cfg.hybrid_lanes > 0)) r->lane_sweep_footprint = lane_footprint_of(*r, true);
     if (r->group_fits) r->group_footprint = group_footprint_of(*r);
     if (r->footprint > srv->arena_size)
         return fail(CFPQ_ENOMEM, "request needs " + std::to_string(r->footprint) +
@@ -973,7 +1004,7 @@ cfpq_status cfpq_server_submit(cfpq_server* srv, const cfpq_graph* graph, const 
     r->ticket = srv->next_ticket++;
     r->t_submit = now_s();
     *ticket = r->ticket;
-    if (r->lane) {
+    if (r->lane || take_idle_lane(srv, *r)) {
         srv->lane_pending.push_back(r.get());
         srv->tickets[r->ticket] = std::move(r);
         srv->lane_cv.notify_all();
