@@ -781,7 +781,7 @@ __global__ __launch_bounds__(256) void minplus_cols_row_kernel(const uint64_t* _
 // Overflow check: a new cell that no rule gave a finite sum (still kInf)
 // has a length that did not fit (its Boolean product term exists, so some sum
 // was >= 2^31 - 1); it goes back to 0 (absent).
-// *longest gets the largest length of the others.
+// *longest (unless null) gets the largest length of the others.
 __global__ __launch_bounds__(256) void check_new_cells_kernel(const uint64_t* __restrict__ D,
                                                               uint32_t* __restrict__ LA, int64_t W, int64_t npad,
                                                               int32_t* overflow, uint32_t* longest) {
@@ -804,6 +804,7 @@ __global__ __launch_bounds__(256) void check_new_cells_kernel(const uint64_t* __
             }
         }
     }
+    if (longest == nullptr) return;
     for (int o = 32; o > 0; o >>= 1) most = max(most, static_cast<uint32_t>(__shfl_xor(static_cast<int>(most), o, 64)));
     if ((threadIdx.x & 63) == 0 && most > __hip_atomic_load(longest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
         atomicMax(longest, most);
@@ -1161,7 +1162,10 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
                     std::min({n, static_cast<double>(dcount[br.lhs]), 64.0 * tiles[br.lhs]});
                 const double rows_ms = active_rows * static_cast<double>(xcount[br.left]) / n * 1e-5;
                 const double tile_ms = static_cast<double>(tiles[br.lhs]) * kchunks * 131072.0 / 2e10;
-                const bool pow = powers && pow_ms(tiles[br.lhs]) < tile_ms;
+                // (tile_ms counts every chunk; the VALU kernel passes over those
+                // without bits, all but a few on a chain of 3000 nodes: 26 us a
+                // step, 58 by this estimate, 71 on the matrix cores)
+                const bool pow = powers && pow_ms(tiles[br.lhs]) < 0.7 * tile_ms;
                 const double best_ms = pow ? pow_ms(tiles[br.lhs]) : tile_ms;
                 // (rows_ms is high by up to 6 where rows are short: 27 us
                 // against 164 at n = 4096 and 16 k bits)
@@ -1245,7 +1249,7 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
         for (int32_t a = 0; a < n_nt; ++a) {
             if (!flags[a]) continue;
             check_new_cells_kernel<<<dim3(grid_for(static_cast<int64_t>(mw), 4096)), dim3(256), 0, s>>>(
-                D + a * mw, d_lengths + a * lmat, L.W, L.npad, d_overflow, d_longest);
+                D + a * mw, d_lengths + a * lmat, L.W, L.npad, d_overflow, cells_fit ? d_longest : nullptr);
             CFPQ_HIP(hipGetLastError());
             CFPQ_HIP(hipMemcpyAsync(X + a * mw, Y + a * mw, mw * 8, hipMemcpyDeviceToDevice, s));
         }
