@@ -27,7 +27,7 @@ struct BatchPlan {
     std::vector<int32_t> rules, modes, trans, term, large, small8, small16;
     std::vector<int32_t> sweep[kResidentClasses];  // slots of the resident sweep, by launch class
     int32_t sweep_lds[kResidentClasses] = {};
-    ResidentPlan solo;  // of the last of them
+    ResidentPlan solo;  // of a lone one
     std::vector<int32_t> group;  // slots of the group sweep
     std::vector<GroupSlot> group_slots;  // their descriptors, pointers still to come
     std::vector<size_t> group_off;       // their workspace in the tt region
@@ -58,6 +58,10 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
     p.tt_off.assign(n, 0);
     p.edge_begin.assign(1, 0);
     size_t edge_bytes = 0, tt_bytes = 0;
+    const cfpq_grammar* kept_grammar = nullptr;  // the last one planned for the resident sweep, and its place
+    bool kept_queue = false, kept_ok = false;
+    size_t kept_at = 0;
+    ResidentPlan rp;
     for (int32_t i = 0; i < n; ++i) {
         const cfpq_graph& g = inst[i].graph;
         const cfpq_grammar* gr = inst[i].grammar;
@@ -138,14 +142,25 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
             edge_bytes += align_up(static_cast<size_t>(g.n_edges) * sizeof(cfpq_edge), 256);
         }
         // room for the resident sweep's grammar among the rule triples (in whole
-        // triples), whatever route and schedule the instance takes
+        // triples), whatever route and schedule the instance takes; instances
+        // in a row with one grammar share it
         constexpr size_t kTriples = (sizeof(ResidentGrammar) + 11) / 12;
-        const size_t grammar_at = p.rules.size() / 3;
         if (d.n_rules > 0 && L.npad <= kSmallMaxPad) {
-            p.rules.resize(p.rules.size() + 3 * kTriples, 0);
-            p.modes.resize(p.modes.size() + kTriples, kModeDense);
+            const bool queue = resident_queues(d.n, d.n_edges);
+            if (gr != kept_grammar || queue != kept_queue) {
+                const bool none = kept_grammar == nullptr;
+                kept_grammar = gr;
+                kept_queue = queue;
+                kept_ok = resident_rules(gr, queue, &rp);
+                // (compared by content: where the caller keeps it decides nothing)
+                if (none || std::memcmp(p.rules.data() + 3 * kept_at, &rp.g, sizeof(rp.g)) != 0) {
+                    kept_at = p.rules.size() / 3;
+                    p.rules.resize(p.rules.size() + 3 * kTriples, 0);
+                    p.modes.resize(p.modes.size() + kTriples, kModeDense);
+                    std::memcpy(p.rules.data() + 3 * kept_at, &rp.g, sizeof(rp.g));
+                }
+            }
         }
-        ResidentPlan rp;
         if (d.n_rules == 0) {
             // nothing to iterate: initialisation only
         } else if (swept) {
@@ -154,13 +169,11 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
         } else if (d.kind == kSlotLarge) {
             p.large.push_back(i);
         } else if (sweeps && !d.jacobi && d.dirty &&
-                   resident_plan(gr->bin_rules, gr->n_bin_rules, gr->term_rules, gr->n_term_rules, d.n_nt, d.n,
-                                 d.n_edges, &rp)) {
-            d.rule_off = static_cast<int32_t>(grammar_at);
-            std::memcpy(p.rules.data() + 3 * grammar_at, &rp.g, sizeof(rp.g));
+                   kept_ok && resident_fits(d.n, d.n_edges, &rp)) {
+            d.rule_off = static_cast<int32_t>(kept_at);
             d.tile = rp.turned;
             p.sweep[rp.cls].push_back(i);
-            p.solo = rp;
+            if (n == 1) p.solo = rp;
             p.sweep_lds[rp.cls] = std::max(p.sweep_lds[rp.cls], rp.lds);
             p.swept[i] = 1;
             continue;  // initialised by its workgroup

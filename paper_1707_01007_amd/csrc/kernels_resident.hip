@@ -861,19 +861,19 @@ hipError_t launch(const EngineBuffers& b, const int32_t* ids, int32_t count, int
 
 }  // namespace
 
-bool resident_plan(const cfpq_bin_rule* bin, int32_t n_bin, const cfpq_term_rule* term, int32_t n_term, int32_t n_nt,
-                   int32_t n, int64_t n_edges, ResidentPlan* plan) {
-    if (n <= 0 || n > kSmallMaxPad || n_bin < 1 || n_bin > kRsMaxBin) return false;
+bool resident_rules(const cfpq_grammar* gr, bool queue, ResidentPlan* plan) {
+    const int32_t n_bin = gr->n_bin_rules, n_term = gr->n_term_rules;
+    std::memset(&plan->g, 0, sizeof(plan->g));
+    if (n_bin < 1 || n_bin > kRsMaxBin) return false;
     int32_t rules[3 * kRsMaxBin];
     for (int32_t r = 0; r < n_bin; ++r) {
-        rules[3 * r] = bin[r].lhs;
-        rules[3 * r + 1] = bin[r].left;
-        rules[3 * r + 2] = bin[r].right;
+        rules[3 * r] = gr->bin_rules[r].lhs;
+        rules[3 * r + 1] = gr->bin_rules[r].left;
+        rules[3 * r + 2] = gr->bin_rules[r].right;
     }
-    // sparse graphs of one lane a row: see follow_facts
-    const bool one = resident_lanes(n) == 1, sparse = n_edges < 2 * static_cast<int64_t>(n);
-    if (!resident_grammar(rules, n_bin, n_nt, one && sparse, &plan->g)) return false;
-    int32_t per_edge = 1;  // the most terminal rules of one label
+    if (!resident_grammar(rules, n_bin, gr->n_nonterminals, queue, &plan->g)) return false;
+    const cfpq_term_rule* term = gr->term_rules;
+    int32_t per_edge = 1;
     bool fits = n_term <= kRsMaxTerm;
     for (int32_t r = 0; r < n_term; ++r) {
         int32_t c = 0;
@@ -881,12 +881,19 @@ bool resident_plan(const cfpq_bin_rule* bin, int32_t n_bin, const cfpq_term_rule
         per_edge = std::max(per_edge, c);
         fits = fits && term[r].terminal < (1 << 23);
     }
+    plan->per_edge = per_edge;
     if (fits) {
         plan->g.n_term = n_term;
         for (int32_t r = 0; r < n_term; ++r) plan->g.term[r] = term[r].terminal << 8 | term[r].lhs;
     }
+    return true;
+}
+
+bool resident_fits(int32_t n, int64_t n_edges, ResidentPlan* plan) {
+    if (n <= 0 || n > kSmallMaxPad) return false;
+    const bool one = resident_lanes(n) == 1, sparse = n_edges < 2 * static_cast<int64_t>(n);
     // an edge enters at most two lists (outgoing, incoming) per terminal rule of its label
-    const int64_t entries = 2 * n_edges * per_edge;
+    const int64_t entries = 2 * n_edges * plan->per_edge;
     // one lane a row: with two edges a node and more.  On sparser graphs a loop
     // sets few bits, and the kernel without the turned code takes a fifth less a
     // loop over rows (two cycles of 64 and 63 nodes, without follow_facts: 5.6

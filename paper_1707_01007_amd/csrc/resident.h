@@ -162,10 +162,20 @@ __host__ __device__ constexpr int32_t resident_max_lds(int32_t cls) { return cls
 // operands (SlotDesc::tile).
 struct ResidentPlan {
     ResidentGrammar g;
+    int32_t per_edge;  // the most terminal rules of one label
     int32_t cls, lds, turned;
 };
-bool resident_plan(const cfpq_bin_rule* bin, int32_t n_bin, const cfpq_term_rule* term, int32_t n_term, int32_t n_nt,
-                   int32_t n, int64_t n_edges, ResidentPlan* plan);
+// Graphs that may follow single facts: sparse, one lane a row.
+inline bool resident_queues(int32_t n, int64_t n_edges) {
+    return resident_lanes(n) == 1 && n_edges < 2 * static_cast<int64_t>(n);
+}
+// The grammar's part (the same for every graph with the same `queue`), then the
+// graph's; resident_plan does both.
+bool resident_rules(const cfpq_grammar* gr, bool queue, ResidentPlan* plan);
+bool resident_fits(int32_t n, int64_t n_edges, ResidentPlan* plan);
+inline bool resident_plan(const cfpq_grammar* gr, int32_t n, int64_t n_edges, ResidentPlan* plan) {
+    return resident_rules(gr, resident_queues(n, n_edges), plan) && resident_fits(n, n_edges, plan);
+}
 
 // What resident_solo leaves in pinned host memory; loop = 1 comes last.
 struct ResidentReport {

@@ -974,8 +974,7 @@ cfpq_status cfpq_server_submit(cfpq_server* srv, const cfpq_graph* graph, const 
     r->tile = rt.tile;
     r->lane = srv->cfg.hybrid_lanes > 0 && r->L.npad >= kHybridMinRows;
     const int32_t nb = static_cast<int32_t>(r->bin.size());
-    r->swept = r->small && resident_plan(r->bin.data(), nb, r->term.data(), static_cast<int32_t>(r->term.size()),
-                                         r->n_nt, r->n, r->n_edges, &r->sweep);
+    r->swept = r->small && resident_plan(grammar, r->n, r->n_edges, &r->sweep);
     r->modes.assign(nb, kModeDense);
     if (!r->small && !r->lane) {
         for (int32_t q = 0; q < nb; ++q) r->modes[q] = engine_rule_mode(r->bin.data(), nb, q, r->n_edges, r->L.npad);
