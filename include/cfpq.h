@@ -494,6 +494,8 @@ CFPQ_API cfpq_status cfpq_batch_autotune_workspace_bytes(int32_t n_instances, co
  * their current route (the table's, or the default) -- so the overlap of
  * resident workgroups with the tile work list is part of the measurement --
  * as the median host wall time of `reps` runs (0 = 3) after one warm-up run.
+ * (Candidates that run the same program -- tiles of a side whose instances all
+ * run as row sweeps -- are timed once and get the same time.)
  * A candidate replaces the current route only if it is more than 2% faster.
  * Every choice is recorded in the batch tuning table, which
  * cfpq_batch_closure and servers created afterwards read.  The sample's

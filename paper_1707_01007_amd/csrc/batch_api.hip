@@ -44,6 +44,12 @@ struct BatchPlan {
     std::vector<size_t> tt_off;  // per slot: byte offset of its transposes (large) in the tt region
 };
 
+// Whether the group sweep takes an instance with these options.
+bool group_takes(const cfpq_instance& inst, const cfpq_options& o, GroupGrammar* g) {
+    return inst.grammar->n_bin_rules > 0 && o.dirty_worklist && o.schedule == CFPQ_SCHEDULE_INPLACE &&
+           o.hybrid == CFPQ_HYBRID_AUTO && group_grammar(inst.grammar, inst.graph.n_nodes, inst.graph.n_edges, g);
+}
+
 // Tables and workspace layout of a batch.  Each instance takes its route
 // from batch_route (forced, or the tuning table); the workspace reserves the
 // transposes and changed-row bitmaps of every instance with rules whatever its
@@ -114,8 +120,7 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
         // the group sweep takes its instances whatever tile the routes name: the
         // tiles are those of the dense rules, which it has fewer of
         GroupGrammar gg;
-        const bool swept = sweeps && d.n_rules > 0 && d.dirty && !d.jacobi && o.hybrid == CFPQ_HYBRID_AUTO &&
-                           p.group.size() < kGroupMaxSlots && group_grammar(gr, d.n, g.n_edges, &gg);
+        const bool swept = sweeps && p.group.size() < kGroupMaxSlots && group_takes(inst[i], o, &gg);
         if (swept) {
             p.group.push_back(i);
             p.group_slots.push_back(group_slot(gg, d.n));
@@ -338,6 +343,7 @@ cfpq_status cfpq_batch_autotune(int32_t n_instances, const cfpq_instance* instan
     // The sample: the first max_per_bucket instances of every padded side (all
     // with max_per_bucket = 0) that have something to iterate, in input order.
     std::map<int64_t, int32_t> per_side;
+    std::map<int64_t, bool> tiled;  // by side: some instance's loops depend on the tile
     std::vector<cfpq_instance> sample;
     for (int32_t i = 0; i < n_instances; ++i) {
         const cfpq_instance& in = instances[i];
@@ -345,6 +351,8 @@ cfpq_status cfpq_batch_autotune(int32_t n_instances, const cfpq_instance* instan
         int32_t& k = per_side[layout_for(in.graph.n_nodes).npad];
         if (max_per_bucket > 0 && k >= max_per_bucket) continue;
         ++k;
+        GroupGrammar gg;
+        if (o.max_iters > 0 || !group_takes(in, o, &gg)) tiled[layout_for(in.graph.n_nodes).npad] = true;
         sample.push_back(in);
     }
     const int32_t count = static_cast<int32_t>(sample.size());
@@ -391,9 +399,11 @@ cfpq_status cfpq_batch_autotune(int32_t n_instances, const cfpq_instance* instan
         BatchRoute best = current;
         for (size_t c = 0; c < cands.size(); ++c) {
             routes[npad] = cands[c];
-            float ms = 0.f;
-            st = time_sample(routes, &ms);
-            if (st != CFPQ_OK) return st;
+            float ms = c > 0 ? e.candidates_ms[0] : 0.f;
+            if (c == 0 || tiled[npad]) {  // else the group sweep's, as the first candidate
+                st = time_sample(routes, &ms);
+                if (st != CFPQ_OK) return st;
+            }
             e.candidate_route[c] = cands[c].route;
             e.candidate_tile[c] = cands[c].route == kRouteTiles ? cands[c].tile : 0;
             e.candidates_ms[c] = ms;
