@@ -163,12 +163,12 @@ typedef struct {
     int64_t iterations;      /* loop executions, including the final one that changed nothing */
     int64_t products;        /* Boolean products executed (dense and sparse) */
     double bitops;           /* 2 * npad^3 per executed dense product, npad = cfpq_padded_rows(n);
-                                ROWS / COLS products are not counted */
+                                ROWS / COLS products and rules that sweeps applied are not counted */
     double device_ms;        /* device time from matrix initialisation to the last flag */
     double product_ms;       /* summed duration of the product kernels (options.profile), else 0 */
     int32_t path_used;       /* CFPQ_PATH_BITS, MFMA or FP4 (dense kernel), ROWS or COLS */
     int32_t converged;       /* 1 if the fixpoint was reached */
-    int64_t sparse_products; /* products of `products` that ran as ROWS or COLS */
+    int64_t sparse_products; /* products of `products` that ran as ROWS or COLS, or in a sweep */
     int64_t delta_products;  /* products of `products` with a delta operand: a rule A -> B C whose
                                 operands gained the bits D_B, D_C since the previous loop started
                                 may add D_B x C and B x D_C instead of B x C (hybrid choice) */
@@ -593,7 +593,7 @@ typedef struct {
     double queue_ms;       /* submit -> admission */
     double run_ms;         /* admission -> result copied */
     double latency_ms;     /* submit -> result copied */
-    cfpq_stats stats;      /* iterations, products, bitops of this query */
+    cfpq_stats stats;      /* iterations, products (also sparse ones), bitops of this query */
 } cfpq_request_info;
 
 CFPQ_API void cfpq_server_default_config(cfpq_server_config* cfg);

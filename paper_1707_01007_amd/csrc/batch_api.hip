@@ -466,7 +466,8 @@ static cfpq_status solo_run(BatchPlan& p, const cfpq_instance& inst, hipStream_t
         std::memset(stats, 0, sizeof(*stats));
         stats->iterations = report->iterations;
         stats->products = report->products;
-        stats->bitops = 2.0 * static_cast<double>(d.npad) * d.npad * d.npad * static_cast<double>(report->products);
+        stats->sparse_products = report->products - report->dense;
+        stats->bitops = 2.0 * static_cast<double>(d.npad) * d.npad * d.npad * static_cast<double>(report->dense);
         stats->device_ms = static_cast<double>(report->ticks) / wall_clock_khz();
         stats->path_used = CFPQ_PATH_BITS;
         stats->converged = report->capped == 0 ? 1 : 0;
@@ -738,12 +739,12 @@ static cfpq_status run_batch(int32_t n_instances, const cfpq_instance* instances
             cfpq_stats& st = stats[i];
             st.iterations = hstates[i].iterations;
             st.products = hstates[i].products;
-            st.bitops = 2.0 * static_cast<double>(d.npad) * d.npad * d.npad * static_cast<double>(st.products);
+            st.bitops = 2.0 * static_cast<double>(d.npad) * d.npad * d.npad * static_cast<double>(hstates[i].dense);
             st.device_ms = ms;
             st.product_ms = 0.0;
             st.path_used = d.kind == kSlotLarge ? CFPQ_PATH_FP4 : CFPQ_PATH_BITS;
             st.converged = conv ? 1 : 0;
-            st.sparse_products = 0;
+            st.sparse_products = st.products - hstates[i].dense;
             st.delta_products = 0;
             st.minplus_terms = 0.0;
             st.sparse_bytes = 0.0;

@@ -85,6 +85,7 @@ struct SlotState {
     int32_t fresh;      // admitted, transposes not built yet (large slots)
     int64_t iterations;
     int64_t products;
+    int64_t dense;      // those that multiplied whole matrices
     int32_t changed[CFPQ_MAX_NONTERMINALS];
     int32_t changed_prev[CFPQ_MAX_NONTERMINALS];
 };

@@ -327,6 +327,7 @@ __global__ __launch_bounds__(256) void engine_resident_kernel(const SlotDesc* __
         SlotState* st = states + slot;
         st->iterations = iters;
         st->products = products;
+        st->dense = products;
         st->capped = capped;
         st->done = 1;
         st->active = 0;
@@ -856,7 +857,8 @@ __global__ __launch_bounds__(256) void engine_transpose_kernel(const SlotDesc* _
 // End of a loop: count it and its products for every slot that took part; a
 // slot whose loop set no bit has reached its fixpoint.
 __device__ void engine_finish_body(SlotState* states, EngineState* es, const SlotDesc* __restrict__ descs,
-                                   const int32_t* __restrict__ go_tab, const int32_t* __restrict__ large_ids) {
+                                   const int32_t* __restrict__ go_tab, const int32_t* __restrict__ mode_tab,
+                                   const int32_t* __restrict__ large_ids) {
     const int n_large = es->n_large;
     for (int q = threadIdx.x; q < n_large; q += blockDim.x) {
         const int slot = large_ids[q];
@@ -864,9 +866,13 @@ __device__ void engine_finish_body(SlotState* states, EngineState* es, const Slo
         if (st->in_loop) {
             st->iterations += 1;
             const SlotDesc& d = descs[slot];
-            int launched = 0;
-            for (int r = 0; r < d.n_rules; ++r) launched += go_tab[d.rule_off + r];
+            int launched = 0, dense = 0;
+            for (int r = 0; r < d.n_rules; ++r) {
+                launched += go_tab[d.rule_off + r];
+                dense += mode_tab[d.rule_off + r] == kModeDense ? go_tab[d.rule_off + r] : 0;
+            }
             st->products += launched;
+            st->dense += dense;
             const int n_nt = d.n_nt;
             int any = 0;
             for (int a = 0; a < n_nt; ++a) any |= st->changed[a];
@@ -888,12 +894,13 @@ __device__ void engine_finish_body(SlotState* states, EngineState* es, const Slo
 __global__ __launch_bounds__(256) void engine_tplan_finish_kernel(const SlotDesc* __restrict__ descs,
                                                                   SlotState* states,
                                                                   const int32_t* __restrict__ trans_tab,
-                                                                  const int32_t* __restrict__ go_tab, Job* tjobs,
+                                                                  const int32_t* __restrict__ go_tab,
+                                                                  const int32_t* __restrict__ mode_tab, Job* tjobs,
                                                                   EngineState* es,
                                                                   const int32_t* __restrict__ large_ids) {
     engine_tplan_body(descs, states, trans_tab, tjobs, es, large_ids, 0);
     __syncthreads();
-    engine_finish_body(states, es, descs, go_tab, large_ids);
+    engine_finish_body(states, es, descs, go_tab, mode_tab, large_ids);
 }
 
 }  // namespace
@@ -970,7 +977,7 @@ hipError_t engine_transposes(const EngineBuffers& b, int32_t grid, int32_t plan,
 }
 
 hipError_t engine_tplan_finish(const EngineBuffers& b, hipStream_t s) {
-    engine_tplan_finish_kernel<<<dim3(1), dim3(256), 0, s>>>(b.descs, b.states, b.trans_tab, b.go_tab, b.tjobs,
+    engine_tplan_finish_kernel<<<dim3(1), dim3(256), 0, s>>>(b.descs, b.states, b.trans_tab, b.go_tab, b.mode_tab, b.tjobs,
                                                              b.es, b.large_ids);
     return hipGetLastError();
 }

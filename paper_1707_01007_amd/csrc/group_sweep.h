@@ -42,7 +42,7 @@ struct GroupCtl {
     uint32_t any[4];  // dynamic nonterminals changed by loop t, at t & 3
     int32_t loops, capped, bad_edges;
     int32_t list_top;  // entries of idx in use
-    int64_t products;
+    int64_t products, dense;  // dense: of the rules over two growing operands
     int32_t spare;  // change flag nobody reads
 };
 

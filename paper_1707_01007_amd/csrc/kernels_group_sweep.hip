@@ -573,10 +573,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWide ? 3 :
                 const uint32_t q = d.g.rule[r];
                 c += (before >> (r < d.g.n_lf ? right_of(q) : left_of(q))) & 1u;
             }
+            int32_t dense = 0;
             for (int r = n_lr + d.g.n_ll; r < n_lr + d.g.n_ll + d.g.n_dd; ++r)
-                c += ((before >> left_of(d.g.rule[r])) | (before >> right_of(d.g.rule[r]))) & 1u;
+                dense += ((before >> left_of(d.g.rule[r])) | (before >> right_of(d.g.rule[r]))) & 1u;
             ctl->loops = t;
-            ctl->products += c;
+            ctl->products += c + dense;
+            ctl->dense += dense;
         } else if (before != 0) {
             ctl->capped = 1;
         }
@@ -632,6 +634,7 @@ __global__ __launch_bounds__(64) void group_finish_kernel(const GroupSlot* __res
     SlotState& st = states[slots[i].slot];
     st.iterations = c.loops;
     st.products = c.products;
+    st.dense = c.dense;
     st.capped = c.capped;
     st.bad_edges = c.bad_edges;
     st.done = c.any[own_loop(slots[i], loop) & 3] == 0 ? 1 : 0;

@@ -416,6 +416,7 @@ __device__ __forceinline__ void resident_closure(const SlotDesc& d, const int32_
 
     // ---- the fixpoint: loop t reads the marks of loop t - 1
     int64_t products = 0, t = 0;
+    int dense = 0;  // products by tiles
     int capped = 0;
     int prev = 0, cur = 1, next = 2;  // t % 3 of the last, this and the next loop
     bool refeed = false;  // this loop scatters all bits of T, as the first one does
@@ -523,6 +524,7 @@ __device__ __forceinline__ void resident_closure(const SlotDesc& d, const int32_
                 // tiles of 32 rows i x 128 columns j: the four words of one lane's part of row i
                 const int g = lane >> 5, r32 = lane & 31;
                 const int ti = (n + 31) / 32, tj = lay.rows / 128;
+                dense += n_dd;
                 for (int r = 0; r < n_dd; ++r) {
                     const int h = rs_head(dd, r);
                     const uint32_t* Bm = T + d_nt * mat;
@@ -797,6 +799,7 @@ __device__ __forceinline__ void resident_closure(const SlotDesc& d, const int32_
     if (tid == 0) {
         out->iterations = t;
         out->products = products;
+        out->dense = dense;
         out->capped = capped;
         out->bad_edges = bad_s;
         out->done = 1;
@@ -828,6 +831,7 @@ __global__ __launch_bounds__(threads_for(L)) void resident_solo_kernel(SlotDesc 
     if (threadIdx.x != 0) return;
     report->iterations = st.iterations;
     report->products = st.products;
+    report->dense = st.dense;
     report->capped = st.capped;
     report->bad_edges = st.bad_edges;
     report->ticks = wall_clock64() - begin;

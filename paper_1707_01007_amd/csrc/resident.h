@@ -179,7 +179,7 @@ inline bool resident_plan(const cfpq_grammar* gr, int32_t n, int64_t n_edges, Re
 
 // What resident_solo leaves in pinned host memory; loop = 1 comes last.
 struct ResidentReport {
-    int64_t iterations, products;
+    int64_t iterations, products, dense;
     uint64_t ticks;  // of the constant clock, from start to end
     int32_t capped, bad_edges, loop, pad;
 };

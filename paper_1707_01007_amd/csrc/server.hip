@@ -577,7 +577,8 @@ bool turn(cfpq_server* srv, std::vector<Request*>& admitted) {
             r->t_done = t;
             r->stats.iterations = st.iterations;
             r->stats.products = st.products;
-            r->stats.bitops = 2.0 * static_cast<double>(r->L.npad) * r->L.npad * r->L.npad * st.products;
+            r->stats.sparse_products = st.products - st.dense;
+            r->stats.bitops = 2.0 * static_cast<double>(r->L.npad) * r->L.npad * r->L.npad * st.dense;
             r->stats.device_ms = (r->t_done - r->t_admit) * 1e3;
             r->stats.product_ms = 0.0;
             r->stats.path_used = r->small ? CFPQ_PATH_BITS : CFPQ_PATH_FP4;
