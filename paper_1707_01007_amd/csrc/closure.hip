@@ -486,17 +486,18 @@ cfpq_status closure_impl(const cfpq_graph* graph, const cfpq_grammar* grammar, c
         }
         return rs;
     }
-    // a workspace that holds the product loops' matrices but not the sweeps' (a
-    // server's arena; one sized for other options) gets those loops
-    if (sweeps && sweep_route(graph, grammar, o) && graph->n_edges <= sweep_max_edges(layout_for(graph->n_nodes)) &&
-        workspace_bytes >= loop_workspace(graph, grammar, o, true)) {
-        const cfpq_status rs = closure_sweep(graph, grammar, o, stream, d_workspace, workspace_bytes, d_result, stats);
-        // ended by max_iters: a product loop may reach more than a sweep (its
-        // products read what the rules before them added), so those decide
-        if (rs != CFPQ_ENOTCONV) return rs;
-        clear_last_error();
+    cfpq_status swept = CFPQ_ENOMEM;
+    if (sweeps && sweep_route(graph, grammar, o) && graph->n_edges <= sweep_max_edges(layout_for(graph->n_nodes))) {
+        swept = closure_sweep(graph, grammar, o, stream, d_workspace, workspace_bytes, d_result, stats);
+        // The product loops run where the workspace holds their matrices but
+        // not the sweeps' (a server's arena; one sized for other options), and
+        // after sweeps that max_iters ended: a product loop may reach more
+        // (its products read what the rules before them added).
+        if (swept != CFPQ_ENOMEM && swept != CFPQ_ENOTCONV) return swept;
     }
     const Plan p = make_plan(graph, grammar, o);
+    if (swept == CFPQ_ENOTCONV && workspace_bytes < p.total) return swept;
+    clear_last_error();
     if (p.total > 0 && !d_workspace) return fail(CFPQ_EINVAL, "d_workspace is NULL");
     if (workspace_bytes < p.total)
         return fail(CFPQ_ENOMEM, "workspace too small: need " + std::to_string(p.total) + " bytes");

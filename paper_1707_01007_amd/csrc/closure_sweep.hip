@@ -56,7 +56,9 @@ SweepPlan sweep_plan(const cfpq_graph* gr, const SweepGrammar& g) {
     const size_t lists = static_cast<size_t>(std::max(g.n_list, 1)) * std::max(L.n, 1);
     p.off_wg = take(static_cast<size_t>(2) * g.n_dyn * sweep_groups(L.n) * 4);
     p.off_chg = take(static_cast<size_t>(4) * g.n_dyn * L.W * 8);
+    static_assert(sizeof(SweepCtl) % 256 == 0, "the inbox follows");
     p.off_ctl = take(sizeof(SweepCtl));
+    take(sweep_inbox_bytes(L));  // after ctl, where the kernels look for it
     p.off_list = take(lists * 8);
     p.off_cur = take(lists * 4);
     p.off_near = take(lists * 16);
@@ -192,7 +194,8 @@ cfpq_status closure_sweep(const cfpq_graph* graph, const cfpq_grammar* grammar, 
                       "{\"event\": \"loop\", \"loop\": %lld, \"rules_launched\": %lld, \"changed\": %d, "
                       "\"products\": %lld, \"sparse_products\": %lld, \"delta_products\": %lld, "
                       "\"host_ms\": %.4f}",
-                      static_cast<long long>(loop), static_cast<long long>(launched), __builtin_popcount(any),
+                      static_cast<long long>(loop), static_cast<long long>(launched),
+                      __builtin_popcount(any & ~(kSwInboxBit | kSwHubsBit)),
                       static_cast<long long>(products), static_cast<long long>(sparse), static_cast<long long>(delta),
                       std::chrono::duration<double, std::milli>(now - log_t).count());
         log_t = now;

@@ -30,6 +30,22 @@ struct InitArgs {
     int64_t W, mat_words;
 };
 
+// counter[i * stride] += 1 on the active lanes; the value before it, a different
+// one a lane.  Lanes with the first one's i add together when they are many: a
+// hub's edges (a star of 16384 nodes spent 200 us a kernel on one counter, now
+// 21 in the scatter and 5 in the fill).
+__device__ __forceinline__ int32_t count_up(int32_t* counter, int32_t stride, int32_t i) {
+    constexpr int kMany = 24;
+    int32_t* at = counter + static_cast<int64_t>(i) * stride;
+    const bool same = i == __builtin_amdgcn_readfirstlane(i);
+    const uint64_t m = __ballot(same);
+    if (__popcll(m) < kMany || !same) return atomicAdd(at, 1);
+    const int lane = threadIdx.x & 63, who = __ffsll(static_cast<unsigned long long>(m)) - 1;
+    int32_t base = 0;
+    if (lane == who) base = atomicAdd(at, static_cast<int32_t>(__popcll(m)));
+    return __builtin_amdgcn_readlane(base, who) + static_cast<int32_t>(__popcll(m & ((1ull << lane) - 1)));
+}
+
 // One thread per edge: the bits of Algorithm 1's matrix initialisation, and
 // the lengths of the adjacency lists.  Parallel edges may enter a list twice.
 __global__ __launch_bounds__(256) void sweep_scatter_kernel(const cfpq_edge* __restrict__ edges, int64_t m,
@@ -46,15 +62,26 @@ __global__ __launch_bounds__(256) void sweep_scatter_kernel(const cfpq_edge* __r
     for (int32_t q = 0; q < a.n_term; ++q) {
         if (a.term[q].label != ed.label) continue;
         atomicOr(reinterpret_cast<unsigned long long*>(T + a.term[q].nt * a.mat_words + off), bit);
-        if (a.term[q].out >= 0) atomicAdd(&list[static_cast<int64_t>(a.term[q].out) * a.n + ed.src].y, 1);
-        if (a.term[q].in >= 0) atomicAdd(&list[static_cast<int64_t>(a.term[q].in) * a.n + ed.dst].y, 1);
+        if (a.term[q].out >= 0) count_up(&list[0].y, 2, a.term[q].out * a.n + ed.src);
+        if (a.term[q].in >= 0) count_up(&list[0].y, 2, a.term[q].in * a.n + ed.dst);
     }
 }
+
+// Entries from which a list is a hub's.
+__host__ __device__ inline int32_t hub_list(int64_t W) { return static_cast<int32_t>(kSwHubWords / W); }
+
+// Lists that would be hubs: the fixed operands of lf and of rf rules (n_rules = 0:
+// none are looked for), and their nonterminals.
+struct HubArgs {
+    uint8_t list[2 * kSwMaxRules], nt[2 * kSwMaxRules];
+    int32_t n_rules, n, longest;
+};
 
 // Places of the lists in idx: a workgroup's lists are consecutive, the
 // workgroups' runs come in any order (one atomic each).
 __global__ __launch_bounds__(256) void sweep_place_kernel(int2* list, int32_t* __restrict__ cur,
-                                                          uint4* __restrict__ near, int32_t lists, SweepCtl* ctl) {
+                                                          uint4* __restrict__ near, int32_t lists, SweepCtl* ctl,
+                                                          HubArgs hubs) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     __shared__ int32_t wave_tot[4], base_s;
     const int32_t i = blockIdx.x * 256 + threadIdx.x;
@@ -73,28 +100,36 @@ __global__ __launch_bounds__(256) void sweep_place_kernel(int2* list, int32_t* _
     for (int w = 0; w < wave; ++w) at += wave_tot[w];
     if (i >= lists) return;
     list[i].x = at;
+    if (c >= hubs.longest)
+        for (int32_t r = 0; r < hubs.n_rules; ++r)
+            if (hubs.list[r] == i / hubs.n) {
+                const int32_t q = atomicAdd(&ctl->n_hubs, 1);
+                if (q < kSwMaxHubs) ctl->hub[q] = make_int2(r | hubs.nt[r] << 8, i % hubs.n);
+            }
     cur[i] = 0;
     near[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
 }
 
 __global__ __launch_bounds__(256) void sweep_fill_kernel(const cfpq_edge* __restrict__ edges, int64_t m, InitArgs a,
                                                          const int2* __restrict__ list, int32_t* cur,
-                                                         uint4* near, int32_t* __restrict__ idx) {
+                                                         uint4* near, int32_t* __restrict__ idx, int32_t longest) {
     const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (e >= m) return;
     const cfpq_edge ed = edges[e];
     if (ed.src < 0 || ed.src >= a.n || ed.dst < 0 || ed.dst >= a.n || ed.label < 0 || ed.label >= a.n_terminals)
         return;  // counted by the scatter
-    auto put = [&](int64_t i, int32_t k) {
+    auto put = [&](int32_t i, int32_t k) {
         const int2 l = list[i];
-        const int32_t nth = atomicAdd(cur + i, 1);
+        // (hubs' lists come out sorted; the others stay in the order of the
+        // atomics, which spreads the bits that a scatter sets together)
+        const int32_t nth = l.y >= longest ? count_up(cur, 1, i) : atomicAdd(cur + i, 1);
         idx[l.x + nth] = k;
         put_near(reinterpret_cast<uint16_t*>(near + i), nth, l.y, k);
     };
     for (int32_t q = 0; q < a.n_term; ++q) {
         if (a.term[q].label != ed.label) continue;
-        if (a.term[q].out >= 0) put(static_cast<int64_t>(a.term[q].out) * a.n + ed.src, ed.dst);
-        if (a.term[q].in >= 0) put(static_cast<int64_t>(a.term[q].in) * a.n + ed.dst, ed.src);
+        if (a.term[q].out >= 0) put(a.term[q].out * a.n + ed.src, ed.dst);
+        if (a.term[q].in >= 0) put(a.term[q].in * a.n + ed.dst, ed.src);
     }
 }
 
@@ -166,7 +201,12 @@ __device__ __forceinline__ bool pull_list(const uint64_t* src, int64_t W, const 
 // every dynamic nonterminal and is their only writer.
 //  1. Pulls, a wavefront a row: per head the changed rows its lists select
 //     (in the first loop rows of T, which hold the initial bits, in later ones
-//     the last loop's D) and P's row; the new bits are stored at once.
+//     the last loop's D) and P's row; the new bits are stored at once.  A hub's
+//     rows (a list of many entries: up to 32 MiB, which one workgroup takes
+//     600 us for) are pulled by all workgroups, 64 entries a wavefront, into
+//     an inbox row that its own workgroup takes over a loop later (a star of
+//     16384 nodes, S -> A S | a: 1427 -> 208 us with the counters below, 428 by
+//     products).
 //  2. Scatters, per head of an rf rule: from the bits its operands gained in
 //     step 1 (an operand that is itself such a head feeds a loop later, from
 //     D; in the first loop T's rows feed).  Few bits are scattered one by one
@@ -194,7 +234,9 @@ __global__ __launch_bounds__(1024) void sweep_kernel(SweepArgs a) {
     const int n_dyn = a.g.n_dyn;
     const int cur = a.t & 3, prev = (a.t - 1) & 3, next = (a.t + 1) & 3;
     SweepCtl* ctl = a.ctl;
-    const uint32_t any_prev = kFirst ? ~0u : ctl->any[prev];
+    uint32_t any_prev = kFirst ? ~0u : ctl->any[prev];
+    if (kFirst && (WPL <= 2 || ctl->n_hubs == 0 || ctl->n_hubs > kSwMaxHubs)) any_prev &= ~kSwHubsBit;
+    const auto hubs = [&] { return WPL > 2 && (any_prev & kSwHubsBit) != 0; };
     if (blockIdx.x == 0) {
         for (int64_t x = threadIdx.x; x < n_dyn * W; x += blockDim.x) a.chg[next * n_dyn * W + x] = 0;
         if (threadIdx.x < kSwMaxDyn) ctl->gained[next][threadIdx.x] = 0;
@@ -296,6 +338,7 @@ __global__ __launch_bounds__(1024) void sweep_kernel(SweepArgs a) {
                 continue;
             }
             const int2 l = a.list[i];
+            if (hubs() && l.y >= hub_list(W)) continue;
             if (whole || l.y <= kLongPull)
                 got |= pull_list<WPL>(src, W, off, lane, l, whole ? wave : 0, whole ? 16 : 1, a.idx, live, acc);
             else
@@ -349,6 +392,58 @@ __global__ __launch_bounds__(1024) void sweep_kernel(SweepArgs a) {
         }
     }
 
+    // hubs: what the last loop left in the inbox of this workgroup's rows, then
+    // this workgroup's part of their lists, as far as T lacks it
+    if (hubs()) {
+        const int32_t n_hubs = ctl->n_hubs;
+        auto* inbox = reinterpret_cast<uint64_t*>(ctl + 1);  // [2][kSwMaxHubs][W], by loop parity
+        for (int q = 0; q < n_hubs; ++q) {  // uniform over the workgroup
+            const int lr = ctl->hub[q].y - row0, r = ctl->hub[q].x & 255;
+            if (r >= a.g.n_lf) continue;
+            if (kFirst || !(any_prev & kSwInboxBit) || lr < 0 || lr >= nrows) continue;
+            if (wave == 0) {
+                uint64_t* in = inbox + (static_cast<int64_t>(prev & 1) * kSwMaxHubs + q) * W;
+                uint64_t acc[WPL];
+#pragma unroll
+                for (int u = 0; u < WPL; ++u) {
+                    acc[u] = in[off[u]];
+                    if (valid[u]) in[off[u]] = 0;
+                }
+                commit(a.g.lf[r].head, lr, acc);
+            }
+            __syncthreads();
+        }
+        for (int q = 0; q < n_hubs; ++q) {
+            const int r = ctl->hub[q].x & 255;
+            if (r >= a.g.n_lf) continue;
+            const auto rule = a.g.lf[r];
+            const int c = rule.right;
+            if (kFirst ? !((a.g.init_mask >> c) & 1u) : !((any_prev >> c) & 1u)) continue;
+            const int32_t node = ctl->hub[q].y;
+            const int2 l = a.list[static_cast<int64_t>(rule.left) * a.n + node];
+            const uint64_t* src = kFirst ? a.T + a.g.dyn_nt[c] * a.mat_words : a.Dprev + c * a.mat_words;
+            auto live = [&](int32_t k) { return kFirst || ((marks[c * W + (k >> 6)] >> (k & 63)) & 1ull) != 0; };
+            uint64_t acc[WPL];
+#pragma unroll
+            for (int u = 0; u < WPL; ++u) acc[u] = 0;
+            if (!pull_list<WPL>(src, W, off, lane, l, static_cast<int>(blockIdx.x + gridDim.x * wave),
+                                static_cast<int>(16 * gridDim.x), a.idx, live, acc))
+                continue;
+            const uint64_t* trow = a.T + a.g.dyn_nt[rule.head] * a.mat_words + static_cast<int64_t>(node) * W;
+            auto* in = reinterpret_cast<unsigned long long*>(
+                inbox + (static_cast<int64_t>(cur & 1) * kSwMaxHubs + q) * W);
+            bool fresh = false;
+#pragma unroll
+            for (int u = 0; u < WPL; ++u) {
+                const uint64_t nw = valid[u] ? acc[u] & ~trow[off[u]] : 0;
+                if (nw == 0) continue;
+                fresh = true;
+                atomicOr(in + off[u], static_cast<unsigned long long>(nw));
+            }
+            if (__ballot(fresh) != 0 && lane == 0) atomicOr(&any_s, kSwInboxBit);
+        }
+    }
+
     // ---- 2. scatters
     const uint64_t all_rows = nrows == 64 ? ~0ull : (1ull << nrows) - 1;
     // rows of operand h that feed this loop's scatters, and where they are
@@ -360,6 +455,29 @@ __global__ __launch_bounds__(1024) void sweep_kernel(SweepArgs a) {
     auto feed_row = [&](int h, int lr) -> const uint64_t* {
         if (kFirst) return T_row(h, lr);
         return (late(h) ? a.Dprev : a.Dcur) + h * a.mat_words + static_cast<int64_t>(row0 + lr) * W;
+    };
+    // The hubs of rf rule r among the bits f: their lists are rows of the operand's
+    // matrix, ORed in whole.  Entry by entry the bits of one word wait for each
+    // other: the first loop of a star of 16384 nodes, S -> S A | a, 218 us, and 861
+    // with its list in order; 75 so.
+    auto hub_bits = [&](int r, uint64_t (&f)[WPL], uint64_t* xrow) {
+        for (int q = 0; q < ctl->n_hubs; ++q) {
+            if ((ctl->hub[q].x & 255) != a.g.n_lf + r) continue;
+            const int32_t k = ctl->hub[q].y;
+            bool mine = false;
+#pragma unroll
+            for (int u = 0; u < WPL; ++u)
+                if (lane + 64 * u == k >> 6 && ((f[u] >> (k & 63)) & 1ull)) {
+                    mine = true;
+                    f[u] &= ~(1ull << (k & 63));
+                }
+            if (__ballot(mine) == 0) continue;
+            const uint64_t* row = a.T + (ctl->hub[q].x >> 8) * a.mat_words + static_cast<int64_t>(k) * W;
+#pragma unroll
+            for (int u = 0; u < WPL; ++u)
+                if (valid[u]) atomicOr(reinterpret_cast<unsigned long long*>(xrow + off[u]),
+                                       static_cast<unsigned long long>(row[off[u]]));
+        }
     };
     // the first loop's heads of ll rules alone come first: they may feed the others
     const uint32_t only_ll = kFirst ? a.g.ll_mask & ~a.g.rf_mask : 0;
@@ -403,6 +521,7 @@ __global__ __launch_bounds__(1024) void sweep_kernel(SweepArgs a) {
                     uint64_t f[WPL];
 #pragma unroll
                     for (int q = 0; q < WPL; ++q) f[q] = valid[q] ? frow[off[q]] : 0;
+                    if (hubs()) hub_bits(r, f, xrow);
                     const int64_t l = static_cast<int64_t>(a.g.rf[r].right) * a.n;
 #pragma unroll
                     for (int q = 0; q < WPL; ++q)
@@ -498,6 +617,7 @@ __global__ __launch_bounds__(1024) void sweep_kernel(SweepArgs a) {
     }
     __syncthreads();
     if (threadIdx.x == 0 && any_s != 0) {
+        if (hubs()) any_s |= kSwHubsBit;
         const uint32_t have = __hip_atomic_load(&ctl->any[cur], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if ((any_s & ~have) != 0) atomicOr(&ctl->any[cur], any_s);
     }
@@ -624,9 +744,20 @@ hipError_t launch_sweep_init(const SweepGrammar& g, const SweepBuffers& b, const
     if (g.n_list > 0) {
         // also without edges: the sweeps read every node's 16-byte form, written here
         const int32_t lists = g.n_list * L.n;
+        HubArgs hubs{};
+        hubs.n = L.n;
+        hubs.longest = hub_list(L.W);
+        for (int r = 0; sweep_hubs(L) && r < g.n_lf + g.n_rf; ++r) {
+            const uint8_t l = r < g.n_lf ? g.lf[r].left : g.rf[r - g.n_lf].right;
+            hubs.list[hubs.n_rules] = l;
+            for (int q = 0; q < g.n_term; ++q)
+                if (g.term[q].out == l) hubs.nt[hubs.n_rules] = static_cast<uint8_t>(g.term[q].nt);
+            ++hubs.n_rules;
+        }
         sweep_place_kernel<<<dim3(static_cast<unsigned>((lists + 255) / 256)), dim3(256), 0, s>>>(b.list, b.cur, b.near,
-                                                                                                 lists, b.ctl);
-        if (m > 0) sweep_fill_kernel<<<eg, dim3(256), 0, s>>>(edges, m, a, b.list, b.cur, b.near, b.idx);
+                                                                                                 lists, b.ctl, hubs);
+        const int32_t longest = sweep_hubs(L) ? hub_list(L.W) : INT32_MAX;
+        if (m > 0) sweep_fill_kernel<<<eg, dim3(256), 0, s>>>(edges, m, a, b.list, b.cur, b.near, b.idx, longest);
     }
     return hipGetLastError();
 }

@@ -77,17 +77,35 @@ inline int32_t sweep_groups(int32_t n) { return (n + sweep_rows(n) - 1) / sweep_
 // False when the grammar is beyond the tables above.
 bool sweep_grammar(const cfpq_grammar* gr, SweepGrammar* out);
 
+// Hubs: lists whose rows make this many words and more.  They are pulled by all
+// workgroups together, or scattered as a row of their matrix (kernels_sweep.hip);
+// at most kSwMaxHubs of them, or none is.
+constexpr int64_t kSwHubWords = 512 * 1024;
+constexpr int kSwMaxHubs = 32;
+// In SweepCtl::any beside the mask: rows wait in the inbox; there are hubs (set
+// with some other bit only, so that 0 is still the fixpoint).
+constexpr uint32_t kSwInboxBit = 1u << 31, kSwHubsBit = 1u << 30;
+// Looked for above 8192 nodes: below, a list is at most 8 MiB of rows, and the
+// code for them costs the sweeps 2% (dense loops at 7001 nodes 26.6 -> 27.2 us).
+inline bool sweep_hubs(const Layout& L) { return L.W > 128; }
+
 // Control block on the device.  Flags and counts of loop t are at index t & 3;
 // each loop clears the next one's.
-struct SweepCtl {
+struct alignas(256) SweepCtl {
     uint32_t any[4];                          // mask of the dynamic nonterminals that changed
     unsigned long long gained[4][kSwMaxDyn];  // bits gained (grammars with dd rules)
     int32_t loops;                            // loops executed
     int32_t bad_edges;
     int64_t products, sparse, delta, dense;   // rules run, by kind
     int32_t list_top;                         // bump allocator of the adjacency lists
-    int32_t pad;
+    int32_t n_hubs;                           // entries of hub that would be used
+    int2 hub[kSwMaxHubs];                     // lf rule, or n_lf + rf rule, | fixed operand << 8; node
 };
+
+// The inbox follows the control block: [2][kSwMaxHubs][W], by loop parity.
+inline size_t sweep_inbox_bytes(const Layout& L) {
+    return sweep_hubs(L) ? static_cast<size_t>(2) * kSwMaxHubs * L.W * 8 : 0;
+}
 
 // What the host reads while loops are in flight (pinned host memory).
 struct SweepReport {
