@@ -392,7 +392,9 @@ CFPQ_API cfpq_status cfpq_conjunctive_workspace_bytes(const cfpq_graph* graph, c
  * tile and no max_iters, at most 16384 nodes, and no rule that reads the head
  * of a rule with k >= 2, the one-conjunct rules are closed first, as
  * cfpq_closure does with its default options (environment included), and the
- * other rules run once, counted as one more loop.
+ * other rules run once, counted as one more loop.  An out-of-range device edge
+ * is then reported as by cfpq_closure: the call returns CFPQ_EINVAL after the
+ * one-conjunct rules have run on the other edges.
  */
 CFPQ_API cfpq_status cfpq_conjunctive_closure(const cfpq_graph* graph, const cfpq_grammar* grammar,
                                               int32_t n_conj_rules, const cfpq_conj_rule* conj_rules,
@@ -535,11 +537,12 @@ CFPQ_API cfpq_status cfpq_batch_tune_set(const cfpq_batch_tune_entry* entry);
  * the dirty worklist, instances of 513 to 4096 nodes with at most 16 edges per
  * padded row and a grammar of at most 32 binary and 32 terminal rules run as
  * row sweeps, whatever tile their route names: only rules over two growing
- * operands are multiplied (256 x 256 tiles).
+ * operands are multiplied (256 x 256 tiles).  (With several such rules those
+ * of more than 2048 nodes and two edges a node stay on their route.)
  * Results are bit-identical to cfpq_closure on each instance alone.  opt:
- * schedule must be INPLACE and warm_start 0; dirty_worklist, capture,
- * hybrid and max_iters apply to every instance; path, tile and profile are
- * ignored.  Instances are limited to 2^19 nodes.
+ * schedule must be INPLACE and warm_start 0; dirty_worklist, hybrid and
+ * max_iters apply to every instance, capture to those that run as tiles; path,
+ * tile and profile are ignored.  Instances are limited to 2^19 nodes.
  * stats: NULL or n_instances entries (device_ms is the whole batch's time).
  * Device edges are checked by the initialisation kernel, which skips an
  * out-of-range edge; the call then returns CFPQ_EINVAL naming the instance,

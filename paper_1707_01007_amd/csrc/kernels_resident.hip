@@ -59,7 +59,6 @@ constexpr int32_t kTileBits = L == 4 ? 16384 : L == 2 ? 8192 : 4096;
 template <int L>
 constexpr int32_t kTurnBits = L == 1 ? 1 : 4;
 
-// kDD: the slots have dd rules.  kTurn: their LDS may hold transposed operands.
 // Following single facts: while a loop gains only a few bits (two cycles, a
 // chain: thousands of loops of one or two), one wavefront applies the rules to
 // those instead of to all rows: a bit (i, j) of C gives A -> B C the bits (k, j)
@@ -195,6 +194,7 @@ __device__ __forceinline__ void follow_facts(const Rules& u, FactQueue& q, uint3
     }
 }
 
+// kDD: the slots have dd rules.  kTurn: their LDS may hold transposed operands.
 // d: the slot's descriptor, grammar: where its rules would be, out: its state.
 template <int L, bool kDD, bool kTurn>
 __device__ __forceinline__ void resident_closure(const SlotDesc& d, const int32_t* __restrict__ grammar,

@@ -651,7 +651,7 @@ __global__ void sweep_report_kernel(const SweepCtl* __restrict__ ctl, int32_t t,
 
 template <int WPL, bool kFirst>
 hipError_t sweep_launch(const SweepArgs& a, dim3 grid, size_t lds, hipStream_t s) {
-    // more than 64 KiB of dynamic LDS has to be asked for, once per kernel and device
+    // more than 64 KiB of dynamic LDS has to be asked for
     if (lds > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sweep_kernel<WPL, kFirst>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
