@@ -106,6 +106,15 @@ bool sweep_route(const cfpq_graph* g, const cfpq_grammar* gr, const cfpq_options
     SweepGrammar sg;
     if (!sweep_grammar(gr, &sg)) return false;
     if (sg.n_dd > 0 && g->n_nodes > kMfmaMaxNodes) return false;
+    // Only rules of two growing operands: a sweep has nothing of its own to add,
+    // and its products, which see a loop's bits in the next one, take more
+    // loops than the product loops, which work in place.  From 8193 nodes the
+    // products are what a closure costs.  S -> S S, times of the sweeps over
+    // the loops': chains 0.9 to 1.2 at 8000 nodes, 1.3 to 2.0 from 9000
+    // (16000: 10.4 ms against 5.3), grids 1.07 and 1.02 to 1.2, random graphs
+    // of 15 edges a node 1.26 and 1.4 to 1.5; trees and components of 20
+    // nodes, which end after five cheap loops, 0.8 and 0.9.
+    if (sg.n_dd > 0 && sg.n_lf == 0 && sg.n_rf == 0 && g->n_nodes > kSwLoopNodes) return false;
     return true;
 }
 

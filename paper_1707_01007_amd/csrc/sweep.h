@@ -36,6 +36,7 @@ constexpr int kSwMaxRules = 32;      // rules with a fixed operand, per kind
 constexpr int kSwMaxDyn = 8;         // nonterminals that head a binary rule
 constexpr int kSwMaxLists = 32;      // adjacency lists of fixed operands, outgoing and incoming
 constexpr int kSwMaxTerm = 32;       // terminal rules
+constexpr int32_t kSwLoopNodes = 8192;  // past them a grammar of growing pairs alone keeps the product loops
 constexpr int64_t kSwMaxWords = 256;  // words per row (16384 nodes): 64 rows of them fill 132 of the 160 KiB of LDS
 
 // Edges up to which the adjacency lists are reserved (each edge may enter several).
