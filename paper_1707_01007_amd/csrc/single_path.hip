@@ -304,6 +304,7 @@ __global__ __launch_bounds__(256) void minplus_kernel(const uint64_t* __restrict
 constexpr int32_t kPowMaxLength = 16;
 constexpr int kPowStep = 8, kPowBias = 67;
 constexpr uint32_t kCellsMaxLength = 127;  // of minplus_cells_kernel, below
+constexpr double kShortRows = 0.3;         // of the row walk's estimate, where the rows may be short
 constexpr int kCellsWords = 16;
 typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 
@@ -1121,7 +1122,12 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
         // X_B in it) pair, against 20 T (i, j, k) terms/s over the active tiles
         // on the VALU or, while no operand length exceeds 16 (the longest so
         // far was read back with the flags), the matrix cores' time.
-        const bool powers = p.any_tiles && flags[n_nt + 1] <= kPowMaxLength;
+        // No rule's tiles take as long as the least that the powers or the cell
+        // walk take (0.7 tile_ms >= 0.02, see below: from 769 nodes on): neither
+        // is asked for, and the longest length is not tracked for them (50 nodes:
+        // 370 us a closure against 390).
+        const bool others = p.any_tiles && 0.7 * static_cast<double>(L.W * L.W * kchunks) * 131072.0 / 2e10 >= 0.02;
+        const bool powers = others && flags[n_nt + 1] <= kPowMaxLength;
         // 128 x 128 tiles, 2 T terms/s a workgroup and at best 500 over the
         // chip, after a pass over the lengths (4 bytes a cell at 3 TB/s)
         auto pow_ms = [&](int32_t active) {
@@ -1131,7 +1137,7 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
         };
         // the cell walk: the operand bytes, the words of D, and 0.55 ns a cell
         // at n = 4096 (0.3 to 0.5 where new cells fill words; n = 8192: 0.76)
-        const bool cells_fit = p.any_tiles && static_cast<uint32_t>(flags[n_nt + 1]) <= kCellsMaxLength;
+        const bool cells_fit = others && static_cast<uint32_t>(flags[n_nt + 1]) <= kCellsMaxLength;
         auto cells_walk_ms = [&](unsigned long long cells) {
             return 0.03 + static_cast<double>(L.npad) * L.npad * 3e-9 +
                    static_cast<double>(cells) * (1.4e-7 + 1e-10 * L.npad);
@@ -1169,7 +1175,7 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
                 const double best_ms = pow ? pow_ms(tiles[br.lhs]) : tile_ms;
                 // (rows_ms is high by up to 6 where rows are short: 27 us
                 // against 164 at n = 4096 and 16 k bits)
-                if (cells_fit && cells_walk_ms(dcount[br.lhs]) < std::min(0.3 * rows_ms, best_ms)) {
+                if (cells_fit && cells_walk_ms(dcount[br.lhs]) < std::min(kShortRows * rows_ms, best_ms)) {
                     CFPQ_HIP(bytes(br, false));
                     const int64_t wgs = (p.L.mat_words + kCellsWords - 1) / kCellsWords;
                     minplus_cells_kernel<<<dim3(static_cast<unsigned>(std::min<int64_t>(wgs, 65536))), dim3(256), 0,
@@ -1178,7 +1184,10 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
                     CFPQ_HIP(hipGetLastError());
                     continue;
                 }
-                rows = rows_ms < best_ms;
+                // so much that of the two the powers of two have to win by as much:
+                // 3000 nodes, one edge a node: 36 us for the rows (130 by the
+                // estimate), 104 for the powers (89)
+                rows = (pow ? kShortRows * rows_ms : rows_ms) < best_ms;
                 on_tiles[r] = rows ? 0 : pow ? 2 : 1;
             }
             if (rows) {
