@@ -304,7 +304,6 @@ __global__ __launch_bounds__(256) void minplus_kernel(const uint64_t* __restrict
 constexpr int32_t kPowMaxLength = 16;
 constexpr int kPowStep = 8, kPowBias = 67;
 constexpr uint32_t kCellsMaxLength = 127;  // of minplus_cells_kernel, below
-constexpr double kShortRows = 0.3;         // of the row walk's estimate, where the rows may be short
 constexpr int kCellsWords = 16;
 typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 
@@ -1175,7 +1174,7 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
                 const double best_ms = pow ? pow_ms(tiles[br.lhs]) : tile_ms;
                 // (rows_ms is high by up to 6 where rows are short: 27 us
                 // against 164 at n = 4096 and 16 k bits)
-                if (cells_fit && cells_walk_ms(dcount[br.lhs]) < std::min(kShortRows * rows_ms, best_ms)) {
+                if (cells_fit && cells_walk_ms(dcount[br.lhs]) < std::min(0.3 * rows_ms, best_ms)) {
                     CFPQ_HIP(bytes(br, false));
                     const int64_t wgs = (p.L.mat_words + kCellsWords - 1) / kCellsWords;
                     minplus_cells_kernel<<<dim3(static_cast<unsigned>(std::min<int64_t>(wgs, 65536))), dim3(256), 0,
@@ -1184,10 +1183,10 @@ cfpq_status cfpq_single_path(const cfpq_graph* graph, const cfpq_grammar* gramma
                     CFPQ_HIP(hipGetLastError());
                     continue;
                 }
-                // so much that of the two the powers of two have to win by as much:
-                // 3000 nodes, one edge a node: 36 us for the rows (130 by the
-                // estimate), 104 for the powers (89)
-                rows = (pow ? kShortRows * rows_ms : rows_ms) < best_ms;
+                // and the powers of two have to win against 0.6 of it: 3000 nodes,
+                // one edge a node, 36 us for the rows (130 by the estimate) and 104
+                // for the powers (89); 1000 nodes, few long rows, 95 and 30
+                rows = (pow ? 0.6 * rows_ms : rows_ms) < best_ms;
                 on_tiles[r] = rows ? 0 : pow ? 2 : 1;
             }
             if (rows) {
