@@ -32,7 +32,6 @@ struct BatchPlan {
     std::vector<GroupSlot> group_slots;  // their descriptors, pointers still to come
     std::vector<size_t> group_off;       // their workspace in the tt region
     GroupLists group_lists;
-    std::vector<char> swept;       // by slot: runs in one of the two sweeps
     std::vector<int32_t> all_ids;  // the slots whose matrices the batch initialises (not the resident sweep's)
     std::vector<int64_t> edge_begin;
     std::vector<size_t> edge_copy_off;  // per slot: byte offset in the edge region, or SIZE_MAX (device edges)
@@ -58,7 +57,6 @@ bool group_takes(const cfpq_instance& inst, const cfpq_options& o, GroupGrammar*
 cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options& o, BatchPlan& p,
                        const RouteMap* overrides = nullptr, bool jacobi_resident = false, bool sweeps = true) {
     p.n = n;
-    p.swept.assign(n, 0);
     p.descs.resize(n);
     p.edge_copy_off.assign(n, SIZE_MAX);
     p.tt_off.assign(n, 0);
@@ -169,7 +167,6 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
         if (d.n_rules == 0) {
             // nothing to iterate: initialisation only
         } else if (swept) {
-            p.swept[i] = 1;
             continue;  // initialised by group_init
         } else if (d.kind == kSlotLarge) {
             p.large.push_back(i);
@@ -180,7 +177,6 @@ cfpq_status plan_batch(int32_t n, const cfpq_instance* inst, const cfpq_options&
             p.sweep[rp.cls].push_back(i);
             if (n == 1) p.solo = rp;
             p.sweep_lds[rp.cls] = std::max(p.sweep_lds[rp.cls], rp.lds);
-            p.swept[i] = 1;
             continue;  // initialised by its workgroup
         } else if (d.W == 4) {
             p.small8.push_back(i);
@@ -752,7 +748,11 @@ static cfpq_status run_batch(int32_t n_instances, const cfpq_instance* instances
         }
     }
     if (cut->empty()) return CFPQ_OK;
-    const auto swept_end = std::stable_partition(cut->begin(), cut->end(), [&](int32_t i) { return p.swept[i] != 0; });
+    std::vector<char> swept(n_instances, 0);  // ran in one of the two sweeps
+    for (int32_t i : p.group) swept[i] = 1;
+    for (const auto& ids : p.sweep)
+        for (int32_t i : ids) swept[i] = 1;
+    const auto swept_end = std::stable_partition(cut->begin(), cut->end(), [&](int32_t i) { return swept[i] != 0; });
     *n_swept = static_cast<size_t>(swept_end - cut->begin());
     return fail(CFPQ_ENOTCONV, "max_iters reached before the fixpoint in some instance");
 }

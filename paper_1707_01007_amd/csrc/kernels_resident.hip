@@ -867,8 +867,10 @@ hipError_t launch(const EngineBuffers& b, const int32_t* ids, int32_t count, int
 
 bool resident_rules(const cfpq_grammar* gr, bool queue, ResidentPlan* plan) {
     const int32_t n_bin = gr->n_bin_rules, n_term = gr->n_term_rules;
-    std::memset(&plan->g, 0, sizeof(plan->g));
-    if (n_bin < 1 || n_bin > kRsMaxBin) return false;
+    if (n_bin < 1 || n_bin > kRsMaxBin) {
+        std::memset(&plan->g, 0, sizeof(plan->g));
+        return false;
+    }
     int32_t rules[3 * kRsMaxBin];
     for (int32_t r = 0; r < n_bin; ++r) {
         rules[3 * r] = gr->bin_rules[r].lhs;
