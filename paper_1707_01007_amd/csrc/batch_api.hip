@@ -443,7 +443,7 @@ static cfpq_status solo_run(BatchPlan& p, const cfpq_instance& inst, hipStream_t
     void* pb = nullptr;
     CFPQ_HIP(pinned_readback(at + kSoloEdgeBytes, &pb));
     auto* report = static_cast<ResidentReport*>(pb);
-    report->loop = 0;
+    report->dense = report->loop = 0;
     d.T = inst.d_result;
     d.edges = inst.graph.edges;
     if (by_copy) {

@@ -831,7 +831,7 @@ __global__ __launch_bounds__(threads_for(L)) void resident_solo_kernel(SlotDesc 
     if (threadIdx.x != 0) return;
     report->iterations = st.iterations;
     report->products = st.products;
-    report->dense = st.dense;
+    if constexpr (kDD) report->dense = st.dense;
     report->capped = st.capped;
     report->bad_edges = st.bad_edges;
     report->ticks = wall_clock64() - begin;
